@@ -332,6 +332,8 @@ static sp24_status mm_dispatch(const MmArgs& a, hipStream_t st)
         s = launch_mm_skinny(a, st, &handled);
         if (handled) return s;
     }
+    s = launch_mm_ksplit(a, st, &handled);
+    if (handled) return s;
     return launch_mm_simple(a, st);
 }
 

@@ -56,6 +56,9 @@ struct MmArgs {
 // General kernel: any M, N; both layouts; both B orders.  One wavefront per 32x32 tile of D.
 sp24_status launch_mm_simple(const MmArgs& a, hipStream_t st);
 
+// N-major B at any alignment, K split across the wavefronts of a workgroup; false in *handled for other problems.
+sp24_status launch_mm_ksplit(const MmArgs& a, hipStream_t st, bool* handled);
+
 // Streaming kernel for N <= 32; returns false in *handled when the problem does not fit it.
 sp24_status launch_mm_skinny(const MmArgs& a, hipStream_t st, bool* handled);
 

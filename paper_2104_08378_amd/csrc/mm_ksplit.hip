@@ -1,0 +1,281 @@
+// Products with an N-major B whose rows start at any address (an odd number of columns, or a view with an odd
+// pitch): the activations that a previous product left as [features, tokens] for a prompt of arbitrary length.
+// The tiled kernels' transfers go straight from memory to LDS and need 16-byte aligned rows; here B passes through
+// registers, loaded 16 bytes per lane from wherever the row starts, and is written to LDS aligned.
+//
+// One workgroup per 64 x 64 tile of D, eight wavefronts that split K among themselves: 64-column tile kb goes to
+// wavefront kb % 8, each accumulates a whole 64 x 64 partial tile, and the eight are added through LDS in wavefront
+// order.  Such products have few tiles (1024 x 509: 128) and would be bound by the latency of their loads; with K
+// split eight ways every compute unit keeps eight times the bytes in flight, and a wavefront's LDS image of B is
+// its own, so the loop has no barrier at all.  The compressed (or dense) first operand goes from memory into
+// registers in the matrix instruction's own lane order.
+//
+// Measured against the general kernel that took these products before (us, operands rotating; the aligned N next to
+// each on the tiled kernels in brackets): 1024 x 509 x 4096 int8 482 -> 15.8; 8192 x 17 x 8192 bf16 443 -> 32.9;
+// 4096 x 1155 x 4096 bf16 676 -> 93 [N = 1152: 36], int8 856 -> 67 [23]; 3744 x 5453 x 1984 f8 1559 -> 171 [43].  On
+// many tiles it is bound by the loads: a 64 x 64 tile moves twice the operand bytes per product of a 128 x 128 one.
+#include "mm_tiled.hpp"
+
+#include <cstring>
+
+namespace sp24 {
+
+namespace {
+
+constexpr int kSplitWaves = 8;
+constexpr int TM = 2, TN = 2;                       // 32 x 32 accumulator tiles per wavefront
+
+// 16 bytes from any address (one dwordx4 load)
+__device__ __forceinline__ uint4v load16_any(const uint8_t* p)
+{
+    uint4v v;
+    __builtin_memcpy(&v, p, 16);
+    return v;
+}
+
+// the value's bytes moved down by `bytes` (0 .. 15), zeros on top
+__device__ __forceinline__ uint4v shift_down(uint4v v, int bytes)
+{
+    unsigned __int128 x = __builtin_bit_cast(unsigned __int128, v);
+    x >>= 8 * bytes;
+    return __builtin_bit_cast(uint4v, x);
+}
+
+// between a wavefront's own LDS writes and reads: the LDS serves them in order, only the compiler must keep it
+__device__ __forceinline__ void wave_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// result element (m, n) from the accumulated value
+template <int DT, typename ACC>
+__device__ __forceinline__ void put(const MmArgs& a, int64_t m, int64_t n, ACC v)
+{
+    const int64_t at = m * a.ldd + n;
+    if constexpr (DT == SP24_I8) {
+        float s = 0.0f, b = 0.0f;
+        if (a.out != SP24_I32) epilogue_row(a.epi, m, s, b);
+        if (a.out == SP24_I32) store_bits<SP24_I32>(a.D, at, (uint32_t)v);
+        else if (a.out == SP24_I8) store_bits<SP24_I8>(a.D, at, output_bits<SP24_I8>(v, s, b, a.epi));
+        else if (a.out == SP24_F32) store_bits<SP24_F32>(a.D, at, output_bits<SP24_F32>(v, s, b, a.epi));
+        else if (a.out == SP24_F16) store_bits<SP24_F16>(a.D, at, output_bits<SP24_F16>(v, s, b, a.epi));
+        else store_bits<SP24_BF16>(a.D, at, output_bits<SP24_BF16>(v, s, b, a.epi));
+    } else {
+        if (a.out == SP24_F32) store_out<SP24_F32>(a.D, at, v);
+        else if (a.out == SP24_F16) store_out<SP24_F16>(a.D, at, v);
+        else store_out<SP24_BF16>(a.D, at, v);
+    }
+}
+
+} // namespace
+
+template <int DT, bool SPARSE>
+__global__ __launch_bounds__(64 * kSplitWaves) void k_mm_ksplit(MmArgs a, int tiles_m, int tiles_n)
+{
+    constexpr int ES = is8<DT> ? 1 : 2;
+    constexpr int BM = 32 * TM, BN = 32 * TN;
+    constexpr int kRowB = BN * ES, kChunks = kRowB / 16;      // a K row of B in LDS: bytes, 16-byte chunks
+    constexpr int kImage = 64 * kRowB;                        // 64 K rows
+    constexpr int NJ = kImage / 1024;                         // 16-byte pieces of the image per lane
+    constexpr int kRowsPerPiece = 64 / kChunks;               // K rows from a lane's piece to its next
+    constexpr int NA = SPARSE ? (ES == 1 ? 1 : 2) : 2 * ES;   // 16-byte pieces of a row block of A per lane and tile
+    using acc_t = typename acc_of<DT>::type;
+    constexpr int kRedBytes = kSplitWaves * 16 * 64 * 4;
+    constexpr int kLds = kSplitWaves * kImage > kRedBytes ? kSplitWaves * kImage : kRedBytes;
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[kLds];
+
+    int tm, tn;
+    tile_of_workgroup(tiles_m, tiles_n, tm, tn);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 31, q = lane >> 5;
+    const int64_t K = a.K, tiles_k = (K + 63) / 64;
+
+    // ---- B: this lane's pieces of a tile's image are rows row0, row0 + kRowsPerPiece, ..., chunk c of each ----
+    const int64_t ldb = a.ldb * ES, col0 = (int64_t)tn * BN * ES;                 // bytes
+    const int64_t b_bytes = (K - 1) * ldb + a.N * ES;                             // from B to its last element's end
+    const int row0 = lane / kChunks, c = lane % kChunks;
+    const int valid = (int)min((int64_t)kChunks, (a.N * ES - col0 + 15) / 16);    // chunks that hold columns of the matrix
+    const int64_t src0 = col0 + min(c, valid - 1) * 16;                           // byte of a row; past the last chunk: never stored
+    const int64_t tile_reach = 63 * ldb + col0 + (valid - 1) * 16 + 16;           // end of a tile's last piece, from the tile's first row
+    uint8_t* const image = lds + wave * kImage;
+    const int dst0 = row0 * kRowB + ((c ^ nmajor_swizzle<ES>(row0, kChunks)) << 4);
+    static_assert(kRowsPerPiece % 8 == 0, "the swizzle is the same for all of a lane's pieces");
+    const uint8_t* const Bp = reinterpret_cast<const uint8_t*>(a.B);
+    auto load_b = [&](int64_t kb, uint4v (&v)[NJ]) {
+        const int64_t first = kb * 64 * ldb;
+        if (kb * 64 + 64 <= K && first + tile_reach <= b_bytes) {
+            const uint8_t* p = Bp + first + row0 * ldb + src0;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) v[j] = load16_any(p + j * kRowsPerPiece * ldb);
+        } else {
+            // the last rows: pieces that would end past the last element are read up to it and moved into place,
+            // rows past K are zeros
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const int64_t k = kb * 64 + row0 + j * kRowsPerPiece;
+                const int64_t at = min(k, K - 1) * ldb + src0;
+                const int64_t over = max((int64_t)0, at + 16 - b_bytes);
+                const uint4v x = shift_down(load16_any(Bp + at - over), (int)over);
+                v[j] = k < K ? x : uint4v{0u, 0u, 0u, 0u};
+            }
+        }
+    };
+    nmajor_frags<BN, TN, ES> frags;
+    frags.init(0, lane);
+
+    // ---- A ----
+    const bool canonical = SPARSE && a.layout == SP24_LAYOUT_CANONICAL;
+    const uint8_t* a_src[TM];
+    const uint8_t* m_src[TM];
+    int64_t a_step, m_step;                                   // bytes per 64-column tile
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int64_t m = min((int64_t)tm * BM + i * 32 + r, a.M - 1);            // ragged M: a valid row, never stored
+        if constexpr (!SPARSE) {
+            a_src[i] = reinterpret_cast<const uint8_t*>(a.A) + m * a.lda * ES + 16 * q;
+            m_src[i] = nullptr;
+        } else if (canonical) {
+            a_src[i] = reinterpret_cast<const uint8_t*>(a.A) + m * (K / 2 * ES) + 16 * ES * q;
+            m_src[i] = reinterpret_cast<const uint8_t*>(a.meta) + m * (K / 8) + 4 * q;
+        } else {
+            const int64_t rb = min((int64_t)tm * TM + i, a.M / 32 - 1);
+            a_src[i] = reinterpret_cast<const uint8_t*>(a.A) + rb * (K / 64) * (1024 * ES) + lane * 16;
+            m_src[i] = reinterpret_cast<const uint8_t*>(a.meta) + rb * (K / 64) * 256 + lane * 4;
+        }
+    }
+    a_step = !SPARSE ? 64 * ES : canonical ? 32 * ES : 1024 * ES;
+    m_step = canonical ? 8 : 256;
+    const int64_t piece_step = !SPARSE ? 32 : canonical ? 16 : 1024;              // from a lane's piece of a tile to its next
+    auto load_a = [&](int64_t kb, int4v (&v)[TM][NA], uint32_t (&code)[TM]) {
+        const bool whole = kb * 64 + 64 <= K;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+#pragma unroll
+            for (int s = 0; s < NA; ++s) {
+                // first column of A that the piece holds (a piece of a row is all before K or all past it)
+                const int64_t col = kb * 64 + (SPARSE ? 32 * q + 16 * s : (32 * s + 16 * q) / ES);
+                v[i][s] = int4v{0, 0, 0, 0};
+                if (whole || col < K) v[i][s] = *reinterpret_cast<const int4v*>(a_src[i] + kb * a_step + s * piece_step);
+            }
+            code[i] = 0;
+            if constexpr (SPARSE) {
+                const uint8_t* p = m_src[i] + kb * m_step;
+                if (whole || kb * 64 + 32 * q + 32 <= K) __builtin_memcpy(&code[i], p, 4);
+                else if (kb * 64 + 32 * q < K) {              // 16 columns left
+                    uint16_t half;
+                    __builtin_memcpy(&half, p, 2);
+                    code[i] = half;
+                }
+            }
+        }
+    };
+
+    acc_t acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = acc_t{};
+
+    uint4v bv[NJ];
+    int4v av[TM][NA];
+    uint32_t code[TM];
+    if (wave < tiles_k) {
+        load_b(wave, bv);
+        load_a(wave, av, code);
+    }
+    for (int64_t kb = wave; kb < tiles_k; kb += kSplitWaves) {
+        wave_order();                                         // behind the reads of the previous tile
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) *reinterpret_cast<uint4v*>(image + dst0 + j * kRowsPerPiece * kRowB) = bv[j];
+        int4v x[TM][NA];
+        uint32_t xc[TM];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+#pragma unroll
+            for (int s = 0; s < NA; ++s) x[i][s] = av[i][s];
+            xc[i] = code[i];
+        }
+        wave_order();
+        const int64_t next = kb + kSplitWaves < tiles_k ? kb + kSplitWaves : kb;   // the last tile is loaded again, unused
+        load_b(next, bv);
+        load_a(next, av, code);
+        if constexpr (SPARSE) {
+            constexpr int NI = ES;                            // instructions per tile: 8-bit one of 64 columns, 16-bit two of 32
+#pragma unroll
+            for (int s = 0; s < NI; ++s)
+#pragma unroll
+                for (int nj = 0; nj < TN; ++nj) {
+                    const uint4v lo = frags.piece(image, s, nj), hi = frags.piece(image, s + NI, nj);
+                    int8v b;
+                    b[0] = lo[0]; b[1] = lo[1]; b[2] = lo[2]; b[3] = lo[3];
+                    b[4] = hi[0]; b[5] = hi[1]; b[6] = hi[2]; b[7] = hi[3];
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) {
+                        if (s == 0) acc[i][nj] = smfmac32<DT, 0>(x[i][0], b, acc[i][nj], (int)xc[i]);
+                        else acc[i][nj] = smfmac32<DT, 1>(x[i][NA - 1], b, acc[i][nj], (int)xc[i]);
+                    }
+                }
+        } else {
+#pragma unroll
+            for (int s = 0; s < NA; ++s)
+#pragma unroll
+                for (int nj = 0; nj < TN; ++nj) {
+                    const int4v b = __builtin_bit_cast(int4v, frags.piece(image, s, nj));
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) acc[i][nj] = mfma32<DT>(x[i][s], b, acc[i][nj]);
+                }
+        }
+    }
+
+    // the eight partial tiles, added in wavefront order, one 32 x 32 block at a time
+    uint32_t (*red)[16][64] = reinterpret_cast<uint32_t (*)[16][64]>(lds);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            __syncthreads();                                  // the images, or the previous block, are done with
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                auto v = acc[i][j][e];
+                red[wave][e][lane] = __builtin_bit_cast(uint32_t, v);
+            }
+            __syncthreads();
+            const int64_t n = (int64_t)tn * BN + j * 32 + r;
+#pragma unroll
+            for (int e = wave; e < 16; e += kSplitWaves) {
+                using val_t = typename std::conditional<DT == SP24_I8, int, float>::type;
+                val_t sum = 0;
+#pragma unroll
+                for (int w = 0; w < kSplitWaves; ++w) sum += __builtin_bit_cast(val_t, red[w][e][lane]);
+                const int64_t m = (int64_t)tm * BM + i * 32 + 8 * (e / 4) + 4 * q + (e % 4);
+                if (m < a.M && n < a.N) put<DT>(a, m, n, sum);
+            }
+        }
+}
+
+template <int DT>
+static sp24_status run_ksplit(const MmArgs& a, hipStream_t st)
+{
+    const int tiles_m = (int)((a.M + 32 * TM - 1) / (32 * TM)), tiles_n = (int)((a.N + 32 * TN - 1) / (32 * TN));
+    const dim3 grid((unsigned)(tiles_m * tiles_n)), block(64 * kSplitWaves);
+    if (a.sparse) k_mm_ksplit<DT, true><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
+    else k_mm_ksplit<DT, false><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
+    return hipGetLastError() == hipSuccess ? SP24_OK : SP24_ERR_LAUNCH;
+}
+
+sp24_status launch_mm_ksplit(const MmArgs& a, hipStream_t st, bool* handled)
+{
+    *handled = false;
+    if (a.conv.on || a.bo != SP24_B_NMAJOR || a.k_slices > 1) return SP24_OK;
+    if (a.M > ((int64_t)1 << 30) || a.N > ((int64_t)1 << 30) || ((a.M + 63) / 64) * ((a.N + 63) / 64) >= ((int64_t)1 << 30)) return SP24_OK;
+    *handled = true;
+    if (a.in == SP24_I8) return run_ksplit<SP24_I8>(a, st);
+    if (a.in == SP24_F8) return run_ksplit<SP24_F8>(a, st);
+    if (a.in == SP24_F16) return run_ksplit<SP24_F16>(a, st);
+    return run_ksplit<SP24_BF16>(a, st);
+}
+
+} // namespace sp24
