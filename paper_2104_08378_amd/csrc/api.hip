@@ -326,6 +326,8 @@ static sp24_status mm_dispatch(const MmArgs& a, hipStream_t st)
         s = launch_mm_skinny(a, st, &handled);
         if (handled) return s;
     }
+    s = launch_conv_narrow(a, st, &handled);
+    if (handled) return s;
     s = launch_mm_tiled(a, st, &handled);
     if (handled) return s;
     if (tiled_first && !a.conv.on) {
