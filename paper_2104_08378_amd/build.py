@@ -1,4 +1,5 @@
-"""Build libsp24.so (hand-written HIP, gfx950 only) in-tree with hipcc.
+"""Build libsp24.so (hand-written HIP, gfx950 only) in-tree with hipcc, and the native half of the Python binding
+(_sp24_host.so, host code only) with g++ against the installed torch.
 
     python -m paper_2104_08378_amd.build
 
@@ -9,10 +10,12 @@ shims, no fallback.
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsp24.so")
+HOST = os.path.join(HERE, "_sp24_host.so")      # native marshalling of the binding's calls (csrc/host_calls.cpp)
 PROBE = os.path.join(HERE, "sp24_probe")        # stand-alone measurement of the chip's ceilings (csrc/probe.hip)
 SOURCES = ["api.hip", "prune_compress.hip", "permute.hip", "permute_search.hip", "splitk.hip", "mm_simple.hip", "mm_ksplit.hip", "conv_narrow.hip", "mm_skinny.hip", "mm_tiled.hip"] + [
     "mm_tiled_%s_%s.hip" % (i, o) for i, o in
@@ -24,6 +27,16 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-command-line-argument",
 ]
+
+
+def host_flags():
+    import torch
+    root = os.path.dirname(torch.__file__)
+    compile_flags = ["-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+                     f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f"-I{root}/include", f"-I{root}/include/torch/csrc/api/include",
+                     "-I/opt/rocm/include", f"-I{sysconfig.get_paths()['include']}"]
+    link_flags = [f"-L{HERE}", "-l:libsp24.so", f"-L{root}/lib", "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
+    return compile_flags, link_flags
 
 
 def build(verbose=False):
@@ -38,18 +51,23 @@ def build(verbose=False):
         objs.append(obj)
     probe_cmd = ["hipcc", *[f for f in FLAGS if f != "-fPIC"], os.path.join(CSRC, "probe.hip"), "-o", PROBE]
     procs.append(("probe.hip", subprocess.Popen(probe_cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    host_compile, host_link = host_flags()
+    host_obj = os.path.join(CSRC, "host_calls.o")
+    procs.append(("host_calls.cpp", subprocess.Popen(["g++", *host_compile, "-c", os.path.join(CSRC, "host_calls.cpp"), "-o", host_obj],
+                                                     stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     failed = False
     for src, p in procs:
         out, _ = p.communicate()
         out = "\n".join(l for l in out.splitlines() if "is not a recognized feature for this target" not in l)
         if p.returncode != 0:
             failed = True
-            print(f"hipcc failed for {src}:\n{out}", file=sys.stderr)
+            print(f"compilation failed for {src}:\n{out}", file=sys.stderr)
         elif verbose and out.strip():
             print(out)
     if failed:
         raise RuntimeError("libsp24 build failed")
     subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
+    subprocess.check_call(["g++", "-shared", "-o", HOST, host_obj, *host_link])
     return LIB
 
 

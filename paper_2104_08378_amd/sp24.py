@@ -1,5 +1,8 @@
 """Python binding of libsp24.so: argument marshalling only.
 
+The calls go through ``_sp24_host.so`` (``csrc/host_calls.cpp``), which marshals a well-formed call natively; whatever
+it declines runs the Python code below it, which says what is wrong.
+
 Each function mirrors the C entry point of the same name (``include/sp24.h``):
 it checks that the tensors live on the GPU, allocates the outputs with torch,
 passes raw device pointers and the current HIP stream, and raises on a non-zero
@@ -7,6 +10,8 @@ status.  Every arithmetic step runs in the library's HIP kernels; there is no
 fallback: if ``libsp24.so`` is not built the import of the symbols fails loudly.
 """
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
@@ -21,6 +26,7 @@ B_KMAJOR, B_NMAJOR = 0, 1
 _DT = {torch.float16: F16, torch.bfloat16: BF16, torch.int8: I8, torch.float32: F32, torch.int32: I32, torch.float8_e4m3fn: F8}
 _LAYOUT = {"canonical": CANONICAL, "tiled": TILED}
 _lib = None
+_host = None
 
 
 class Sp24Error(RuntimeError):
@@ -74,6 +80,21 @@ def lib():
             getattr(L, name).restype = i32
         _lib = L
     return _lib
+
+
+def _load_host():
+    """The native marshalling of the calls, beside libsp24.so."""
+    global _host
+    if _host is None:
+        lib()
+        path = os.path.join(os.path.dirname(LIB_PATH), "_sp24_host.so")
+        if not os.path.exists(path):
+            raise RuntimeError(f"{path} is missing: build it with `python -m paper_2104_08378_amd.build`")
+        loader = importlib.machinery.ExtensionFileLoader("_sp24_host", path)
+        host = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_sp24_host", path, loader=loader))
+        loader.exec_module(host)
+        _host = host
+    return _host
 
 
 def status_string(status):
@@ -157,6 +178,9 @@ def _check(status, where):
 
 def sp24_prune(A, out=None):
     """P = A with the two smallest-magnitude entries of each group of 4 zeroed; out may be A."""
+    done = (_host or _load_host()).sp24_prune(A, out)
+    if done is not None:
+        return done
     _rowmajor(A, "A")
     M, K = A.shape
     P = _out(out, (M, K), A.dtype, A.device)
@@ -167,6 +191,9 @@ def sp24_prune(A, out=None):
 
 def sp24_compress(A, layout="canonical", out=None):
     """Return (V, meta): V [M, K/2] of A's dtype, meta uint8 [M, K/8] (both flat-permuted for "tiled")."""
+    done = (_host or _load_host()).sp24_compress(A, layout, out)
+    if done is not None:
+        return done
     _rowmajor(A, "A")
     M, K = A.shape
     if out is None:
@@ -183,6 +210,9 @@ def sp24_compress(A, layout="canonical", out=None):
 
 
 def sp24_decompress(V, meta, layout="canonical", out=None):
+    done = (_host or _load_host()).sp24_decompress(V, meta, layout, out)
+    if done is not None:
+        return done
     M, K = _compressed(V, meta)
     P = _out(out, (M, K), V.dtype, V.device)
     _check(lib().sp24_decompress(V.data_ptr(), meta.data_ptr(), P.data_ptr(), M, K, P.stride(0), _DT[V.dtype],
@@ -192,6 +222,9 @@ def sp24_decompress(V, meta, layout="canonical", out=None):
 
 def sp24_prune_transposable(A, out=None):
     """2:4 along rows and along columns: per 4x4 block the two-per-row-and-column pattern that keeps the most magnitude."""
+    done = (_host or _load_host()).sp24_prune_transposable(A, out)
+    if done is not None:
+        return done
     _rowmajor(A, "A")
     M, K = A.shape
     P = _out(out, (M, K), A.dtype, A.device)
@@ -259,6 +292,9 @@ def sp24_permute_search(A, sweeps=1, perm=None):
 
 def sp24_mask_apply(W, meta, layout="canonical", out=None):
     """W with every position that the metadata does not record set to +0 (the pattern is kept, not re-selected)."""
+    done = (_host or _load_host()).sp24_mask_apply(W, meta, layout, out)
+    if done is not None:
+        return done
     _rowmajor(W, "W")
     M, K = W.shape
     _meta_arg(meta, M, K)
@@ -270,6 +306,9 @@ def sp24_mask_apply(W, meta, layout="canonical", out=None):
 
 def sp24_compress_masked(W, meta, layout="canonical", out=None):
     """Compressed values of W at the positions the metadata records."""
+    done = (_host or _load_host()).sp24_compress_masked(W, meta, layout, out)
+    if done is not None:
+        return done
     _rowmajor(W, "W")
     M, K = W.shape
     _meta_arg(meta, M, K)
@@ -294,6 +333,9 @@ def _b_args(B, b_order):
 
 def sp24_spmm(V, meta, B, out_dtype, b_order="k", layout="canonical", out=None):
     """D [M, N] = decompress(V, meta) @ B.  B is [N, K] for b_order "k", [K, N] for "n"."""
+    done = (_host or _load_host()).sp24_spmm(V, meta, B, out_dtype, b_order, layout, out)
+    if done is not None:
+        return done
     M, K = _compressed(V, meta)
     N, Kb, bo = _b_args(B, b_order)
     if Kb != K:
@@ -307,6 +349,9 @@ def sp24_spmm(V, meta, B, out_dtype, b_order="k", layout="canonical", out=None):
 
 def sp24_gemm_dense(A, B, out_dtype, b_order="k", out=None):
     """D [M, N] = A @ B on the dense matrix cores (speedup denominator)."""
+    done = (_host or _load_host()).sp24_gemm_dense(A, B, out_dtype, b_order, out)
+    if done is not None:
+        return done
     _rowmajor(A, "A")
     M, K = A.shape
     N, Kb, bo = _b_args(B, b_order)
@@ -337,6 +382,9 @@ def _workspace(workspace, M, N, K, dtype, device):
 def sp24_spmm_splitk(V, meta, B, out_dtype, b_order="k", layout="canonical", workspace=None, out=None):
     """sp24_spmm with the inner dimension split across workgroups (shapes with few output tiles); ``workspace``: a
     device tensor of at least sp24_splitk_workspace_bytes(...) bytes, allocated here when None."""
+    done = (_host or _load_host()).sp24_spmm_splitk(V, meta, B, out_dtype, b_order, layout, workspace, out)
+    if done is not None:
+        return done
     M, K = _compressed(V, meta)
     N, Kb, bo = _b_args(B, b_order)
     if Kb != K:
@@ -369,6 +417,9 @@ def sp24_spmm_splitk_static(V, meta, B, out_dtype, b_order="k", layout="canonica
 
 def sp24_gemm_dense_splitk(A, B, out_dtype, b_order="k", workspace=None, out=None):
     """sp24_gemm_dense with the inner dimension split across workgroups."""
+    done = (_host or _load_host()).sp24_gemm_dense_splitk(A, B, out_dtype, b_order, workspace, out)
+    if done is not None:
+        return done
     _rowmajor(A, "A")
     M, K = A.shape
     N, Kb, bo = _b_args(B, b_order)
@@ -397,6 +448,9 @@ def _conv_args(X, K, R, S, pad, stride):
 def sp24_spmm_conv2d(V, meta, X, out_dtype, R, S, pad=(0, 0), stride=(1, 1), layout="canonical", out=None):
     """D [M, n_img*OH*OW] = decompress(V, meta) applied as a bank of M filters to the NHWC input X, with no
     im2col matrix in memory.  Filter column k = (r*S + s)*C + c."""
+    done = (_host or _load_host()).sp24_spmm_conv2d(V, meta, X, out_dtype, R, S, pad, stride, layout, out)
+    if done is not None:
+        return done
     M, K = _compressed(V, meta)
     geom, N = _conv_args(X, K, R, S, pad, stride)
     _same_type(X, V, "X")
@@ -408,6 +462,9 @@ def sp24_spmm_conv2d(V, meta, X, out_dtype, R, S, pad=(0, 0), stride=(1, 1), lay
 
 def sp24_conv2d_dense(A, X, out_dtype, R, S, pad=(0, 0), stride=(1, 1), out=None):
     """The same convolution with the dense filter matrix A [M, R*S*C] on the dense matrix cores."""
+    done = (_host or _load_host()).sp24_conv2d_dense(A, X, out_dtype, R, S, pad, stride, out)
+    if done is not None:
+        return done
     _rowmajor(A, "A")
     M, K = A.shape
     geom, N = _conv_args(X, K, R, S, pad, stride)
@@ -433,6 +490,9 @@ def sp24_spmm_i8_scaled(V, meta, B, out_dtype, w_scale, x_scale, bias=None, relu
                         layout="canonical", out=None):
     """int8 sparse product with the quantised path's epilogue fused into the store: per-row weight scale,
     per-tensor activation scale, optional bias and ReLU; out_dtype int8 (re-quantised by inv_y_scale) or a float type."""
+    done = (_host or _load_host()).sp24_spmm_i8_scaled(V, meta, B, out_dtype, w_scale, x_scale, bias, relu, inv_y_scale, b_order, layout, out)
+    if done is not None:
+        return done
     M, K = _compressed(V, meta)
     N, Kb, bo = _b_args(B, b_order)
     if Kb != K:
@@ -448,6 +508,9 @@ def sp24_spmm_i8_scaled(V, meta, B, out_dtype, w_scale, x_scale, bias=None, relu
 
 def sp24_gemm_dense_i8_scaled(A, B, out_dtype, w_scale, x_scale, bias=None, relu=False, inv_y_scale=1.0, b_order="k", out=None):
     """The same epilogue on the dense int8 product."""
+    done = (_host or _load_host()).sp24_gemm_dense_i8_scaled(A, B, out_dtype, w_scale, x_scale, bias, relu, inv_y_scale, b_order, out)
+    if done is not None:
+        return done
     _rowmajor(A, "A")
     M, K = A.shape
     N, Kb, bo = _b_args(B, b_order)
@@ -465,6 +528,9 @@ def sp24_gemm_dense_i8_scaled(A, B, out_dtype, w_scale, x_scale, bias=None, relu
 def sp24_spmm_conv2d_i8_scaled(V, meta, X, out_dtype, R, S, w_scale, x_scale, bias=None, relu=False, inv_y_scale=1.0,
                                pad=(0, 0), stride=(1, 1), layout="canonical", out=None):
     """int8 sparse convolution (implicit GEMM) with the quantised path's epilogue; w_scale per output channel."""
+    done = (_host or _load_host()).sp24_spmm_conv2d_i8_scaled(V, meta, X, out_dtype, R, S, w_scale, x_scale, bias, relu, inv_y_scale, pad, stride, layout, out)
+    if done is not None:
+        return done
     M, K = _compressed(V, meta)
     geom, N = _conv_args(X, K, R, S, pad, stride)
     _same_type(X, V, "X")
@@ -479,6 +545,9 @@ def sp24_spmm_conv2d_i8_scaled(V, meta, X, out_dtype, R, S, w_scale, x_scale, bi
 def sp24_conv2d_dense_i8_scaled(A, X, out_dtype, R, S, w_scale, x_scale, bias=None, relu=False, inv_y_scale=1.0, pad=(0, 0),
                                 stride=(1, 1), out=None):
     """The same with the dense int8 filter matrix."""
+    done = (_host or _load_host()).sp24_conv2d_dense_i8_scaled(A, X, out_dtype, R, S, w_scale, x_scale, bias, relu, inv_y_scale, pad, stride, out)
+    if done is not None:
+        return done
     _rowmajor(A, "A")
     M, K = A.shape
     geom, N = _conv_args(X, K, R, S, pad, stride)
