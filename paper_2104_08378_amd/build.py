@@ -17,7 +17,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsp24.so")
 HOST = os.path.join(HERE, "_sp24_host.so")      # native marshalling of the binding's calls (csrc/host_calls.cpp)
 PROBE = os.path.join(HERE, "sp24_probe")        # stand-alone measurement of the chip's ceilings (csrc/probe.hip)
-SOURCES = ["api.hip", "prune_compress.hip", "permute.hip", "permute_search.hip", "splitk.hip", "mm_simple.hip", "mm_ksplit.hip", "conv_narrow.hip", "mm_skinny.hip", "mm_tiled.hip"] + [
+SOURCES = ["api.hip", "prune_compress.hip", "permute.hip", "permute_search.hip", "splitk.hip", "mm_simple.hip", "mm_ksplit.hip", "conv_narrow.hip", "mm_skinny.hip", "mm_tiled.hip", "mm_staged.hip",
+           "mm_staged_f16.hip", "mm_staged_bf16.hip", "mm_staged_i8.hip", "mm_staged_f8.hip"] + [
     "mm_tiled_%s_%s.hip" % (i, o) for i, o in
     [("f16", "f32"), ("f16", "f16"), ("f16", "bf16"), ("bf16", "f32"), ("bf16", "f16"), ("bf16", "bf16"),
      ("i8", "i32"), ("i8", "i8"), ("i8", "f32"), ("i8", "f16"), ("i8", "bf16"), ("f8", "f32"), ("f8", "f16"), ("f8", "bf16")]]
@@ -25,7 +26,8 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
     # hipcc must not form packed-fp32 instructions by itself on this target
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    "-Wall", "-Wno-unused-command-line-argument",
+    # -Winline-asm: a note for every transfer that sets m0, megabytes of them, which stall the compilers on their pipes
+    "-Wall", "-Wno-unused-command-line-argument", "-Wno-inline-asm",
 ]
 
 

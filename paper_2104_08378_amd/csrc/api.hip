@@ -316,6 +316,16 @@ static bool tiled_before_streaming(const MmArgs& a)
     return !a.sparse && a.N > 8 && tiles >= 86;
 }
 
+// Sparse products that the tiled kernels do not take: tiles of their shape with B staged through registers, or (N-major,
+// few tiles) K split across the wavefronts of a workgroup, which the former leaves idle.  Measured on N-major products
+// with an odd N: below 256 tiles of 128 x 128 the K-splitting kernel is up to twice as fast on long K (1024 x 509 x 4096
+// bf16 20 against 38 us), from there on the staged one (6784 x 939 x 6464: 193 -> 104 us).
+static bool staged_before_ksplit(const MmArgs& a)
+{
+    if (a.conv.on || a.bo == SP24_B_KMAJOR) return true;      // the K-splitting kernel does not take them anyway
+    return ((a.M + 127) / 128) * ((a.N + 127) / 128) >= 256;
+}
+
 // The kernel for a checked product: streaming (N <= 32), tiled, or general.
 static sp24_status mm_dispatch(const MmArgs& a, hipStream_t st)
 {
@@ -332,6 +342,10 @@ static sp24_status mm_dispatch(const MmArgs& a, hipStream_t st)
     if (handled) return s;
     if (tiled_first && !a.conv.on) {
         s = launch_mm_skinny(a, st, &handled);
+        if (handled) return s;
+    }
+    if (staged_before_ksplit(a)) {
+        s = launch_mm_staged(a, st, &handled);
         if (handled) return s;
     }
     s = launch_mm_ksplit(a, st, &handled);

@@ -59,6 +59,10 @@ sp24_status launch_mm_simple(const MmArgs& a, hipStream_t st);
 // N-major B at any alignment, K split across the wavefronts of a workgroup; false in *handled for other problems.
 sp24_status launch_mm_ksplit(const MmArgs& a, hipStream_t st, bool* handled);
 
+// Sparse products and convolutions that the tiled kernels do not take, on tiles of their shape; false in *handled for
+// other problems.
+sp24_status launch_mm_staged(const MmArgs& a, hipStream_t st, bool* handled);
+
 // Sparse 3x3 convolution of 8-bit inputs in chunks of 64 channels; false in *handled for other problems.
 sp24_status launch_conv_narrow(const MmArgs& a, hipStream_t st, bool* handled);
 

@@ -14,9 +14,7 @@
 // each on the tiled kernels in brackets): 1024 x 509 x 4096 int8 482 -> 15.8; 8192 x 17 x 8192 bf16 443 -> 32.9;
 // 4096 x 1155 x 4096 bf16 676 -> 93 [N = 1152: 36], int8 856 -> 67 [23]; 3744 x 5453 x 1984 f8 1559 -> 171 [43].  On
 // many tiles it is bound by the loads: a 64 x 64 tile moves twice the operand bytes per product of a 128 x 128 one.
-#include "mm_tiled.hpp"
-
-#include <cstring>
+#include "mm_operands.hpp"
 
 namespace sp24 {
 
@@ -25,22 +23,6 @@ namespace {
 constexpr int kSplitWaves = 8;
 constexpr int TM = 2, TN = 2;                       // 32 x 32 accumulator tiles per wavefront
 
-// 16 bytes from any address (one dwordx4 load)
-__device__ __forceinline__ uint4v load16_any(const uint8_t* p)
-{
-    uint4v v;
-    __builtin_memcpy(&v, p, 16);
-    return v;
-}
-
-// the value's bytes moved down by `bytes` (0 .. 15), zeros on top
-__device__ __forceinline__ uint4v shift_down(uint4v v, int bytes)
-{
-    unsigned __int128 x = __builtin_bit_cast(unsigned __int128, v);
-    x >>= 8 * bytes;
-    return __builtin_bit_cast(uint4v, x);
-}
-
 // between a wavefront's own LDS writes and reads: the LDS serves them in order, only the compiler must keep it
 __device__ __forceinline__ void wave_order()
 {
@@ -48,6 +30,36 @@ __device__ __forceinline__ void wave_order()
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
+
+// The dense first operand of TM blocks of 32 rows in the dense instruction's lane order, as compressed_rows
+template <int DT, int TM>
+struct dense_rows {
+    static constexpr int ES = is8<DT> ? 1 : 2;
+    static constexpr int NA = 2 * ES;
+    const uint8_t* src[TM];
+    int64_t row_bytes;
+    int q;
+    __device__ __forceinline__ void init(const MmArgs& a, int64_t block0, int lane)
+    {
+        q = lane >> 5;
+        row_bytes = a.K * ES;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+            src[i] = reinterpret_cast<const uint8_t*>(a.A) + min((block0 + i) * 32 + (lane & 31), a.M - 1) * a.lda * ES + 16 * q;
+    }
+    __device__ __forceinline__ void load(int64_t kb, int4v (&v)[TM][NA], uint32_t (&code)[TM]) const
+    {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+#pragma unroll
+            for (int s = 0; s < NA; ++s) {
+                const int64_t at = kb * (64 * ES) + 32 * s;
+                v[i][s] = __builtin_bit_cast(int4v, load16_aligned(at + 16 * q < row_bytes ? src[i] + at : k_zero_row));
+            }
+            code[i] = 0;
+        }
+    }
+};
 
 // result element (m, n) from the accumulated value
 template <int DT, typename ACC>
@@ -76,11 +88,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_mm_ksplit(MmArgs a, int ti
 {
     constexpr int ES = is8<DT> ? 1 : 2;
     constexpr int BM = 32 * TM, BN = 32 * TN;
-    constexpr int kRowB = BN * ES, kChunks = kRowB / 16;      // a K row of B in LDS: bytes, 16-byte chunks
-    constexpr int kImage = 64 * kRowB;                        // 64 K rows
-    constexpr int NJ = kImage / 1024;                         // 16-byte pieces of the image per lane
-    constexpr int kRowsPerPiece = 64 / kChunks;               // K rows from a lane's piece to its next
-    constexpr int NA = SPARSE ? (ES == 1 ? 1 : 2) : 2 * ES;   // 16-byte pieces of a row block of A per lane and tile
+    constexpr int kImage = 64 * BN * ES;                      // 64 K rows of B in LDS
     using acc_t = typename acc_of<DT>::type;
     constexpr int kRedBytes = kSplitWaves * 16 * 64 * 4;
     constexpr int kLds = kSplitWaves * kImage > kRedBytes ? kSplitWaves * kImage : kRedBytes;
@@ -93,85 +101,19 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_mm_ksplit(MmArgs a, int ti
     const int r = lane & 31, q = lane >> 5;
     const int64_t K = a.K, tiles_k = (K + 63) / 64;
 
-    // ---- B: this lane's pieces of a tile's image are rows row0, row0 + kRowsPerPiece, ..., chunk c of each ----
-    const int64_t ldb = a.ldb * ES, col0 = (int64_t)tn * BN * ES;                 // bytes
-    const int64_t b_bytes = (K - 1) * ldb + a.N * ES;                             // from B to its last element's end
-    const int row0 = lane / kChunks, c = lane % kChunks;
-    const int valid = (int)min((int64_t)kChunks, (a.N * ES - col0 + 15) / 16);    // chunks that hold columns of the matrix
-    const int64_t src0 = col0 + min(c, valid - 1) * 16;                           // byte of a row; past the last chunk: never stored
-    const int64_t tile_reach = 63 * ldb + col0 + (valid - 1) * 16 + 16;           // end of a tile's last piece, from the tile's first row
+    using pieces_t = nmajor_pieces<BN, ES, 64, 64>;
+    constexpr int NJ = pieces_t::NJ;
+    pieces_t pieces;
+    pieces.init(a, tn, lane);
     uint8_t* const image = lds + wave * kImage;
-    const int dst0 = row0 * kRowB + ((c ^ nmajor_swizzle<ES>(row0, kChunks)) << 4);
-    static_assert(kRowsPerPiece % 8 == 0, "the swizzle is the same for all of a lane's pieces");
-    const uint8_t* const Bp = reinterpret_cast<const uint8_t*>(a.B);
-    auto load_b = [&](int64_t kb, uint4v (&v)[NJ]) {
-        const int64_t first = kb * 64 * ldb;
-        if (kb * 64 + 64 <= K && first + tile_reach <= b_bytes) {
-            const uint8_t* p = Bp + first + row0 * ldb + src0;
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) v[j] = load16_any(p + j * kRowsPerPiece * ldb);
-        } else {
-            // the last rows: pieces that would end past the last element are read up to it and moved into place,
-            // rows past K are zeros
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                const int64_t k = kb * 64 + row0 + j * kRowsPerPiece;
-                const int64_t at = min(k, K - 1) * ldb + src0;
-                const int64_t over = max((int64_t)0, at + 16 - b_bytes);
-                const uint4v x = shift_down(load16_any(Bp + at - over), (int)over);
-                v[j] = k < K ? x : uint4v{0u, 0u, 0u, 0u};
-            }
-        }
-    };
     nmajor_frags<BN, TN, ES> frags;
     frags.init(0, lane);
 
     // ---- A ----
-    const bool canonical = SPARSE && a.layout == SP24_LAYOUT_CANONICAL;
-    const uint8_t* a_src[TM];
-    const uint8_t* m_src[TM];
-    int64_t a_step, m_step;                                   // bytes per 64-column tile
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        const int64_t m = min((int64_t)tm * BM + i * 32 + r, a.M - 1);            // ragged M: a valid row, never stored
-        if constexpr (!SPARSE) {
-            a_src[i] = reinterpret_cast<const uint8_t*>(a.A) + m * a.lda * ES + 16 * q;
-            m_src[i] = nullptr;
-        } else if (canonical) {
-            a_src[i] = reinterpret_cast<const uint8_t*>(a.A) + m * (K / 2 * ES) + 16 * ES * q;
-            m_src[i] = reinterpret_cast<const uint8_t*>(a.meta) + m * (K / 8) + 4 * q;
-        } else {
-            const int64_t rb = min((int64_t)tm * TM + i, a.M / 32 - 1);
-            a_src[i] = reinterpret_cast<const uint8_t*>(a.A) + rb * (K / 64) * (1024 * ES) + lane * 16;
-            m_src[i] = reinterpret_cast<const uint8_t*>(a.meta) + rb * (K / 64) * 256 + lane * 4;
-        }
-    }
-    a_step = !SPARSE ? 64 * ES : canonical ? 32 * ES : 1024 * ES;
-    m_step = canonical ? 8 : 256;
-    const int64_t piece_step = !SPARSE ? 32 : canonical ? 16 : 1024;              // from a lane's piece of a tile to its next
-    auto load_a = [&](int64_t kb, int4v (&v)[TM][NA], uint32_t (&code)[TM]) {
-        const bool whole = kb * 64 + 64 <= K;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-#pragma unroll
-            for (int s = 0; s < NA; ++s) {
-                // first column of A that the piece holds (a piece of a row is all before K or all past it)
-                const int64_t col = kb * 64 + (SPARSE ? 32 * q + 16 * s : (32 * s + 16 * q) / ES);
-                v[i][s] = int4v{0, 0, 0, 0};
-                if (whole || col < K) v[i][s] = *reinterpret_cast<const int4v*>(a_src[i] + kb * a_step + s * piece_step);
-            }
-            code[i] = 0;
-            if constexpr (SPARSE) {
-                const uint8_t* p = m_src[i] + kb * m_step;
-                if (whole || kb * 64 + 32 * q + 32 <= K) __builtin_memcpy(&code[i], p, 4);
-                else if (kb * 64 + 32 * q < K) {              // 16 columns left
-                    uint16_t half;
-                    __builtin_memcpy(&half, p, 2);
-                    code[i] = half;
-                }
-            }
-        }
-    };
+    using rows_t = typename std::conditional<SPARSE, compressed_rows<DT, TM>, dense_rows<DT, TM>>::type;
+    constexpr int NA = rows_t::NA;
+    rows_t rows;
+    rows.init(a, (int64_t)tm * TM, lane);
 
     acc_t acc[TM][TN];
 #pragma unroll
@@ -183,13 +125,12 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_mm_ksplit(MmArgs a, int ti
     int4v av[TM][NA];
     uint32_t code[TM];
     if (wave < tiles_k) {
-        load_b(wave, bv);
-        load_a(wave, av, code);
+        pieces.load((int64_t)wave * 64, bv);
+        rows.load(wave, av, code);
     }
     for (int64_t kb = wave; kb < tiles_k; kb += kSplitWaves) {
         wave_order();                                         // behind the reads of the previous tile
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) *reinterpret_cast<uint4v*>(image + dst0 + j * kRowsPerPiece * kRowB) = bv[j];
+        pieces.store(image, bv);
         int4v x[TM][NA];
         uint32_t xc[TM];
 #pragma unroll
@@ -200,8 +141,8 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_mm_ksplit(MmArgs a, int ti
         }
         wave_order();
         const int64_t next = kb + kSplitWaves < tiles_k ? kb + kSplitWaves : kb;   // the last tile is loaded again, unused
-        load_b(next, bv);
-        load_a(next, av, code);
+        pieces.load(next * 64, bv);
+        rows.load(next, av, code);
         if constexpr (SPARSE) {
             constexpr int NI = ES;                            // instructions per tile: 8-bit one of 64 columns, 16-bit two of 32
 #pragma unroll

@@ -18,9 +18,7 @@
 // kernel.  The sparse variant reads one contiguous stream per workgroup front
 // to back, with the tile addresses of a batch a constant apart (a start tile
 // per workgroup cost it 10 %: an address computation per load).
-#include "common.hpp"
-#include "launch.hpp"
-#include "mfma.hpp"
+#include "mm_operands.hpp"
 
 namespace sp24 {
 
@@ -60,10 +58,10 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_mm_skinny(MmArgs a)
     const uint4v* Vp = reinterpret_cast<const uint4v*>(a.A);
     const uint32_t* Mp = reinterpret_cast<const uint32_t*>(a.meta);
     const int64_t tile_first = rb * (a.K / 64) + kb_first;   // tiled layout: this row block's first tile of the share
-    // canonical layout: lane (m % 32, h) reads its slot's 16 bytes of values and 4 bytes of codes from row m
+    // canonical layout: each lane gathers its slot from row m; a K that is no multiple of 64 ends in a partial tile
     const bool canonical = SPARSE && a.layout == SP24_LAYOUT_CANONICAL;
-    const uint8_t* vrow = reinterpret_cast<const uint8_t*>(a.A) + m * (a.K / 2 * ES) + (ES == 1 ? 16 : 32) * q + kb_first * 32 * ES;
-    const uint8_t* mrow = reinterpret_cast<const uint8_t*>(a.meta) + m * (a.K / 8) + 4 * q + kb_first * 8;
+    compressed_rows<DT, 1> rows;
+    if constexpr (SPARSE) rows.init(a, rb, lane);
 
     acc_t acc = {};
     const uint4v zero4 = {0u, 0u, 0u, 0u};
@@ -83,12 +81,12 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_mm_skinny(MmArgs a)
             if constexpr (SPARSE) {
                 const int64_t tile = tile_first + kb;
                 if (canonical) {
-                    codes[u] = ok ? *reinterpret_cast<const uint32_t*>(mrow + kb * 8) : 0u;
-                    if constexpr (is8<DT>) va[u][0] = ok ? *reinterpret_cast<const uint4v*>(vrow + kb * 32) : zero4;
-                    else {
-                        va[u][0] = ok ? *reinterpret_cast<const uint4v*>(vrow + kb * 64) : zero4;
-                        va[u][1] = ok ? *reinterpret_cast<const uint4v*>(vrow + kb * 64 + 16) : zero4;
-                    }
+                    int4v v[1][rows.NA];
+                    uint32_t code[1];
+                    rows.load(kb_first + kb, v, code);       // zeros past K; a slice ends at its own last tile
+                    codes[u] = code[0];
+#pragma unroll
+                    for (int s = 0; s < rows.NA; ++s) va[u][s] = ok ? __builtin_bit_cast(uint4v, v[0][s]) : zero4;
                 } else {
                     // the compressed operand passes once: loads marked as such leave B, which every workgroup re-reads,
                     // in the L2 (8192 x 8192 x 16 bf16 with the operand streamed from HBM: 21.1 -> 19.3 us)
@@ -179,7 +177,6 @@ sp24_status launch_mm_skinny(const MmArgs& a, hipStream_t st, bool* handled)
     const int es = esize_of(a.in);
     bool ok = a.N <= 32 && a.bo == SP24_B_KMAJOR && (reinterpret_cast<uintptr_t>(a.B) & 15u) == 0 && (a.ldb * es) % 16 == 0 &&
               a.M >= 32 && (a.M + 31) / 32 < ((int64_t)1 << 31);
-    if (a.sparse && a.layout == SP24_LAYOUT_CANONICAL) ok = ok && a.K % 64 == 0;
     if (!ok) return SP24_OK;
     *handled = true;
     if (a.in == SP24_I8) {

@@ -1,0 +1,8 @@
+// Products whose second operand passes through registers (mm_staged.hpp), f8 inputs.
+#include "mm_staged.hpp"
+
+namespace sp24 {
+
+sp24_status staged_f8(const MmArgs& a, hipStream_t st) { return run_staged<SP24_F8>(a, st); }
+
+} // namespace sp24
