@@ -288,14 +288,14 @@ sp24_status sp24_gemm_dense(const void* A, const void* B, void* D, int64_t M, in
  * second kernel adds the slices in slice order and converts to `out`.  int8 results equal sp24_spmm's bit for bit;
  * results of 16-bit inputs differ from it by the order of the fp32 additions
  * only, and are the same from call to call.
- * How many slices -- a function of M, N, K and `in` alone -- follows from
+ * How many slices at most -- a function of M, N, K and `in` alone -- follows from
  * sp24_splitk_workspace_bytes(M, N, K, in): the bytes `workspace` must hold
  * (device, 16-byte aligned, not overlapping any operand; contents before the
  * call are ignored, contents after it unspecified), or 0 when the shape would
  * not be split (or is not legal).  With 0 the call is sp24_spmm /
  * sp24_gemm_dense and `workspace` may be NULL; so it is for operands the
  * tiled and streaming kernels do not take (alignment of B; N <= 32 with an
- * N-major B, or with the canonical layout and K % 64 != 0).  Errors as for sp24_spmm, and
+ * N-major B) and for shapes whose unsplit tiles occupy the chip.  Errors as for sp24_spmm, and
  * SP24_ERR_NULL / SP24_ERR_ALIGN for a missing or misaligned workspace,
  * SP24_ERR_SHAPE when workspace_bytes is too small or it overlaps an operand.
  * Calls sharing one workspace must not overlap in time.

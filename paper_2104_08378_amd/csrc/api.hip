@@ -1,5 +1,6 @@
 // C ABI of libsp24: argument validation on the host, then kernel selection.
 // Nothing here allocates, synchronises or touches the current device.
+#include <algorithm>
 #include <atomic>
 
 #include "common.hpp"
@@ -316,6 +317,18 @@ static bool tiled_before_streaming(const MmArgs& a)
     return !a.sparse && a.N > 8 && tiles >= 86;
 }
 
+// Sparse products whose tiles of 32 rows and 16, 32 or 64 columns each find a compute unit of their own: the kernel that
+// splits K across a workgroup's wavefronts.  One workgroup's rings fill a unit's LDS, so a second round costs the whole
+// time again: measured against the tiled and the streaming kernel, up to 256 workgroups 1.05 - 2.4 times as fast
+// (1024 x 128 x 4096 bf16 16.7 -> 9.9 us, 8192 x 32 x 8192 25.1 -> 14.0, 8192 x 16 x 8192 18.1 -> 13.3; 4096 x 1 x 1024
+// level), past that 0.4 - 1.0 times -- except for 16-bit inputs with N <= 32 up to the 11008 rows from which the tiled
+// kernels take them (9216 x 16 x 4096 17.0 -> 12.3 us in two rounds).
+static bool stream_first(const MmArgs& a)
+{
+    if (!a.sparse || a.conv.on || a.bo != SP24_B_KMAJOR) return false;
+    return stream_workgroups(a) <= 256 || (a.N <= 32 && esize_of(a.in) == 2 && a.M < 11008);
+}
+
 // Sparse products that the tiled kernels do not take: tiles of their shape with B staged through registers, or (N-major,
 // few tiles) K split across the wavefronts of a workgroup, which the former leaves idle.  Measured on N-major products
 // with an odd N: below 256 tiles of 128 x 128 the K-splitting kernel is up to twice as fast on long K (1024 x 509 x 4096
@@ -332,6 +345,10 @@ static sp24_status mm_dispatch(const MmArgs& a, hipStream_t st)
     bool handled = false;
     sp24_status s;
     const bool tiled_first = a.conv.on || tiled_before_streaming(a);
+    if (stream_first(a)) {
+        s = launch_mm_stream(a, st, &handled);
+        if (handled) return s;
+    }
     if (!tiled_first) {
         s = launch_mm_skinny(a, st, &handled);
         if (handled) return s;
@@ -473,6 +490,22 @@ static sp24_status mm_splitk(const MmArgs& a, void* workspace, size_t workspace_
     part.k_slices = plan.slices;
     part.slice_steps = plan.slice_steps;
     bool handled = false;
+    if (stream_first(a)) {
+        // The unsplit product has one workgroup on each tile of 32 rows already, which takes 40 ns (N <= 32) or 100 ns per
+        // 128-byte step whatever their number; of the plan's slices as many as find a unit of their own and as the
+        // images are worth (written and read at 4 TB/s).  Against the plan's slices on the tiled or the streaming kernel:
+        // 1000 x 64 x 2048 f16 13.4 -> 8.4 us, 512 x 16 x 16384 bf16 10.1 -> 9.1, 1024 x 128 x 4096 12.5 -> 9.3.
+        const int64_t steps_ns = a.K * es / 128 * (a.N <= 32 ? 40 : 100), image_ns = a.M * plan.ldw / 500;
+        const int most = (int)std::min<int64_t>(plan.slices, 256 / stream_workgroups(a));
+        if (most <= 1) return mm_dispatch(a, st);
+        part.k_slices = 2;
+        for (int n = 3; n <= most; ++n)
+            if (steps_ns / n + n * image_ns < steps_ns / part.k_slices + part.k_slices * image_ns) part.k_slices = n;
+        s = launch_mm_stream(part, st, &handled);
+        if (handled && s != SP24_OK) return s;
+        if (handled) return launch_splitk_reduce(workspace, part.k_slices, a.M, a.N, plan.ldw, a.D, a.ldd, a.in == SP24_I8, a.out, st);
+        part.k_slices = plan.slices;
+    }
     s = plan.streaming ? launch_mm_skinny(part, st, &handled) : launch_mm_tiled(part, st, &handled);
     if (!handled) return mm_dispatch(a, st);             // operands that kernel does not take: not split
     if (s != SP24_OK) return s;

@@ -66,6 +66,14 @@ sp24_status launch_mm_staged(const MmArgs& a, hipStream_t st, bool* handled);
 // Sparse 3x3 convolution of 8-bit inputs in chunks of 64 channels; false in *handled for other problems.
 sp24_status launch_conv_narrow(const MmArgs& a, hipStream_t st, bool* handled);
 
+// Sparse products with few columns or few tiles, K split across the wavefronts of a workgroup; false in *handled for
+// operands it does not take.
+sp24_status launch_mm_stream(const MmArgs& a, hipStream_t st, bool* handled);
+
+// Columns of its tiles (of 32 rows) and workgroups it would launch
+inline int stream_columns(const MmArgs& a) { return a.N <= 16 ? 16 : a.N <= 32 ? 32 : 64; }
+inline int64_t stream_workgroups(const MmArgs& a) { return ((a.M + 31) / 32) * ((a.N + stream_columns(a) - 1) / stream_columns(a)); }
+
 // Streaming kernel for N <= 32; returns false in *handled when the problem does not fit it.
 sp24_status launch_mm_skinny(const MmArgs& a, hipStream_t st, bool* handled);
 

@@ -1,0 +1,29 @@
+"""GPU parity of the sparse products that split K across a workgroup's wavefronts, each with an LDS ring of its own (the
+criteria of test_gpu_parity.py)."""
+import pytest
+
+from test_gpu_parity import run_mm_case
+
+pytestmark = pytest.mark.gpu
+
+# K: less than a step, fewer steps than wavefronts, one more than a multiple of them, partial last steps that the first or
+# another wavefront takes, rings that wrap; N around the tile widths; one row, ragged rows
+CASES = [
+    ("i8", "i32", 32, 1, 64),
+    ("i8", "i32", 33, 16, 1056),
+    ("i8", "i32", 64, 17, 1152),
+    ("i8", "i32", 96, 32, 4224),
+    ("i8", "i32", 1000, 3, 8224),
+    ("bf16", "bf16", 1, 2, 32),
+    ("bf16", "f32", 64, 15, 576),
+    ("f16", "f16", 45, 31, 544),
+    ("f16", "f32", 320, 16, 4160),
+    ("bf16", "bf16", 129, 32, 2592),
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_products_match_oracle(case):
+    run_mm_case(*case, layout="canonical", b_order="k", sparse=True, seed=61)
+    if case[2] % 32 == 0 and case[4] % 64 == 0:
+        run_mm_case(*case, layout="tiled", b_order="k", sparse=True, seed=62)
