@@ -306,11 +306,13 @@ __device__ __forceinline__ void dma_rows(const uint8_t* base, const uint32_t (&o
 // wavefront's tile is written to LDS as a row-major image in the output type and read back 16 bytes per lane,
 // so that a store instruction covers whole rows of the wavefront's tile (256 or 512 contiguous bytes each).
 // `scratch` is this wavefront's own 32 x kPitch bytes.
-// Outputs whose rows are not whole, aligned 16-byte chunks (an odd number of columns): 2- and 4-byte ones are stored
-// directly.  1-byte ones, where a direct store moves 32 bytes of a row, go through the image all the same: the 16-byte
-// stores then start at any address, the last chunk of a row is cut to its columns, and they are ordinary stores, so
-// that the two halves of a cache line that two of them share meet in the L2 (4096 x 8191 x 1024 int8, re-quantised:
-// 79.5 -> 40.0 us, x 509: 18.5 -> 10.1; through the image, 2- and 4-byte outputs were 3 % faster to 5 % slower).
+// Outputs whose rows are not whole, aligned 16-byte chunks (an odd number of columns): accumulators that need no scaling
+// are stored directly.  The quantised path's, which would read scale and bias of every element's row again (and, as int8,
+// store 32 bytes of a row at a time), go through the image all the same: the 16-byte stores then start at any address, the
+// last chunk of a row is cut to its columns, and they are ordinary stores, so that the two halves of a cache line that
+// two of them share meet in the L2 (4096 x 8191 x 1024 int8, re-quantised: 79.5 -> 40.0 us, x 509: 18.5 -> 10.1; to bf16 68.4 ->
+// 35.9, to float 67.9 -> 43.3.
+// Plain 2- and 4-byte outputs were 3 % faster to 5 % slower through the image).
 template <int OUT, int TN>
 struct epilogue_geometry {
     static constexpr int kOsz = out_size<OUT>();
@@ -332,6 +334,7 @@ struct epilogue_geometry {
 };
 
 // the first `bytes` (1 .. 15) of a 16-byte value, to any address
+template <int ES>
 __device__ __forceinline__ void store_front(uint8_t* to, uint4v v, int bytes)
 {
     if (bytes & 8) {
@@ -347,13 +350,17 @@ __device__ __forceinline__ void store_front(uint8_t* to, uint4v v, int bytes)
         to += 4;
         v[0] = v[1];
     }
-    if (bytes & 2) {
-        const uint16_t w = (uint16_t)v[0];
-        __builtin_memcpy(to, &w, 2);
-        to += 2;
-        v[0] >>= 16;
+    if constexpr (ES <= 2) {
+        if (bytes & 2) {
+            const uint16_t w = (uint16_t)v[0];
+            __builtin_memcpy(to, &w, 2);
+            to += 2;
+            v[0] >>= 16;
+        }
     }
-    if (bytes & 1) *to = (uint8_t)v[0];
+    if constexpr (ES == 1) {
+        if (bytes & 1) *to = (uint8_t)v[0];
+    }
 }
 
 template <int DT, int OUT, int TM, int TN>
@@ -363,7 +370,8 @@ __device__ __forceinline__ void store_wave_tile(const MmArgs& a, typename acc_of
     using G = epilogue_geometry<OUT, TN>;
     constexpr int kOsz = G::kOsz, kPitch = G::kPitch;
     const bool vec_ok = (reinterpret_cast<uintptr_t>(a.D) & 15u) == 0 && (a.ldd * kOsz) % 16 == 0 && a.N % (16 / kOsz) == 0;
-    if (kOsz > 1 && !vec_ok) {
+    constexpr bool kScaled = DT == SP24_I8 && OUT != SP24_I32;
+    if (!kScaled && !vec_ok) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -433,9 +441,9 @@ __device__ __forceinline__ void store_wave_tile(const MmArgs& a, typename acc_of
             // B panels that neighbouring tiles share
             if (grow < a.M && gcol < a.N) {
                 uint8_t* const to = Dp + (grow * a.ldd + gcol) * kOsz;
-                if (kOsz > 1 || vec_ok) __builtin_nontemporal_store(v, reinterpret_cast<uint4v*>(to));
-                else if (gcol + 16 <= a.N) __builtin_memcpy(to, &v, 16);
-                else store_front(to, v, (int)(a.N - gcol));
+                if (!kScaled || vec_ok) __builtin_nontemporal_store(v, reinterpret_cast<uint4v*>(to));
+                else if (gcol + 16 / kOsz <= a.N) __builtin_memcpy(to, &v, 16);
+                else store_front<kOsz>(to, v, (int)(a.N - gcol) * kOsz);
             }
         }
     }
