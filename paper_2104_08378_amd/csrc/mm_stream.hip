@@ -94,17 +94,15 @@ __global__ __launch_bounds__(64 * NW) void k_spmm_stream(MmArgs a, int tiles_m, 
     int v_piece[2];                                   // canonical: 16-byte piece of the row's 64 bytes of values
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
-        // canonical: four lanes to a row; the piece at slot lane % 4 is rotated by the row so that the reads of 16 rows
-        // hit 16 different 16-byte columns of the banks
         const int row = x * 16 + (lane >> 2);
-        v_piece[x] = (lane & 3) ^ ((row >> 2) & 3);
+        v_piece[x] = canonical_piece(row, lane & 3);
         const int64_t rows_left = a.M - 1 - (int64_t)tm * 32;       // ragged M: a valid row, never stored
         v_off[x] = canonical ? (uint32_t)(min((int64_t)row, rows_left) * vrow) + v_piece[x] * 16 : x * 1024 + lane * 16;
     }
 #pragma unroll
     for (int t = 0; t < T64; ++t) {
         const int64_t rows_left = a.M - 1 - (int64_t)tm * 32;
-        m_off[t] = canonical ? (uint32_t)(min((int64_t)r, rows_left) * mrow) + 8 * t + 4 * q : t * 256 + lane * 4;
+        m_off[t] = canonical ? (uint32_t)(min((int64_t)(t * 16 + lane / (2 * T64)), rows_left) * mrow) + (lane % (2 * T64)) * 4 : t * 256 + lane * 4;
     }
     uint8_t* const ring = lds + wave * (NS * kStage);
     auto fetch = [&](int step, int u) {
@@ -124,7 +122,7 @@ __global__ __launch_bounds__(64 * NW) void k_spmm_stream(MmArgs a, int tiles_m, 
                                 ring + kVOff + x * 1024);
 #pragma unroll
         for (int t = 0; t < T64; ++t)
-            lds_dma_tail<true>(m_base + (int64_t)step * m_step, m_off[t], (canonical ? (8 * t + 4 * q) * 8 * ES : 64 * ES * t) >= tail,
+            lds_dma_tail<true>(m_base + (int64_t)step * m_step, m_off[t], (canonical ? (lane % (2 * T64)) * 32 * ES : 64 * ES * t) >= tail,
                                ring + kMOff + t * 256);
 #pragma unroll
         for (int j = 0; j < NB; ++j)
@@ -136,8 +134,11 @@ __global__ __launch_bounds__(64 * NW) void k_spmm_stream(MmArgs a, int tiles_m, 
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         const int piece = is8<DT> ? 2 * j + q : 2 * q + j;
-        a_off[j] = kVOff + (canonical ? r * 64 + ((piece ^ ((r >> 2) & 3)) << 4) : j * 1024 + lane * 16);
+        a_off[j] = kVOff + (canonical ? r * 64 + canonical_piece(r, piece) * 16 : j * 1024 + lane * 16);
     }
+    int m_read[T64];
+#pragma unroll
+    for (int t = 0; t < T64; ++t) m_read[t] = kMOff + (canonical ? r * (8 * T64) + (2 * t + q) * 4 : t * 256 + lane * 4);
     const int br = BR == 16 ? r & 15 : r;             // 16 columns: the upper half computes them again, never stored
 #pragma unroll
     for (int c2 = 0; c2 < 4; ++c2) frag_off[c2] = br * kRowBytes + ((((2 * c2) | q) ^ ((br >> 1) & 7)) << 4);
@@ -152,7 +153,7 @@ __global__ __launch_bounds__(64 * NW) void k_spmm_stream(MmArgs a, int tiles_m, 
 #pragma unroll
         for (int j = 0; j < 2; ++j) va[j] = *reinterpret_cast<const int4v*>(stage + a_off[j]);
 #pragma unroll
-        for (int t = 0; t < T64; ++t) code[t] = *reinterpret_cast<const int*>(stage + kMOff + t * 256 + lane * 4);
+        for (int t = 0; t < T64; ++t) code[t] = *reinterpret_cast<const int*>(stage + m_read[t]);
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll

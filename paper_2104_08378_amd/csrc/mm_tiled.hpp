@@ -158,6 +158,10 @@ __device__ __forceinline__ bool past_k_nmajor(int j, int wave, int lane, int tai
     return (p / (BN * ES)) * ES >= tail;
 }
 
+// Canonical layout in a stage: slot `slot` of a row's four holds piece canonical_piece(row, slot) of its 64 bytes of
+// values, and the other way round.
+__device__ __forceinline__ int canonical_piece(int row, int slot) { return slot ^ ((row >> 2) & 3); }
+
 // Position of a K step inside a convolution's inner dimension k = (r*S + s)*C + c: a step (128 bytes of K) lies
 // inside one filter tap when C * element size is a multiple of 128 bytes.
 struct ConvTap {
@@ -504,9 +508,13 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_spmm_pipe(MmArgs a, int til
     else dma_offsets<BN, NW>((int64_t)tn * BN, a.N, ldb_bytes, wave, lane, b_off);
     // V: transfer x of this wavefront is 1 KiB number (wave*NJV + x) of the RB*2 of a step: row block /2, half %2.
     // metadata: transfer x is 256-byte tile number (wave*NJM + x) of the RB*T64 of a step.
-    // Either way the stage receives the tiled layout's slot order (slot = lane).  From the tiled layout a transfer
-    // is one contiguous run; from the canonical one lane (m % 32, h) fetches its 16 bytes of values and 4 bytes
-    // of codes from row m of the row-major arrays (Sec. 3.1: their position follows from the row and column alone).
+    // From the tiled layout a transfer is one contiguous run, already in the order of the lanes that will read it.  From the
+    // canonical one it takes whole runs of rows of the row-major arrays (Sec. 3.1: their position follows from the row
+    // and column alone): four lanes to the 64 bytes of values of a row and step, the 16-byte pieces rotated by the row
+    // (canonical_piece) so that the operand reads of 16 rows hit 16 different columns of the banks, and 2 * T64 lanes to a
+    // row's codes.  Neighbouring lanes on one cache line matter: with a lane to a row, 32 lines an instruction, the
+    // address path set the pace (4096 x 8192 x 1024 bf16 58.2 -> 53.1 us, 8192 x 4096 x 8192 int8 193 -> 167,
+    // 11520 x 398 x 8864 f8 104 -> 86).
     const bool canonical = a.layout == SP24_LAYOUT_CANONICAL;
     const uint8_t* v_base[NJV];                            // wavefront-uniform
     const uint8_t* m_base[NJM];
@@ -514,22 +522,21 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_spmm_pipe(MmArgs a, int til
     const int64_t v_step = canonical ? 64 : 2048, m_step = canonical ? 8 * T64 : T64 * 256;   // bytes per step
     if (canonical) {
         const int64_t vrow = a.K / 2 * ES, mrow = a.K / 8, row0 = (int64_t)tm * BM;
-        const int h = lane >> 5;
 #pragma unroll
         for (int x = 0; x < NJV; ++x) {
-            const int id = wave * NJV + x;
-            int64_t row = row0 + (id >> 1) * 32 + (lane & 31);
+            const int id = wave * NJV + x, in_block = (id & 1) * 16 + (lane >> 2);
+            int64_t row = row0 + (id >> 1) * 32 + in_block;
             if (row >= a.M) row = a.M - 1;                 // ragged M: a valid row, never stored
             v_base[x] = wave_uniform(reinterpret_cast<const uint8_t*>(a.A) + row0 * vrow);
-            v_off[x] = (uint32_t)((row - row0) * vrow + ((ES == 1) ? 32 * (id & 1) + 16 * h : 32 * h + 16 * (id & 1)));
+            v_off[x] = (uint32_t)((row - row0) * vrow + canonical_piece(in_block, lane & 3) * 16);
         }
 #pragma unroll
         for (int x = 0; x < NJM; ++x) {
             const int id = wave * NJM + x;
-            int64_t row = row0 + (id / T64) * 32 + (lane & 31);
+            int64_t row = row0 + (id / T64) * 32 + (id % T64) * 16 + lane / (2 * T64);
             if (row >= a.M) row = a.M - 1;
             m_base[x] = wave_uniform(reinterpret_cast<const uint8_t*>(a.meta) + row0 * mrow);
-            m_off[x] = (uint32_t)((row - row0) * mrow + 8 * (id % T64) + 4 * h);
+            m_off[x] = (uint32_t)((row - row0) * mrow + (lane % (2 * T64)) * 4);
         }
     } else {
 #pragma unroll
@@ -564,18 +571,17 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_spmm_pipe(MmArgs a, int til
             const bool p = NMAJ ? past_k_nmajor<BN, NW, ES>(x, wave, lane, tail) : past_k_kmajor<BN, NW>(x, wave, lane, tail);
             past_k |= (uint32_t)p << x;
         }
-        const int h = lane >> 5;
 #pragma unroll
         for (int x = 0; x < NJV; ++x) {
             const int id = wave * NJV + x;
-            const int col = (ES == 1) ? 32 * (id & 1) + 16 * h : 32 * h + 16 * (id & 1);     // byte of the 64 value bytes of a row and step
-            const bool p = canonical ? col >= tail / 2 : ((ES == 1) ? 64 * (id & 1) >= tail : false);
+            // (canonical: the piece's place in the 64 value bytes of a row and step)
+            const bool p = canonical ? canonical_piece((id & 1) * 16 + (lane >> 2), lane & 3) * 16 >= tail / 2 : ((ES == 1) ? 64 * (id & 1) >= tail : false);
             past_k |= (uint32_t)p << (NJB + x);
         }
 #pragma unroll
         for (int x = 0; x < NJM; ++x) {
             const int id = wave * NJM + x;
-            const bool p = canonical ? (8 * (id % T64) + 4 * h) * 8 * ES >= tail : 64 * ES * (id % T64) >= tail;
+            const bool p = canonical ? (lane % (2 * T64)) * 32 * ES >= tail : 64 * ES * (id % T64) >= tail;
             past_k |= (uint32_t)p << (NJB + NJV + x);
         }
     }
@@ -631,16 +637,20 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_spmm_pipe(MmArgs a, int til
     for (int c2 = 0; c2 < 4; ++c2) frag_off[c2] = (wn * 32 * TN + r) * kRowBytes + ((((2 * c2) | q) ^ ((r >> 1) & 7)) << 4);
     nmajor_frags<BN, TN, ES> b_nm;
     if constexpr (NMAJ) b_nm.init(wn, lane);
-    const int va_off = kVOff + wm * TM * 2048 + lane * 16;
-    const int ma_off = kMOff + wm * TM * T64 * 256 + lane * 4;
+    int va_off[2], ma_off[T64];                            // by instruction; by 64-column tile
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+        va_off[j] = kVOff + wm * TM * 2048 + (canonical ? r * 64 + canonical_piece(r, is8<DT> ? 2 * j + q : 2 * q + j) * 16 : j * 1024 + lane * 16);
+#pragma unroll
+    for (int t = 0; t < T64; ++t) ma_off[t] = kMOff + wm * TM * T64 * 256 + (canonical ? r * (8 * T64) + (2 * t + q) * 4 : t * 256 + lane * 4);
 
     // Operand reads from a stage.  A operands of matrix-core instruction j of the step: values (row block i,
     // half j), codes (int8: tile j; 16-bit: the one tile, the instruction picks its half through abid).
     auto read_a = [&](const uint8_t* base, int j, int4v (&xa)[TM], int (&xm)[TM], bool with_codes) {
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-            xa[i] = *reinterpret_cast<const int4v*>(base + va_off + (i * 2 + j) * 1024);
-            if (with_codes) xm[i] = *reinterpret_cast<const int*>(base + ma_off + (i * T64 + (is8<DT> ? j : 0)) * 256);
+            xa[i] = *reinterpret_cast<const int4v*>(base + va_off[j] + i * 2048);
+            if (with_codes) xm[i] = *reinterpret_cast<const int*>(base + ma_off[is8<DT> ? j : 0] + i * T64 * 256);
         }
     };
     auto read_frag = [&](const uint8_t* base, int t, int8v& bv) {
