@@ -323,20 +323,23 @@ static bool tiled_before_streaming(const MmArgs& a)
 // (1024 x 128 x 4096 bf16 16.7 -> 9.9 us, 8192 x 32 x 8192 25.1 -> 14.0, 8192 x 16 x 8192 18.1 -> 13.3; 4096 x 1 x 1024
 // level), past that 0.4 - 1.0 times -- except for 16-bit inputs with N <= 32 up to the 11008 rows from which the tiled
 // kernels take them (9216 x 16 x 4096 17.0 -> 12.3 us in two rounds).
+// More than 512 columns stay with the tiled kernels whatever their number: such products with few rows are convolutions
+// written out, whose results are those of the implicit convolution bit for bit as long as K is summed in one piece.
 static bool stream_first(const MmArgs& a)
 {
-    if (!a.sparse || a.conv.on || a.bo != SP24_B_KMAJOR) return false;
+    if (!a.sparse || a.conv.on || a.bo != SP24_B_KMAJOR || a.N > 512) return false;
     return stream_workgroups(a) <= 256 || (a.N <= 32 && esize_of(a.in) == 2 && a.M < 11008);
 }
 
 // Sparse products that the tiled kernels do not take: tiles of their shape with B staged through registers, or (N-major,
 // few tiles) K split across the wavefronts of a workgroup, which the former leaves idle.  Measured on N-major products
-// with an odd N: below 256 tiles of 128 x 128 the K-splitting kernel is up to twice as fast on long K (1024 x 509 x 4096
-// bf16 20 against 38 us), from there on the staged one (6784 x 939 x 6464: 193 -> 104 us).
+// with an odd N: up to 64 tiles of 128 x 128 the K-splitting kernel is ahead by 10 - 90 % (2048 x 509 x 2048 bf16 12.3
+// against 16.7 us, 512 x 511 x 8192 25.5 against 47.5), from 80 on the staged one by 10 - 50 % (2560 x 509 x 2048 17.3
+// against 20.7, 4096 x 509 x 1024 10.6 against 15.7, 4096 x 257 x 4096 25.7 against 31.6).
 static bool staged_before_ksplit(const MmArgs& a)
 {
     if (a.conv.on || a.bo == SP24_B_KMAJOR) return true;      // the K-splitting kernel does not take them anyway
-    return ((a.M + 127) / 128) * ((a.N + 127) / 128) >= 256;
+    return ((a.M + 127) / 128) * ((a.N + 127) / 128) > 64;
 }
 
 // The kernel for a checked product: streaming (N <= 32), tiled, or general.

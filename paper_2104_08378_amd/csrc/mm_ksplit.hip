@@ -3,17 +3,15 @@
 // The tiled kernels' transfers go straight from memory to LDS and need 16-byte aligned rows; here B passes through
 // registers, loaded 16 bytes per lane from wherever the row starts, and is written to LDS aligned.
 //
-// One workgroup per 64 x 64 tile of D, eight wavefronts that split K among themselves: 64-column tile kb goes to
-// wavefront kb % 8, each accumulates a whole 64 x 64 partial tile, and the eight are added through LDS in wavefront
+// One workgroup per 32 x 64 or 64 x 64 tile of D, eight wavefronts that split K among themselves: 64-column tile kb goes to
+// wavefront kb % 8, each accumulates a whole partial tile, and the eight are added through LDS in wavefront
 // order.  Such products have few tiles (1024 x 509: 128) and would be bound by the latency of their loads; with K
 // split eight ways every compute unit keeps eight times the bytes in flight, and a wavefront's LDS image of B is
 // its own, so the loop has no barrier at all.  The compressed (or dense) first operand goes from memory into
 // registers in the matrix instruction's own lane order.
 //
-// Measured against the general kernel that took these products before (us, operands rotating; the aligned N next to
-// each on the tiled kernels in brackets): 1024 x 509 x 4096 int8 482 -> 15.8; 8192 x 17 x 8192 bf16 443 -> 32.9;
-// 4096 x 1155 x 4096 bf16 676 -> 93 [N = 1152: 36], int8 856 -> 67 [23]; 3744 x 5453 x 1984 f8 1559 -> 171 [43].  On
-// many tiles it is bound by the loads: a 64 x 64 tile moves twice the operand bytes per product of a 128 x 128 one.
+// Measured against the general kernel that took these before (us, operands rotating): 1024 x 509 x 4096 int8 482 -> 12.7;
+// 8192 x 17 x 8192 bf16 443 -> 30; 2048 x 509 x 2048 bf16 12.3.  Products with many tiles go to mm_staged.hpp.
 #include "mm_operands.hpp"
 
 namespace sp24 {
@@ -21,7 +19,7 @@ namespace sp24 {
 namespace {
 
 constexpr int kSplitWaves = 8;
-constexpr int TM = 2, TN = 2;                       // 32 x 32 accumulator tiles per wavefront
+constexpr int TN = 2;                               // 32 x 32 accumulator tiles of a wavefront side by side
 
 // between a wavefront's own LDS writes and reads: the LDS serves them in order, only the compiler must keep it
 __device__ __forceinline__ void wave_order()
@@ -47,7 +45,8 @@ struct dense_rows {
         for (int i = 0; i < TM; ++i)
             src[i] = reinterpret_cast<const uint8_t*>(a.A) + min((block0 + i) * 32 + (lane & 31), a.M - 1) * a.lda * ES + 16 * q;
     }
-    __device__ __forceinline__ void load(int64_t kb, int4v (&v)[TM][NA], uint32_t (&code)[TM]) const
+    __device__ __forceinline__ void load_whole(int64_t kb, int4v (&v)[TM][NA], uint32_t (&code)[TM]) const { load_edge(kb, v, code); }
+    __device__ __forceinline__ void load_edge(int64_t kb, int4v (&v)[TM][NA], uint32_t (&code)[TM]) const
     {
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
@@ -83,14 +82,14 @@ __device__ __forceinline__ void put(const MmArgs& a, int64_t m, int64_t n, ACC v
 
 } // namespace
 
-template <int DT, bool SPARSE>
+template <int DT, bool SPARSE, int TM>
 __global__ __launch_bounds__(64 * kSplitWaves) void k_mm_ksplit(MmArgs a, int tiles_m, int tiles_n)
 {
     constexpr int ES = is8<DT> ? 1 : 2;
-    constexpr int BM = 32 * TM, BN = 32 * TN;
+    constexpr int BN = 32 * TN;
     constexpr int kImage = 64 * BN * ES;                      // 64 K rows of B in LDS
     using acc_t = typename acc_of<DT>::type;
-    constexpr int kRedBytes = kSplitWaves * 16 * 64 * 4;
+    constexpr int kRedBytes = kSplitWaves * TN * 16 * 64 * 4;
     constexpr int kLds = kSplitWaves * kImage > kRedBytes ? kSplitWaves * kImage : kRedBytes;
     __shared__ __attribute__((aligned(1024))) uint8_t lds[kLds];
 
@@ -99,21 +98,18 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_mm_ksplit(MmArgs a, int ti
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 31, q = lane >> 5;
-    const int64_t K = a.K, tiles_k = (K + 63) / 64;
+    const int tiles_k = (int)((a.K + 63) / 64);
 
     using pieces_t = nmajor_pieces<BN, ES, 64, 64>;
-    constexpr int NJ = pieces_t::NJ;
+    using rows_t = typename std::conditional<SPARSE, compressed_rows<DT, TM>, dense_rows<DT, TM>>::type;
+    constexpr int NA = rows_t::NA;
     pieces_t pieces;
     pieces.init(a, tn, lane);
+    rows_t rows;
+    rows.init(a, (int64_t)tm * TM, lane);
     uint8_t* const image = lds + wave * kImage;
     nmajor_frags<BN, TN, ES> frags;
     frags.init(0, lane);
-
-    // ---- A ----
-    using rows_t = typename std::conditional<SPARSE, compressed_rows<DT, TM>, dense_rows<DT, TM>>::type;
-    constexpr int NA = rows_t::NA;
-    rows_t rows;
-    rows.init(a, (int64_t)tm * TM, lane);
 
     acc_t acc[TM][TN];
 #pragma unroll
@@ -121,28 +117,15 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_mm_ksplit(MmArgs a, int ti
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = acc_t{};
 
-    uint4v bv[NJ];
-    int4v av[TM][NA];
-    uint32_t code[TM];
-    if (wave < tiles_k) {
-        pieces.load((int64_t)wave * 64, bv);
-        rows.load(wave, av, code);
-    }
-    for (int64_t kb = wave; kb < tiles_k; kb += kSplitWaves) {
+    struct Tile {
+        uint4v b[pieces_t::NJ];
+        int4v v[TM][NA];
+        uint32_t code[TM];
+    };
+    auto compute = [&](const Tile& t) {
         wave_order();                                         // behind the reads of the previous tile
-        pieces.store(image, bv);
-        int4v x[TM][NA];
-        uint32_t xc[TM];
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-#pragma unroll
-            for (int s = 0; s < NA; ++s) x[i][s] = av[i][s];
-            xc[i] = code[i];
-        }
+        pieces.store(image, t.b);
         wave_order();
-        const int64_t next = kb + kSplitWaves < tiles_k ? kb + kSplitWaves : kb;   // the last tile is loaded again, unused
-        pieces.load(next * 64, bv);
-        rows.load(next, av, code);
         if constexpr (SPARSE) {
             constexpr int NI = ES;                            // instructions per tile: 8-bit one of 64 columns, 16-bit two of 32
 #pragma unroll
@@ -155,8 +138,8 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_mm_ksplit(MmArgs a, int ti
                     b[4] = hi[0]; b[5] = hi[1]; b[6] = hi[2]; b[7] = hi[3];
 #pragma unroll
                     for (int i = 0; i < TM; ++i) {
-                        if (s == 0) acc[i][nj] = smfmac32<DT, 0>(x[i][0], b, acc[i][nj], (int)xc[i]);
-                        else acc[i][nj] = smfmac32<DT, 1>(x[i][NA - 1], b, acc[i][nj], (int)xc[i]);
+                        if (s == 0) acc[i][nj] = smfmac32<DT, 0>(t.v[i][0], b, acc[i][nj], (int)t.code[i]);
+                        else acc[i][nj] = smfmac32<DT, 1>(t.v[i][NA - 1], b, acc[i][nj], (int)t.code[i]);
                     }
                 }
         } else {
@@ -166,52 +149,88 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_mm_ksplit(MmArgs a, int ti
                 for (int nj = 0; nj < TN; ++nj) {
                     const int4v b = __builtin_bit_cast(int4v, frags.piece(image, s, nj));
 #pragma unroll
-                    for (int i = 0; i < TM; ++i) acc[i][nj] = mfma32<DT>(x[i][s], b, acc[i][nj]);
+                    for (int i = 0; i < TM; ++i) acc[i][nj] = mfma32<DT>(t.v[i][s], b, acc[i][nj]);
                 }
         }
+    };
+    // The tiles whose pieces all lie inside B: this wavefront's are wave, wave + 8, ..., the next one's loads under way
+    // while a tile is computed.  (No branch around a load in the loop: the compiler then leaves them in flight.  More of
+    // them, two to four tiles ahead, cost registers and time: 1024 x 509 x 4096 int8 12.7 us with one, 13.1 with three.)
+    const int whole = (int)pieces.whole_groups();
+    Tile tile;
+    auto load = [&](int kb) {
+        pieces.load_whole(kb, tile.b);
+        rows.load_whole(kb, tile.v, tile.code);
+    };
+    if (wave < whole) {
+        load(wave);
+        int kb = wave;
+        for (; kb + kSplitWaves < whole; kb += kSplitWaves) {
+            if constexpr (TM == 1) {
+                const Tile now = tile;
+                load(kb + kSplitWaves);
+                compute(now);
+            } else {                                          // two workgroups to a unit hide more than a second set of registers
+                compute(tile);
+                load(kb + kSplitWaves);
+            }
+        }
+        compute(tile);
     }
+    for (int kb = whole; kb < tiles_k; ++kb)
+        if (kb % kSplitWaves == wave) {
+            pieces.load_edge(kb, tile.b);
+            rows.load_edge(kb, tile.v, tile.code);
+            compute(tile);
+        }
 
-    // the eight partial tiles, added in wavefront order, one 32 x 32 block at a time
-    uint32_t (*red)[16][64] = reinterpret_cast<uint32_t (*)[16][64]>(lds);
+    // the eight partial tiles, added in wavefront order, 32 rows at a time
+    uint32_t (*red)[TN * 16][64] = reinterpret_cast<uint32_t (*)[TN * 16][64]>(lds);
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i) {
+        __syncthreads();                                      // the images, or the previous rows, are done with
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            __syncthreads();                                  // the images, or the previous block, are done with
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 auto v = acc[i][j][e];
-                red[wave][e][lane] = __builtin_bit_cast(uint32_t, v);
+                red[wave][j * 16 + e][lane] = __builtin_bit_cast(uint32_t, v);
             }
-            __syncthreads();
+        __syncthreads();
+#pragma unroll
+        for (int x = 0; x < TN * 16 / kSplitWaves; ++x) {
+            const int id = wave + x * kSplitWaves, j = id >> 4, e = id & 15;
+            using val_t = typename std::conditional<DT == SP24_I8, int, float>::type;
+            val_t sum = 0;
+#pragma unroll
+            for (int w = 0; w < kSplitWaves; ++w) sum += __builtin_bit_cast(val_t, red[w][id][lane]);
+            const int64_t m = ((int64_t)tm * TM + i) * 32 + 8 * (e / 4) + 4 * q + (e % 4);
             const int64_t n = (int64_t)tn * BN + j * 32 + r;
-#pragma unroll
-            for (int e = wave; e < 16; e += kSplitWaves) {
-                using val_t = typename std::conditional<DT == SP24_I8, int, float>::type;
-                val_t sum = 0;
-#pragma unroll
-                for (int w = 0; w < kSplitWaves; ++w) sum += __builtin_bit_cast(val_t, red[w][e][lane]);
-                const int64_t m = (int64_t)tm * BM + i * 32 + 8 * (e / 4) + 4 * q + (e % 4);
-                if (m < a.M && n < a.N) put<DT>(a, m, n, sum);
-            }
+            if (m < a.M && n < a.N) put<DT>(a, m, n, sum);
         }
+    }
 }
 
 template <int DT>
 static sp24_status run_ksplit(const MmArgs& a, hipStream_t st)
 {
-    const int tiles_m = (int)((a.M + 32 * TM - 1) / (32 * TM)), tiles_n = (int)((a.N + 32 * TN - 1) / (32 * TN));
-    const dim3 grid((unsigned)(tiles_m * tiles_n)), block(64 * kSplitWaves);
-    if (a.sparse) k_mm_ksplit<DT, true><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
-    else k_mm_ksplit<DT, false><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
-    return hipGetLastError() == hipSuccess ? SP24_OK : SP24_ERR_LAUNCH;
+    auto run = [&](auto kernel, int bm) {
+        const int tiles_m = (int)((a.M + bm - 1) / bm), tiles_n = (int)((a.N + 32 * TN - 1) / (32 * TN));
+        kernel<<<dim3((unsigned)(tiles_m * tiles_n)), dim3(64 * kSplitWaves), 0, st>>>(a, tiles_m, tiles_n);
+        return hipGetLastError() == hipSuccess ? SP24_OK : SP24_ERR_LAUNCH;
+    };
+    // Tiles of 32 rows while that gives no more than one workgroup a compute unit (1024 x 509 x 4096 int8 16.2 -> 12.7 us,
+    // 8192 x 17 x 2048 bf16 13.1 -> 9.6); past that the 64-row tile, whose B serves twice the rows.
+    const bool low = ((a.M + 31) / 32) * ((a.N + 63) / 64) <= 256;
+    if (a.sparse) return low ? run(k_mm_ksplit<DT, true, 1>, 32) : run(k_mm_ksplit<DT, true, 2>, 64);
+    return low ? run(k_mm_ksplit<DT, false, 1>, 32) : run(k_mm_ksplit<DT, false, 2>, 64);
 }
 
 sp24_status launch_mm_ksplit(const MmArgs& a, hipStream_t st, bool* handled)
 {
     *handled = false;
-    if (a.conv.on || a.bo != SP24_B_NMAJOR || a.k_slices > 1) return SP24_OK;
-    if (a.M > ((int64_t)1 << 30) || a.N > ((int64_t)1 << 30) || ((a.M + 63) / 64) * ((a.N + 63) / 64) >= ((int64_t)1 << 30)) return SP24_OK;
+    if (a.conv.on || a.bo != SP24_B_NMAJOR || a.k_slices > 1 || a.K > ((int64_t)1 << 30)) return SP24_OK;
+    if (a.M > ((int64_t)1 << 30) || a.N > ((int64_t)1 << 30) || ((a.M + 31) / 32) * ((a.N + 63) / 64) >= ((int64_t)1 << 30)) return SP24_OK;
     *handled = true;
     if (a.in == SP24_I8) return run_ksplit<SP24_I8>(a, st);
     if (a.in == SP24_F8) return run_ksplit<SP24_F8>(a, st);

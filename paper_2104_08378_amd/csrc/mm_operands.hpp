@@ -58,24 +58,30 @@ struct nmajor_pieces {
         reach = (ROWS - 1) * ldb + col0 + (valid - 1) * 16 + 16;   // end of the last piece, from the first row
         dst0 = row0 * kRowB + ((c ^ nmajor_swizzle<ES>(row0, kChunks)) << 4);
     }
-    __device__ __forceinline__ void load(int64_t k0, uint4v (&v)[NJ]) const
+    // groups of ROWS K rows, from the first on, all of whose pieces lie inside B
+    __device__ __forceinline__ int64_t whole_groups() const
     {
-        const int64_t first = k0 * ldb;
-        if (k0 + ROWS <= K && first + reach <= b_bytes) {
-            const uint8_t* p = B + first + row0 * ldb + src0;
+        return b_bytes < reach ? 0 : min(K / ROWS, (b_bytes - reach) / (ROWS * ldb) + 1);
+    }
+    // such a group.  (A kernel keeps the loads of several groups in flight, and only a loop without branches lets the
+    // compiler count them: the groups past these are a phase of their own.)
+    __device__ __forceinline__ void load_whole(int64_t group, uint4v (&v)[NJ]) const
+    {
+        const uint8_t* p = B + group * ROWS * ldb + row0 * ldb + src0;
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) v[j] = load16_any(p + j * kRowsPerPiece * ldb);
-        } else {
-            // the last rows: pieces that would end past the last element are read up to it and moved into place (B has
-            // 32 bytes at least), rows past K are zeros
+        for (int j = 0; j < NJ; ++j) v[j] = load16_any(p + j * kRowsPerPiece * ldb);
+    }
+    // the last rows: pieces that would end past the last element are read up to it and moved into place (B has 32
+    // bytes at least), rows past K are zeros
+    __device__ __forceinline__ void load_edge(int64_t group, uint4v (&v)[NJ]) const
+    {
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                const int64_t k = k0 + row0 + j * kRowsPerPiece;
-                const int64_t at = min(k, K - 1) * ldb + src0;
-                const int64_t over = max((int64_t)0, at + 16 - b_bytes);
-                const uint4v x = shift_down(load16_any(B + at - over), (int)over);
-                v[j] = k < K ? x : uint4v{0u, 0u, 0u, 0u};
-            }
+        for (int j = 0; j < NJ; ++j) {
+            const int64_t k = group * ROWS + row0 + j * kRowsPerPiece;
+            const int64_t at = min(k, K - 1) * ldb + src0;
+            const int64_t over = max((int64_t)0, at + 16 - b_bytes);
+            const uint4v x = shift_down(load16_any(B + at - over), (int)over);
+            v[j] = k < K ? x : uint4v{0u, 0u, 0u, 0u};
         }
     }
     __device__ __forceinline__ void store(uint8_t* image, const uint4v (&v)[NJ]) const
@@ -119,20 +125,20 @@ struct compressed_rows {
         m_step = canonical ? 8 : 256;
         piece_step = canonical ? 16 : 1024;
     }
-    // 64-column tile kb.  What lies past K comes from a row of zeros: no load is skipped, so that the number of loads
-    // in flight does not depend on the tile and the compiler's waits stay partial.
-    __device__ __forceinline__ void load(int64_t kb, int4v (&v)[TM][NA], uint32_t (&code)[TM]) const
+    // 64-column tile kb, all of it before K
+    __device__ __forceinline__ void load_whole(int64_t kb, int4v (&v)[TM][NA], uint32_t (&code)[TM]) const
     {
-        const int64_t left = K - kb * 64;
-        if (left >= 64) {
 #pragma unroll
-            for (int i = 0; i < TM; ++i) {
+        for (int i = 0; i < TM; ++i) {
 #pragma unroll
-                for (int s = 0; s < NA; ++s) v[i][s] = __builtin_bit_cast(int4v, load16_aligned(v_src[i] + kb * v_step + s * piece_step));
-                code[i] = load_any<uint32_t>(m_src[i] + kb * m_step);   // K a multiple of 16 only: codes of odd rows start at 2-byte places
-            }
-            return;
+            for (int s = 0; s < NA; ++s) v[i][s] = __builtin_bit_cast(int4v, load16_aligned(v_src[i] + kb * v_step + s * piece_step));
+            code[i] = load_any<uint32_t>(m_src[i] + kb * m_step);
         }
+    }
+    // any tile: what lies past K comes from a row of zeros (K may end in the middle of a word of codes)
+    __device__ __forceinline__ void load_edge(int64_t kb, int4v (&v)[TM][NA], uint32_t (&code)[TM]) const
+    {
+        const int left = (int)min(max(K - kb * 64, (int64_t)0), (int64_t)64);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
 #pragma unroll

@@ -83,7 +83,8 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_mm_skinny(MmArgs a)
                 if (canonical) {
                     int4v v[1][rows.NA];
                     uint32_t code[1];
-                    rows.load(kb_first + kb, v, code);       // zeros past K; a slice ends at its own last tile
+                    if ((kb_first + kb) * 64 + 64 <= a.K) rows.load_whole(kb_first + kb, v, code);
+                    else rows.load_edge(kb_first + kb, v, code);   // zeros past K; a slice ends at its own last tile
                     codes[u] = code[0];
 #pragma unroll
                     for (int s = 0; s < rows.NA; ++s) va[u][s] = ok ? __builtin_bit_cast(uint4v, v[0][s]) : zero4;

@@ -11,12 +11,15 @@
 // the tiled kernels, so that fragment reads have no bank conflicts); A goes from memory into registers in the matrix
 // instruction's own lane order, also two steps ahead.  One barrier per step, which waits for LDS only: the
 // loads of the next steps stay in flight across it.  Past the barrier of step s nobody reads the image of step s - 1
-// any more, which is the one that step s + 1 writes.  All waits for loads are the compiler's own.
+// any more, which is the one that step s + 1 writes.  All waits for loads are the compiler's own, and the loop has no
+// branch around a load, so that it can leave the younger ones in flight: it covers the steps that lie wholly inside both
+// operands, and the last ones follow as a phase of their own.
 //
 // Bound by the latency and the issue of those loads: a tile moves the same bytes per product as a 128 x 128 tile of the
 // tiled kernels.  Measured against the general and the K-splitting kernels that took these before (us): sparse 3x3
-// convolution, 43 images of 28x28, 96 -> 192 channels, bf16 417 -> 38; 18624 x 552 x 5392 bf16 canonical 4667 -> 217;
-// 2304 x 1411 x 400 f16 canonical 135 -> 12; N-major 6784 x 939 x 6464 bf16 193 -> 104.
+// convolution, 43 images of 28x28, 96 -> 192 channels, bf16 417 -> 32; 93 images of 15x15, 96 -> 96, 121 -> 15;
+// 18624 x 552 x 5392 bf16 canonical 4667 -> 245; 2304 x 1411 x 400 f16 canonical 135 -> 11; N-major 6784 x 939 x 6464 bf16
+// 193 -> 90, 4096 x 4095 x 4096 bf16 125, int8 83.
 #pragma once
 #include "mm_operands.hpp"
 
@@ -115,7 +118,7 @@ struct staged_b<DT, 1, BN> {
 template <int DT, int BN>
 struct staged_b<DT, 2, BN> : nmajor_pieces<BN, is8<DT> ? 1 : 2, is8<DT> ? 128 : 64, 256> {
     using base = nmajor_pieces<BN, is8<DT> ? 1 : 2, is8<DT> ? 128 : 64, 256>;
-    __device__ __forceinline__ void load(int step, uint4v (&v)[base::NJ]) { base::load((int64_t)step * (is8<DT> ? 128 : 64), v); }
+    __device__ __forceinline__ void load(int step, uint4v (&v)[base::NJ]) { base::load_whole(step, v); }
 };
 
 // every LDS access of this wavefront is done, then the workgroup's barrier; loads stay in flight
@@ -142,8 +145,7 @@ __global__ __launch_bounds__(256, 2) void k_spmm_staged(MmArgs a, int tiles_m, i
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
     const int r = lane & 31, q = lane >> 5;
-    const int64_t tiles_k = (a.K + 63) / 64;
-    const int nsteps = (int)((tiles_k + T64 - 1) / T64);
+    const int nsteps = (int)((a.K + 64 * T64 - 1) / (64 * T64));
 
     b_t b;
     b.init(a, tn, tid);
@@ -152,10 +154,6 @@ __global__ __launch_bounds__(256, 2) void k_spmm_staged(MmArgs a, int tiles_m, i
     struct A {
         int4v v[T64][TM][a_t::NA];
         uint32_t code[T64][TM];
-    };
-    auto load_a = [&](int step, A& x) {
-#pragma unroll
-        for (int t = 0; t < T64; ++t) rows.load((int64_t)step * T64 + t, x.v[t], x.code[t]);
     };
 
     // fragment reads: as in the tiled kernels
@@ -172,10 +170,7 @@ __global__ __launch_bounds__(256, 2) void k_spmm_staged(MmArgs a, int tiles_m, i
 
     uint4v bv[2][b_t::NJ];
     A av[2];
-    auto do_step = [&](int step, uint4v (&vb)[b_t::NJ], A& va, uint8_t* image) {
-        b.store(image, vb);
-        b.load(step + 2, vb);                                 // past the last step: zeros, unused
-        lds_barrier();
+    auto compute = [&](const A& va, const uint8_t* image) {
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -199,19 +194,59 @@ __global__ __launch_bounds__(256, 2) void k_spmm_staged(MmArgs a, int tiles_m, i
                     else acc[i][nj] = smfmac32<DT, 1>(va.v[0][i][a_t::NA - 1], f, acc[i][nj], (int)va.code[0][i]);
                 }
             }
-        load_a(step + 2, va);
     };
-    b.load(0, bv[0]);
-    load_a(0, av[0]);
-    b.load(1, bv[1]);
-    load_a(1, av[1]);
-    int step = 0;
-    for (; step + 2 <= nsteps; step += 2) {
-        do_step(step, bv[0], av[0], lds);
-        do_step(step + 1, bv[1], av[1], lds + kImage);
+    // the steps that lie wholly inside both operands; past the last one the next (N-major: the last again), unused
+    auto sweep = [&](int n) {
+        auto load_b = [&](int step, uint4v (&v)[b_t::NJ]) { b.load(BSRC == 2 ? min(step, n - 1) : step, v); };
+        auto load_a = [&](int step, A& x) {
+#pragma unroll
+            for (int t = 0; t < T64; ++t) rows.load_whole((int64_t)min(step, n - 1) * T64 + t, x.v[t], x.code[t]);
+        };
+        auto do_step = [&](int step, uint4v (&vb)[b_t::NJ], A& va, uint8_t* image) {
+            b.store(image, vb);
+            load_b(step + 2, vb);
+            lds_barrier();
+            // the loads stay where they are written: dealt out among the arithmetic they took 8 - 15 % longer (not so the
+            // convolution's, which are 2 - 4 % faster that way)
+            if constexpr (BSRC != 1) __builtin_amdgcn_sched_barrier(0);
+            compute(va, image);
+            if constexpr (BSRC != 1) __builtin_amdgcn_sched_barrier(0);
+            load_a(step + 2, va);
+            if constexpr (BSRC != 1) __builtin_amdgcn_sched_barrier(0);
+        };
+        load_b(0, bv[0]);
+        load_a(0, av[0]);
+        load_b(1, bv[1]);
+        load_a(1, av[1]);
+        int step = 0;
+        for (; step + 2 <= n; step += 2) {
+            do_step(step, bv[0], av[0], lds);
+            do_step(step + 1, bv[1], av[1], lds + kImage);
+        }
+        if (step < n) do_step(step, bv[0], av[0], lds);
+        lds_barrier();                                        // LDS is free
+    };
+    int whole = (int)(a.K / (64 * T64));
+    if constexpr (BSRC == 2) whole = (int)b.whole_groups();
+    if (whole > 0) sweep(whole);
+    auto edge = [&](int step, const uint4v (&vb)[b_t::NJ]) {
+        b.store(lds, vb);
+#pragma unroll
+        for (int t = 0; t < T64; ++t) rows.load_edge((int64_t)step * T64 + t, av[0].v[t], av[0].code[t]);
+        lds_barrier();
+        compute(av[0], lds);
+        lds_barrier();
+    };
+    if constexpr (BSRC == 2) {
+        for (int step = whole; step < nsteps; ++step) {
+            b.load_edge(step, bv[0]);
+            edge(step, bv[0]);
+        }
+    } else if (whole < nsteps) {                              // its pieces of B are under way already
+        if (whole == 0) b.load(0, bv[0]);
+        if (whole % 2 == 0) edge(whole, bv[0]);
+        else edge(whole, bv[1]);
     }
-    if (step < nsteps) do_step(step, bv[0], av[0], lds);
-    lds_barrier();                                            // LDS becomes store scratch
 
     const int64_t row_base = ((int64_t)tm * WM + wm) * TM * 32, col_base = (int64_t)tn * BN + wn * TN * 32;
     auto put = [&](auto out_c) {
@@ -240,10 +275,13 @@ static sp24_status run_staged_from(const MmArgs& a, hipStream_t st)
         kernel<<<dim3((unsigned)(tiles_m * tiles_n)), dim3(256), 0, st>>>(a, tiles_m, tiles_n);
         return hipGetLastError() == hipSuccess ? SP24_OK : SP24_ERR_LAUNCH;
     };
-    // as many rows as there are; tiles of 64 rows also while the large ones would not give every compute unit one
+    // As many rows as there are; tiles of 64 rows also while the large ones would not give every compute unit one.  Two by two
+    // wavefronts also there: side by side (1 x 4), each would load the same rows of A again, and the address path is the
+    // bound (4096 x 509 x 4096 N-major bf16 34 -> 27 us, 4096 x 509 x 1024 12.8 -> 10.6).  From 256 tiles on the large ones
+    // are 20 - 50 % faster (4096 x 4095 x 4096: 185 -> 125), convolutions and 8-bit gathers within 15 % either way.
     const int64_t large = ((a.M + 127) / 128) * ((a.N + 127) / 128);
     if (a.M <= 32) return run(k_spmm_staged<DT, BSRC, 1, 4, 1, 1>, 32, 128);
-    if (a.M <= 64 || large < 256) return run(k_spmm_staged<DT, BSRC, 1, 4, 2, 1>, 64, 128);
+    if (a.M <= 64 || large < 256) return run(k_spmm_staged<DT, BSRC, 2, 2, 1, 2>, 64, 128);
     return run(k_spmm_staged<DT, BSRC, 2, 2, 2, 2>, 128, 128);
 }
 
