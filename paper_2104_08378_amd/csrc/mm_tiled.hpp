@@ -524,19 +524,20 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_spmm_pipe(MmArgs a, int til
         const int64_t vrow = a.K / 2 * ES, mrow = a.K / 8, row0 = (int64_t)tm * BM;
 #pragma unroll
         for (int x = 0; x < NJV; ++x) {
-            const int id = wave * NJV + x, in_block = (id & 1) * 16 + (lane >> 2);
+            const int id = wave * NJV + x, in_block = CONV ? lane & 31 : (id & 1) * 16 + (lane >> 2);
             int64_t row = row0 + (id >> 1) * 32 + in_block;
             if (row >= a.M) row = a.M - 1;                 // ragged M: a valid row, never stored
             v_base[x] = wave_uniform(reinterpret_cast<const uint8_t*>(a.A) + row0 * vrow);
-            v_off[x] = (uint32_t)((row - row0) * vrow + canonical_piece(in_block, lane & 3) * 16);
+            const int piece = !CONV ? canonical_piece(in_block, lane & 3) : is8<DT> ? 2 * (id & 1) + q : 2 * q + (id & 1);
+            v_off[x] = (uint32_t)((row - row0) * vrow + piece * 16);
         }
 #pragma unroll
         for (int x = 0; x < NJM; ++x) {
             const int id = wave * NJM + x;
-            int64_t row = row0 + (id / T64) * 32 + (id % T64) * 16 + lane / (2 * T64);
+            int64_t row = row0 + (id / T64) * 32 + (CONV ? lane & 31 : (id % T64) * 16 + lane / (2 * T64));
             if (row >= a.M) row = a.M - 1;
             m_base[x] = wave_uniform(reinterpret_cast<const uint8_t*>(a.meta) + row0 * mrow);
-            m_off[x] = (uint32_t)((row - row0) * mrow + (lane % (2 * T64)) * 4);
+            m_off[x] = (uint32_t)((row - row0) * mrow + (CONV ? 8 * (id % T64) + 4 * q : (lane % (2 * T64)) * 4));
         }
     } else {
 #pragma unroll
@@ -637,12 +638,14 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_spmm_pipe(MmArgs a, int til
     for (int c2 = 0; c2 < 4; ++c2) frag_off[c2] = (wn * 32 * TN + r) * kRowBytes + ((((2 * c2) | q) ^ ((r >> 1) & 7)) << 4);
     nmajor_frags<BN, TN, ES> b_nm;
     if constexpr (NMAJ) b_nm.init(wn, lane);
-    int va_off[2], ma_off[T64];                            // by instruction; by 64-column tile
+    // by instruction; by 64-column tile.  (A convolution's stage holds the canonical layout in the tiled one's order, whose
+    // offsets are constants apart: the gather of B needs the registers, and a second offset cost it 1 - 2 %.)
+    int va_off[2], ma_off[T64];
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-        va_off[j] = kVOff + wm * TM * 2048 + (canonical ? r * 64 + canonical_piece(r, is8<DT> ? 2 * j + q : 2 * q + j) * 16 : j * 1024 + lane * 16);
+        va_off[j] = kVOff + wm * TM * 2048 + (canonical && !CONV ? r * 64 + canonical_piece(r, is8<DT> ? 2 * j + q : 2 * q + j) * 16 : j * 1024 + lane * 16);
 #pragma unroll
-    for (int t = 0; t < T64; ++t) ma_off[t] = kMOff + wm * TM * T64 * 256 + (canonical ? r * (8 * T64) + (2 * t + q) * 4 : t * 256 + lane * 4);
+    for (int t = 0; t < T64; ++t) ma_off[t] = kMOff + wm * TM * T64 * 256 + (canonical && !CONV ? r * (8 * T64) + (2 * t + q) * 4 : t * 256 + lane * 4);
 
     // Operand reads from a stage.  A operands of matrix-core instruction j of the step: values (row block i,
     // half j), codes (int8: tile j; 16-bit: the one tile, the instruction picks its half through abid).
