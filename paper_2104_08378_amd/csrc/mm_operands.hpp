@@ -33,6 +33,26 @@ __device__ __forceinline__ uint4v shift_down(uint4v v, int bytes)
                   __builtin_amdgcn_alignbyte(0u, v[3], n)};
 }
 
+// result element (m, n) from the accumulated value
+template <int DT, typename ACC>
+__device__ __forceinline__ void put(const MmArgs& a, int64_t m, int64_t n, ACC v)
+{
+    const int64_t at = m * a.ldd + n;
+    if constexpr (DT == SP24_I8) {
+        float s = 0.0f, b = 0.0f;
+        if (a.out != SP24_I32) epilogue_row(a.epi, m, s, b);
+        if (a.out == SP24_I32) store_bits<SP24_I32>(a.D, at, (uint32_t)v);
+        else if (a.out == SP24_I8) store_bits<SP24_I8>(a.D, at, output_bits<SP24_I8>(v, s, b, a.epi));
+        else if (a.out == SP24_F32) store_bits<SP24_F32>(a.D, at, output_bits<SP24_F32>(v, s, b, a.epi));
+        else if (a.out == SP24_F16) store_bits<SP24_F16>(a.D, at, output_bits<SP24_F16>(v, s, b, a.epi));
+        else store_bits<SP24_BF16>(a.D, at, output_bits<SP24_BF16>(v, s, b, a.epi));
+    } else {
+        if (a.out == SP24_F32) store_out<SP24_F32>(a.D, at, v);
+        else if (a.out == SP24_F16) store_out<SP24_F16>(a.D, at, v);
+        else store_out<SP24_BF16>(a.D, at, v);
+    }
+}
+
 // The pieces (16 bytes) of ROWS K rows x BN columns of an N-major B that one of NT threads carries into an LDS image
 // of the layout that nmajor_frags reads: rows row0, row0 + kRowsPerPiece, ..., chunk c of each.
 template <int BN, int ES, int ROWS, int NT>

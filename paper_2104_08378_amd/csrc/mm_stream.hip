@@ -28,26 +28,6 @@ __device__ __forceinline__ void count_down(F&& f)
     }
 }
 
-// result element (m, n) from the accumulated value
-template <int DT, typename ACC>
-__device__ __forceinline__ void put(const MmArgs& a, int64_t m, int64_t n, ACC v)
-{
-    const int64_t at = m * a.ldd + n;
-    if constexpr (DT == SP24_I8) {
-        float s = 0.0f, b = 0.0f;
-        if (a.out != SP24_I32) epilogue_row(a.epi, m, s, b);
-        if (a.out == SP24_I32) store_bits<SP24_I32>(a.D, at, (uint32_t)v);
-        else if (a.out == SP24_I8) store_bits<SP24_I8>(a.D, at, output_bits<SP24_I8>(v, s, b, a.epi));
-        else if (a.out == SP24_F32) store_bits<SP24_F32>(a.D, at, output_bits<SP24_F32>(v, s, b, a.epi));
-        else if (a.out == SP24_F16) store_bits<SP24_F16>(a.D, at, output_bits<SP24_F16>(v, s, b, a.epi));
-        else store_bits<SP24_BF16>(a.D, at, output_bits<SP24_BF16>(v, s, b, a.epi));
-    } else {
-        if (a.out == SP24_F32) store_out<SP24_F32>(a.D, at, v);
-        else if (a.out == SP24_F16) store_out<SP24_F16>(a.D, at, v);
-        else store_out<SP24_BF16>(a.D, at, v);
-    }
-}
-
 } // namespace
 
 template <int DT, int BR, int NW, int NS>
