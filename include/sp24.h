@@ -25,7 +25,9 @@
  *     (a hipStream_t; NULL = the default stream).  Results are valid once the
  *     caller has synchronised that stream.
  *   - All validation happens on the host before any launch: a call that
- *     returns anything but SP24_OK has launched nothing and written nothing.
+ *     returns anything but SP24_OK or SP24_ERR_LAUNCH has launched nothing and
+ *     written nothing.  SP24_ERR_LAUNCH is what the HIP runtime reports after a
+ *     launch, an error that it held from before the call included.
  *   - Leading dimensions are in elements.  A, P, V and meta must be 16-byte
  *     aligned and every row of A and P must start 16-byte aligned
  *     (ld * element_size % 16 == 0); B and D need only the alignment of their

@@ -4,8 +4,10 @@
 //
 // Every function takes the arguments of the sp24.py function of the same name, in its order, positionally.  It handles
 // the call when everything about it is as documented and returns the result; when anything is not -- a wrong type,
-// shape, stride or device, or a status other than SP24_OK, in which case nothing was launched -- it returns None, and
-// the Python code behind it goes through the same call step by step and raises what is to be raised.
+// shape, stride or device, or a status of the library's own checks, all of which come before any launch -- it returns
+// None, and the Python code behind it goes through the same call step by step and raises what is to be raised.
+// SP24_ERR_LAUNCH may come after a launch (an error that the runtime held from before the call; the second kernel of a
+// split product): it is raised from here, so that no call is made twice and no error is lost.
 #include <Python.h>
 
 #include <ATen/ATen.h>
@@ -190,6 +192,20 @@ sp24_status without_gil(F&& f)
 
 PyObject* not_handled() { Py_RETURN_NONE; }
 
+// What a status other than SP24_OK comes to.  (module: this one, which holds sp24.py's exception as Sp24Error.)
+PyObject* refused(PyObject* module, sp24_status s, const char* where)
+{
+    if (s != SP24_ERR_LAUNCH) return not_handled();
+    PyObject* type = PyObject_GetAttrString(module, "Sp24Error");
+    if (!type) return nullptr;
+    if (PyObject* error = PyObject_CallFunction(type, "is", (int)s, where)) {
+        PyErr_SetObject(type, error);
+        Py_DECREF(error);
+    }
+    Py_DECREF(type);
+    return nullptr;
+}
+
 // First operand of a product: the compressed pair (arguments 0 and 1) or a dense matrix (argument 0).
 struct FirstOperand {
     const at::Tensor* A = nullptr;
@@ -234,7 +250,7 @@ struct SecondOperand {
 
 // (V, meta, B, out_dtype, b_order, layout, out) / dense: (A, B, out_dtype, b_order, out)
 template <bool SPARSE>
-PyObject* product(PyObject*, PyObject* const* args, Py_ssize_t)
+PyObject* product(PyObject* self, PyObject* const* args, Py_ssize_t)
 {
     constexpr int b = SPARSE ? 2 : 1;
     Call c{args, true};
@@ -255,12 +271,12 @@ PyObject* product(PyObject*, PyObject* const* args, Py_ssize_t)
         return SPARSE ? sp24_spmm(pa, pm, pb, pd, a.M, x.N, a.K, x.ldb, ldd, ti, to, x.order, l, st)
                       : sp24_gemm_dense(pa, pb, pd, a.M, x.N, a.K, a.lda, x.ldb, ldd, ti, to, x.order, st);
     });
-    return s == SP24_OK ? r.object() : not_handled();
+    return s == SP24_OK ? r.object() : refused(self, s, SPARSE ? "sp24_spmm" : "sp24_gemm_dense");
 }
 
 // (V, meta, B, out_dtype, b_order, layout, workspace, out) / dense: (A, B, out_dtype, b_order, workspace, out)
 template <bool SPARSE>
-PyObject* product_splitk(PyObject*, PyObject* const* args, Py_ssize_t)
+PyObject* product_splitk(PyObject* self, PyObject* const* args, Py_ssize_t)
 {
     constexpr int b = SPARSE ? 2 : 1, w = SPARSE ? b + 4 : b + 3;
     Call c{args, true};
@@ -289,12 +305,12 @@ PyObject* product_splitk(PyObject*, PyObject* const* args, Py_ssize_t)
         return SPARSE ? sp24_spmm_splitk(pa, pm, pb, pd, a.M, x.N, a.K, x.ldb, ldd, ti, to, x.order, l, pw, bytes, st)
                       : sp24_gemm_dense_splitk(pa, pb, pd, a.M, x.N, a.K, a.lda, x.ldb, ldd, ti, to, x.order, pw, bytes, st);
     });
-    return s == SP24_OK ? r.object() : not_handled();
+    return s == SP24_OK ? r.object() : refused(self, s, SPARSE ? "sp24_spmm_splitk" : "sp24_gemm_dense_splitk");
 }
 
 // (V, meta, B, out_dtype, w_scale, x_scale, bias, relu, inv_y_scale, b_order, layout, out) / dense: (A, B, ... b_order, out)
 template <bool SPARSE>
-PyObject* product_scaled(PyObject*, PyObject* const* args, Py_ssize_t)
+PyObject* product_scaled(PyObject* self, PyObject* const* args, Py_ssize_t)
 {
     constexpr int b = SPARSE ? 2 : 1, e = b + 2, o = e + 5;
     Call c{args, true};
@@ -319,7 +335,7 @@ PyObject* product_scaled(PyObject*, PyObject* const* args, Py_ssize_t)
         return SPARSE ? sp24_spmm_i8_scaled(pa, pm, pb, pd, a.M, x.N, a.K, x.ldb, ldd, ws, xs, bias, relu, iy, to, x.order, l, st)
                       : sp24_gemm_dense_i8_scaled(pa, pb, pd, a.M, x.N, a.K, a.lda, x.ldb, ldd, ws, xs, bias, relu, iy, to, x.order, st);
     });
-    return s == SP24_OK ? r.object() : not_handled();
+    return s == SP24_OK ? r.object() : refused(self, s, SPARSE ? "sp24_spmm_i8_scaled" : "sp24_gemm_dense_i8_scaled");
 }
 
 // Input and geometry of a convolution: X at argument i, R and S at i + 2 and i + 3, pad and stride at p and p + 1
@@ -350,7 +366,7 @@ struct ConvInput {
 
 // (V, meta, X, out_dtype, R, S, pad, stride, layout, out) / dense: (A, X, ..., stride, out)
 template <bool SPARSE>
-PyObject* conv(PyObject*, PyObject* const* args, Py_ssize_t)
+PyObject* conv(PyObject* self, PyObject* const* args, Py_ssize_t)
 {
     constexpr int i = SPARSE ? 2 : 1, p = i + 4;
     Call c{args, true};
@@ -371,12 +387,12 @@ PyObject* conv(PyObject*, PyObject* const* args, Py_ssize_t)
         return SPARSE ? sp24_spmm_conv2d(pa, pm, px, pd, a.M, x.n, x.H, x.W, x.C, x.R, x.S, x.ph, x.pw, x.sh, x.sw, ldd, ti, to, l, st)
                       : sp24_conv2d_dense(pa, px, pd, a.M, x.n, x.H, x.W, x.C, x.R, x.S, x.ph, x.pw, x.sh, x.sw, a.lda, ldd, ti, to, st);
     });
-    return s == SP24_OK ? r.object() : not_handled();
+    return s == SP24_OK ? r.object() : refused(self, s, SPARSE ? "sp24_spmm_conv2d" : "sp24_conv2d_dense");
 }
 
 // (V, meta, X, out_dtype, R, S, w_scale, x_scale, bias, relu, inv_y_scale, pad, stride, layout, out) / dense: (A, X, ..., stride, out)
 template <bool SPARSE>
-PyObject* conv_scaled(PyObject*, PyObject* const* args, Py_ssize_t)
+PyObject* conv_scaled(PyObject* self, PyObject* const* args, Py_ssize_t)
 {
     constexpr int i = SPARSE ? 2 : 1, e = i + 4, p = e + 5;
     Call c{args, true};
@@ -402,12 +418,12 @@ PyObject* conv_scaled(PyObject*, PyObject* const* args, Py_ssize_t)
         return SPARSE ? sp24_spmm_conv2d_i8_scaled(pa, pm, px, pd, a.M, x.n, x.H, x.W, x.C, x.R, x.S, x.ph, x.pw, x.sh, x.sw, ldd, ws, xs, bias, relu, iy, to, l, st)
                       : sp24_conv2d_dense_i8_scaled(pa, px, pd, a.M, x.n, x.H, x.W, x.C, x.R, x.S, x.ph, x.pw, x.sh, x.sw, a.lda, ldd, ws, xs, bias, relu, iy, to, st);
     });
-    return s == SP24_OK ? r.object() : not_handled();
+    return s == SP24_OK ? r.object() : refused(self, s, SPARSE ? "sp24_spmm_conv2d_i8_scaled" : "sp24_conv2d_dense_i8_scaled");
 }
 
 // (A, out) -> a matrix of A's shape and type
 template <sp24_status (*OP)(const void*, void*, int64_t, int64_t, int64_t, int64_t, sp24_dtype, void*)>
-PyObject* same_shape(PyObject*, PyObject* const* args, Py_ssize_t)
+PyObject* same_shape(PyObject* self, PyObject* const* args, Py_ssize_t)
 {
     Call c{args, true};
     const at::Tensor* A = c.rowmajor(0);
@@ -420,11 +436,11 @@ PyObject* same_shape(PyObject*, PyObject* const* args, Py_ssize_t)
     void *pp = r.t->data_ptr(), *st = stream();
     const int64_t ldp = r.t->stride(0);
     const sp24_status s = without_gil([&] { return OP(pa, pp, M, K, lda, ldp, t, st); });
-    return s == SP24_OK ? r.object() : not_handled();
+    return s == SP24_OK ? r.object() : refused(self, s, OP == sp24_prune ? "sp24_prune" : "sp24_prune_transposable");
 }
 
 // (A, layout, out): out None only -- a pair of new tensors
-PyObject* compress(PyObject*, PyObject* const* args, Py_ssize_t)
+PyObject* compress(PyObject* self, PyObject* const* args, Py_ssize_t)
 {
     Call c{args, true};
     const at::Tensor* A = c.rowmajor(0);
@@ -439,7 +455,7 @@ PyObject* compress(PyObject*, PyObject* const* args, Py_ssize_t)
     const void* pa = A->data_ptr();
     void *pv = V.data_ptr(), *pm = meta.data_ptr(), *st = stream();
     const sp24_status s = without_gil([&] { return sp24_compress(pa, pv, pm, M, K, lda, t, l, st); });
-    if (s != SP24_OK) return not_handled();
+    if (s != SP24_OK) return refused(self, s, "sp24_compress");
     PyObject* pair = PyTuple_New(2);
     if (!pair) return nullptr;
     PyTuple_SET_ITEM(pair, 0, THPVariable_Wrap(std::move(V)));
@@ -448,7 +464,7 @@ PyObject* compress(PyObject*, PyObject* const* args, Py_ssize_t)
 }
 
 // (V, meta, layout, out)
-PyObject* decompress(PyObject*, PyObject* const* args, Py_ssize_t)
+PyObject* decompress(PyObject* self, PyObject* const* args, Py_ssize_t)
 {
     Call c{args, true};
     FirstOperand a(c, true);
@@ -462,12 +478,12 @@ PyObject* decompress(PyObject*, PyObject* const* args, Py_ssize_t)
     void *pp = r.t->data_ptr(), *st = stream();
     const int64_t ldp = r.t->stride(0);
     const sp24_status s = without_gil([&] { return sp24_decompress(pv, pm, pp, a.M, a.K, ldp, t, l, st); });
-    return s == SP24_OK ? r.object() : not_handled();
+    return s == SP24_OK ? r.object() : refused(self, s, "sp24_decompress");
 }
 
 // (W, meta, layout, out): the masked matrix, or (VALUES) its compressed values -- for those out None only
 template <bool VALUES>
-PyObject* masked(PyObject*, PyObject* const* args, Py_ssize_t)
+PyObject* masked(PyObject* self, PyObject* const* args, Py_ssize_t)
 {
     Call c{args, true};
     const at::Tensor* W = c.rowmajor(0);
@@ -487,7 +503,7 @@ PyObject* masked(PyObject*, PyObject* const* args, Py_ssize_t)
     const sp24_status s = without_gil([&] {
         return VALUES ? sp24_compress_masked(pw, pm, pp, M, K, ldw, t, l, st) : sp24_mask_apply(pw, pm, pp, M, K, ldw, ldp, t, l, st);
     });
-    return s == SP24_OK ? r.object() : not_handled();
+    return s == SP24_OK ? r.object() : refused(self, s, VALUES ? "sp24_compress_masked" : "sp24_mask_apply");
 }
 
 // No exception of torch's (an allocation that fails) crosses into the interpreter: the Python code meets it again.

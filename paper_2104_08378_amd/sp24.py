@@ -1,7 +1,8 @@
 """Python binding of libsp24.so: argument marshalling only.
 
 The calls go through ``_sp24_host.so`` (``csrc/host_calls.cpp``), which marshals a well-formed call natively; whatever
-it declines runs the Python code below it, which says what is wrong.
+it declines runs the Python code below it, which says what is wrong.  (A launch that the runtime rejects is raised from
+there: such a call must not be made again.)
 
 Each function mirrors the C entry point of the same name (``include/sp24.h``):
 it checks that the tensors live on the GPU, allocates the outputs with torch,
@@ -93,6 +94,7 @@ def _load_host():
         loader = importlib.machinery.ExtensionFileLoader("_sp24_host", path)
         host = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_sp24_host", path, loader=loader))
         loader.exec_module(host)
+        host.Sp24Error = Sp24Error                # what it raises
         _host = host
     return _host
 

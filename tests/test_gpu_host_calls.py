@@ -80,3 +80,18 @@ def test_refused_calls_raise():
         sp24.sp24_spmm(V, m, W, torch.float32, layout="other")
     with pytest.raises(ValueError):
         sp24.sp24_prune(W.cpu())
+
+
+def test_a_launch_error_is_raised():
+    """An error that the HIP runtime holds from an earlier call comes out of the next launch as SP24_ERR_LAUNCH: it is
+    raised, and the call is not made a second time."""
+    W = torch.randn((64, 128), device="cuda").half()
+    P, want = torch.empty_like(W), sp24.sp24_prune(W)
+    V, m = sp24.sp24_compress(W)
+    torch.cuda.synchronize()
+    for call in (lambda: sp24.sp24_prune(W, out=P), lambda: sp24.sp24_decompress(V, m, out=P)):
+        assert sp24.lib().hipSetDevice(1 << 20) != 0             # no such device: refused by the host, the current one stays
+        with pytest.raises(sp24.Sp24Error) as e:
+            call()
+        assert e.value.status == 6                               # SP24_ERR_LAUNCH
+    assert torch.equal(sp24.sp24_prune(W, out=P), want)          # and it was reported once
