@@ -119,6 +119,10 @@ struct Call {
             return;
         }
         const long x = PyLong_AsLong(PyTuple_GET_ITEM(o, 0)), y = PyLong_AsLong(PyTuple_GET_ITEM(o, 1));
+        if (PyErr_Occurred()) {                        // past a long
+            PyErr_Clear();
+            ok = false;
+        }
         require(x >= 0 && x <= 4096 && y >= 0 && y <= 4096);
         a = (int)x;
         b = (int)y;

@@ -95,3 +95,19 @@ def test_a_launch_error_is_raised():
             call()
         assert e.value.status == 6                               # SP24_ERR_LAUNCH
     assert torch.equal(sp24.sp24_prune(W, out=P), want)          # and it was reported once
+
+
+@pytest.mark.parametrize("pad,stride", [((1 << 70, 0), (1, 1)), ((0, -(1 << 70)), (1, 1)), ((0, 0), (1 << 70, 1)),
+                                        ((0, 0), (1, 1 << 33)), ((-1, 0), (1, 1)), ((0, 0), (0, 1))])
+def test_geometry_out_of_range_raises_as_the_python_path_does(monkeypatch, pad, stride):
+    W = torch.zeros((32, 9 * 16), dtype=torch.float16, device="cuda")
+    X = torch.zeros((1, 4, 4, 16), dtype=torch.float16, device="cuda")
+    V, m = sp24.sp24_compress(W)
+    raised = []
+    for host in (sp24._host, Declines()):
+        monkeypatch.setattr(sp24, "_host", host)
+        for call in (lambda: sp24.sp24_spmm_conv2d(V, m, X, torch.float16, 3, 3, pad, stride), lambda: sp24.sp24_conv2d_dense(W, X, torch.float16, 3, 3, pad, stride)):
+            with pytest.raises(Exception) as e:
+                call()
+            raised.append(e.type)
+    assert raised[:2] == raised[2:]
