@@ -1,5 +1,6 @@
 """Build libsp24.so (hand-written HIP, gfx950 only) in-tree with hipcc, and the native half of the Python binding
-(_sp24_host.so, host code only) with g++ against the installed torch.
+(_sp24_host.so, host code only) with g++ against the installed torch.  Where torch or its headers are not installed that
+half is left out: the library does not need it, and the binding's Python code does without.
 
     python -m paper_2104_08378_amd.build
 
@@ -32,8 +33,14 @@ FLAGS = [
 
 
 def host_flags():
-    import torch
+    """(compile flags, link flags), or None without torch and its headers."""
+    try:
+        import torch
+    except ImportError:
+        return None
     root = os.path.dirname(torch.__file__)
+    if not os.path.exists(os.path.join(root, "include", "torch", "csrc", "autograd", "python_variable.h")):
+        return None
     compile_flags = ["-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
                      f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f"-I{root}/include", f"-I{root}/include/torch/csrc/api/include",
                      "-I/opt/rocm/include", f"-I{sysconfig.get_paths()['include']}"]
@@ -53,10 +60,10 @@ def build(verbose=False):
         objs.append(obj)
     probe_cmd = ["hipcc", *[f for f in FLAGS if f != "-fPIC"], os.path.join(CSRC, "probe.hip"), "-o", PROBE]
     procs.append(("probe.hip", subprocess.Popen(probe_cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
-    host_compile, host_link = host_flags()
-    host_obj = os.path.join(CSRC, "host_calls.o")
-    procs.append(("host_calls.cpp", subprocess.Popen(["g++", *host_compile, "-c", os.path.join(CSRC, "host_calls.cpp"), "-o", host_obj],
-                                                     stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    host, host_obj = host_flags(), os.path.join(CSRC, "host_calls.o")
+    if host:
+        procs.append(("host_calls.cpp", subprocess.Popen(["g++", *host[0], "-c", os.path.join(CSRC, "host_calls.cpp"), "-o", host_obj],
+                                                         stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     failed = False
     for src, p in procs:
         out, _ = p.communicate()
@@ -69,7 +76,12 @@ def build(verbose=False):
     if failed:
         raise RuntimeError("libsp24 build failed")
     subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
-    subprocess.check_call(["g++", "-shared", "-o", HOST, host_obj, *host_link])
+    if host:
+        subprocess.check_call(["g++", "-shared", "-o", HOST, host_obj, *host[1]])
+    else:
+        print("torch or its headers are missing: _sp24_host.so is not built", file=sys.stderr)
+        if os.path.exists(HOST):
+            os.remove(HOST)                       # of another torch
     return LIB
 
 

@@ -2,7 +2,8 @@
 
 The calls go through ``_sp24_host.so`` (``csrc/host_calls.cpp``), which marshals a well-formed call natively; whatever
 it declines runs the Python code below it, which says what is wrong.  (A launch that the runtime rejects is raised from
-there: such a call must not be made again.)
+there: such a call must not be made again.)  Without that file, or where it was built against another torch, the Python
+code takes every call.
 
 Each function mirrors the C entry point of the same name (``include/sp24.h``):
 it checks that the tensors live on the GPU, allocates the outputs with torch,
@@ -14,6 +15,7 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import warnings
 
 import torch
 
@@ -83,18 +85,28 @@ def lib():
     return _lib
 
 
+class _PythonOnly:
+    """In the place of the native half: declines every call."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 def _load_host():
     """The native marshalling of the calls, beside libsp24.so."""
     global _host
     if _host is None:
         lib()
         path = os.path.join(os.path.dirname(LIB_PATH), "_sp24_host.so")
-        if not os.path.exists(path):
-            raise RuntimeError(f"{path} is missing: build it with `python -m paper_2104_08378_amd.build`")
-        loader = importlib.machinery.ExtensionFileLoader("_sp24_host", path)
-        host = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_sp24_host", path, loader=loader))
-        loader.exec_module(host)
-        host.Sp24Error = Sp24Error                # what it raises
+        try:
+            loader = importlib.machinery.ExtensionFileLoader("_sp24_host", path)
+            host = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_sp24_host", path, loader=loader))
+            loader.exec_module(host)
+            host.Sp24Error = Sp24Error            # what it raises
+        except ImportError as e:
+            warnings.warn(f"calls are marshalled in Python, 3 us slower each: {e} (build it with `python -m paper_2104_08378_amd.build`)",
+                          RuntimeWarning)
+            host = _PythonOnly()
         _host = host
     return _host
 

@@ -3,6 +3,7 @@ header declares, and rejects bad arguments before touching a device."""
 import ctypes
 import os
 import re
+import sys
 
 import pytest
 
@@ -297,3 +298,26 @@ def test_permute_search_validation():
     assert f(A, PERM, 64, 64, 64, sp24.F32, 1, None) == DTYPE
     assert f(A, PERM, 0, 64, 64, sp24.F16, 3, None) == OK               # empty: nothing to do
     assert f(A, PERM, 64, 64, 64, sp24.F16, 0, None) == OK              # no sweeps: nothing launched
+
+
+@pytest.mark.parametrize("contents", [None, b"", b"not a shared object"])
+def test_without_the_native_half_the_python_code_takes_the_calls(monkeypatch, tmp_path, contents):
+    """_sp24_host.so missing, or not loadable by this interpreter and torch: one warning, and the call goes on to the Python
+    code behind it (seen here by the error that only that code raises)."""
+    sp24.lib()
+    if contents is not None:
+        (tmp_path / "_sp24_host.so").write_bytes(contents)
+    monkeypatch.setattr(sp24, "LIB_PATH", str(tmp_path / "libsp24.so"))
+    monkeypatch.setattr(sp24, "_host", None)
+    A = sp24.torch.zeros((32, 64), dtype=sp24.torch.float16)
+    with pytest.warns(RuntimeWarning), pytest.raises(ValueError, match="A must be a GPU tensor"):
+        sp24.sp24_prune(A)
+    with pytest.raises(ValueError, match="must be a GPU tensor"):
+        sp24.sp24_gemm_dense(A, A, sp24.torch.float16)
+
+
+def test_the_library_builds_without_torch(monkeypatch):
+    from paper_2104_08378_amd import build
+    assert build.host_flags() is not None
+    monkeypatch.setitem(sys.modules, "torch", None)              # importing it raises ImportError
+    assert build.host_flags() is None
