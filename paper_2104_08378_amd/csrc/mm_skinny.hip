@@ -25,7 +25,10 @@ namespace sp24 {
 constexpr int kSkinnyWaves = 8;
 constexpr int kSkinnyUnroll = 4;   // tiles whose loads are in flight together, per wavefront
 
-template <int DT, int OUT, bool SPARSE>
+// PARTIAL: a canonical operand whose K is no multiple of 64 ends in a partial tile.  A form of its own: with its look at
+// every piece, and a branch around the loads, in the one kernel, the whole tiles of an 8-bit canonical operand took
+// 15 - 30 % longer (128256 x 8 x 1024: 28.9 -> 37.9 us).
+template <int DT, int OUT, bool SPARSE, bool PARTIAL>
 __global__ __launch_bounds__(64 * kSkinnyWaves) void k_mm_skinny(MmArgs a)
 {
     constexpr int ES = is8<DT> ? 1 : 2;
@@ -58,10 +61,12 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_mm_skinny(MmArgs a)
     const uint4v* Vp = reinterpret_cast<const uint4v*>(a.A);
     const uint32_t* Mp = reinterpret_cast<const uint32_t*>(a.meta);
     const int64_t tile_first = rb * (a.K / 64) + kb_first;   // tiled layout: this row block's first tile of the share
-    // canonical layout: each lane gathers its slot from row m; a K that is no multiple of 64 ends in a partial tile
+    // canonical layout: lane (m % 32, h) reads its slot's 16 bytes of values and 4 bytes of codes from row m
     const bool canonical = SPARSE && a.layout == SP24_LAYOUT_CANONICAL;
+    const uint8_t* vrow = reinterpret_cast<const uint8_t*>(a.A) + m * (a.K / 2 * ES) + (ES == 1 ? 16 : 32) * q + kb_first * 32 * ES;
+    const uint8_t* mrow = reinterpret_cast<const uint8_t*>(a.meta) + m * (a.K / 8) + 4 * q + kb_first * 8;
     compressed_rows<DT, 1> rows;
-    if constexpr (SPARSE) rows.init(a, rb, lane);
+    if constexpr (PARTIAL) rows.init(a, rb, lane);
 
     acc_t acc = {};
     const uint4v zero4 = {0u, 0u, 0u, 0u};
@@ -80,7 +85,7 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_mm_skinny(MmArgs a)
             }
             if constexpr (SPARSE) {
                 const int64_t tile = tile_first + kb;
-                if (canonical) {
+                if constexpr (PARTIAL) {
                     int4v v[1][rows.NA];
                     uint32_t code[1];
                     if ((kb_first + kb) * 64 + 64 <= a.K) rows.load_whole(kb_first + kb, v, code);
@@ -88,6 +93,13 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_mm_skinny(MmArgs a)
                     codes[u] = code[0];
 #pragma unroll
                     for (int s = 0; s < rows.NA; ++s) va[u][s] = ok ? __builtin_bit_cast(uint4v, v[0][s]) : zero4;
+                } else if (canonical) {
+                    codes[u] = ok ? *reinterpret_cast<const uint32_t*>(mrow + kb * 8) : 0u;
+                    if constexpr (is8<DT>) va[u][0] = ok ? *reinterpret_cast<const uint4v*>(vrow + kb * 32) : zero4;
+                    else {
+                        va[u][0] = ok ? *reinterpret_cast<const uint4v*>(vrow + kb * 64) : zero4;
+                        va[u][1] = ok ? *reinterpret_cast<const uint4v*>(vrow + kb * 64 + 16) : zero4;
+                    }
                 } else {
                     // the compressed operand passes once: loads marked as such leave B, which every workgroup re-reads,
                     // in the L2 (8192 x 8192 x 16 bf16 with the operand streamed from HBM: 21.1 -> 19.3 us)
@@ -167,8 +179,9 @@ template <int DT, int OUT>
 static sp24_status run_skinny(const MmArgs& a, hipStream_t st)
 {
     const dim3 grid((unsigned)((a.M + 31) / 32), (unsigned)(a.k_slices > 1 ? a.k_slices : 1)), block(64 * kSkinnyWaves);
-    if (a.sparse) k_mm_skinny<DT, OUT, true><<<grid, block, 0, st>>>(a);
-    else k_mm_skinny<DT, OUT, false><<<grid, block, 0, st>>>(a);
+    if (!a.sparse) k_mm_skinny<DT, OUT, false, false><<<grid, block, 0, st>>>(a);
+    else if (a.K % 64 == 0) k_mm_skinny<DT, OUT, true, false><<<grid, block, 0, st>>>(a);
+    else k_mm_skinny<DT, OUT, true, true><<<grid, block, 0, st>>>(a);
     return hipGetLastError() == hipSuccess ? SP24_OK : SP24_ERR_LAUNCH;
 }
 

@@ -27,3 +27,21 @@ def test_products_match_oracle(case):
     run_mm_case(*case, layout="canonical", b_order="k", sparse=True, seed=61)
     if case[2] % 32 == 0 and case[4] % 64 == 0:
         run_mm_case(*case, layout="tiled", b_order="k", sparse=True, seed=62)
+
+
+# 8-bit operands with more row blocks than compute units and N <= 32: the streaming kernel, whole tiles and K ending in the
+# middle of one (an instantiation of its own), fewer tiles than wavefronts, one row past a block
+MANY_ROWS = [
+    ("i8", "i32", 8224, 1, 64),
+    ("i8", "i32", 8225, 7, 1024),
+    ("i8", "i32", 8224, 16, 96),
+    ("i8", "i32", 8255, 3, 1184),
+    ("i8", "i32", 8193, 31, 2080),
+]
+
+
+@pytest.mark.parametrize("case", MANY_ROWS)
+def test_more_row_blocks_than_compute_units(case):
+    run_mm_case(*case, layout="canonical", b_order="k", sparse=True, seed=63)
+    if case[2] % 32 == 0 and case[4] % 64 == 0:
+        run_mm_case(*case, layout="tiled", b_order="k", sparse=True, seed=64)
