@@ -498,16 +498,26 @@ static sp24_status mm_splitk(const MmArgs& a, void* workspace, size_t workspace_
         // 128-byte step whatever their number; of the plan's slices as many as find a unit of their own and as the
         // images are worth (written and read at 4 TB/s).  Against the plan's slices on the tiled or the streaming kernel:
         // 1000 x 64 x 2048 f16 13.4 -> 8.4 us, 512 x 16 x 16384 bf16 10.1 -> 9.1, 1024 x 128 x 4096 12.5 -> 9.3.
-        const int64_t steps_ns = a.K * es / 128 * (a.N <= 32 ? 40 : 100), image_ns = a.M * plan.ldw / 500;
+        const int64_t steps = a.K * es / 128, steps_ns = steps * (a.N <= 32 ? 40 : 100), image_ns = a.M * plan.ldw / 500;
         const int most = (int)std::min<int64_t>(plan.slices, 256 / stream_workgroups(a));
-        if (most <= 1) return mm_dispatch(a, st);
-        part.k_slices = 2;
-        for (int n = 3; n <= most; ++n)
-            if (steps_ns / n + n * image_ns < steps_ns / part.k_slices + part.k_slices * image_ns) part.k_slices = n;
-        s = launch_mm_stream(part, st, &handled);
-        if (handled && s != SP24_OK) return s;
-        if (handled) return launch_splitk_reduce(workspace, part.k_slices, a.M, a.N, plan.ldw, a.D, a.ldd, a.in == SP24_I8, a.out, st);
-        part.k_slices = plan.slices;
+        int n = most <= 1 ? 1 : 2;
+        for (int x = 3; x <= most; ++x)
+            if (steps_ns / x + x * image_ns < steps_ns / n + n * image_ns) n = x;
+        // With more than 32 columns the plan's eight slices, which tiles of 128 x 128 leave room for, win where a slice is
+        // long.  Measured over 16 - 512 steps a slice: one slice (an unsplit product) is level or up to 40 % ahead until 128
+        // steps, and from 160 on level at best (8192 x 64 x 16384 bf16 48.9 against 36.2 us, 2560 x 128 x 32768 76.0 against
+        // 39.7); two slices are 16 % ahead to 5 % behind until 96 and from 112 on 8 % ahead to 10 % behind (512 x 333 x 16384 19.8
+        // against 17.8); three and more are level or ahead until 128.  The tiled kernels are slower on a canonical operand: two
+        // slices of it stay 14 % and more ahead as far as measured (1000 x 200 x 20480 bf16 29.8 against 37.6).
+        const int64_t longest = a.N <= 32 ? steps : n == 1 ? 128 : a.layout == SP24_LAYOUT_CANONICAL ? 256 : n == 2 ? 104 : 128;
+        if (steps <= longest * n) {
+            if (n == 1) return mm_dispatch(a, st);
+            part.k_slices = n;
+            s = launch_mm_stream(part, st, &handled);
+            if (handled && s != SP24_OK) return s;
+            if (handled) return launch_splitk_reduce(workspace, part.k_slices, a.M, a.N, plan.ldw, a.D, a.ldd, a.in == SP24_I8, a.out, st);
+            part.k_slices = plan.slices;
+        }
     }
     s = plan.streaming ? launch_mm_skinny(part, st, &handled) : launch_mm_tiled(part, st, &handled);
     if (!handled) return mm_dispatch(a, st);             // operands that kernel does not take: not split

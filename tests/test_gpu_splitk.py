@@ -135,3 +135,40 @@ def test_split_products_at_the_sizes_bench_times(dtype, out, M, N, K):
             assert np.array_equal(got.cpu().numpy(), ref)
         else:
             assert rel_err(out_to_f64(got), ref) <= REL_TOL
+
+
+# sparse products whose slices would be long on the kernel that splits K across wavefronts: more than 128 workgroups (one
+# slice, 129 steps and a partial one), two slices of 112 steps, three of 129 -- cut as the workspace was planned instead
+LONG_SLICES = [
+    ("bf16", "f32", 544, 512, 8288, "canonical"),
+    ("i8", "i32", 544, 500, 16512, "tiled"),
+    ("f16", "f16", 512, 333, 14336, "tiled"),
+    ("bf16", "bf16", 352, 384, 24768, "tiled"),
+]
+
+
+@pytest.mark.parametrize("case", LONG_SLICES)
+def test_long_slices_take_the_planned_cut(case):
+    dtype, out, M, N, K, layout = case
+    need = sp24.sp24_splitk_workspace_bytes(M, N, K, IN_DT[dtype])
+    image = M * ((N + 3) // 4 * 4) * 4
+    assert need % image == 0 and need // image >= 4
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")          # NaN bit patterns / -1
+    A, Bt = synth.make(NAME_OF[dtype], M=M, N=N, K=K, seed=24)
+    V, meta = sp24.sp24_compress(to_gpu(A, dtype), layout=layout)
+    D = sp24.sp24_spmm_splitk(V, meta, to_gpu(Bt, dtype), OUT_DT[out], layout=layout, workspace=ws)
+    torch.cuda.synchronize()
+    assert not bool((ws[need - image:] == 0xFF).all())                        # the last of the planned images was written
+    rng = np.random.default_rng(25)
+    rows = np.unique(np.concatenate([[0, 31, 32, 127, 128, M - 1], rng.integers(0, M, 24)]))
+    cols = np.unique(np.concatenate([[0, 1, 63, 64, N - 1], rng.integers(0, N, 24)]))
+    Prows, Bcols = oracle.prune(np.ascontiguousarray(A[rows]), dtype), np.ascontiguousarray(Bt[cols].T)
+    ref = oracle.gemm(Prows, Bcols, dtype)
+    got = D[torch.as_tensor(rows, device="cuda")][:, torch.as_tensor(cols, device="cuda")]
+    if dtype == "i8":
+        assert np.array_equal(got.cpu().numpy(), ref)
+    else:
+        assert rel_err(out_to_f64(got), ref) <= REL_TOL
+        if out == "f32":
+            scale = np.abs(oracle.to_double(Prows, dtype)) @ np.abs(oracle.to_double(Bcols, dtype))
+            assert (np.abs(out_to_f64(got) - ref) <= K * 2.0 ** -24 * scale + 1e-30).all()
