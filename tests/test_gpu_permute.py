@@ -151,6 +151,17 @@ def test_permute_search_order_equals_the_oracle(dtype):
             assert after >= before * (1 - 1e-12)
 
 
+# K/4 = 4, 20, 28, 36, 44, 72, 132, 260, 304 groups: rounds of fewer than eight pairs, and of every remainder of a division by
+# the eight XCDs, where the last round pairs few of the groups or most
+@pytest.mark.parametrize("K", [16, 80, 112, 144, 176, 288, 528, 1040, 1216])
+def test_permute_search_on_group_counts_that_are_no_power_of_two(K):
+    dtype, M = "bf16", 70
+    A = synth.make(NAME_OF[dtype], M=M, N=16, K=K, seed=190 + K)[0]
+    got = sp24.sp24_permute_search(to_gpu(A, dtype), sweeps=2)
+    torch.cuda.synchronize()
+    assert np.array_equal(got.cpu().numpy(), oracle.permute_search(A, dtype, sweeps=2))
+
+
 def test_permute_search_starts_from_a_given_order_and_takes_pitched_rows():
     dtype, M, K = "bf16", 500, 96
     A = synth.make(NAME_OF[dtype], M=M, N=16, K=K, seed=181)[0]
