@@ -102,7 +102,13 @@ __device__ __forceinline__ void halve(double (&v)[L], double (&kept)[(L + 1) / 2
 
 } // namespace
 
-template <int DT>
+// TOGETHER: a barrier every 256 rows, for matrices whose rows fill an L2 with the lines of few such blocks.  Once the order
+// is no longer that of memory every workgroup reads lines all over the matrix, which it shares with the others only
+// while they are at the same rows; with the arithmetic as short as it is the wavefronts drift apart, and each line is
+// then fetched again (an arbitrary start order, us a sweep: 8192 x 4096 bf16 3006 -> 2273, 8192 x 8192 8-bit floats 8892 ->
+// 5284, bf16, whose 256 rows are the whole L2, 10907 -> 11100; four sweeps from the order of memory 6899 -> 6408, 15251 ->
+// 12894 and 18940 -> 17480; the first of them 1037 -> 1069, 2073 -> 2211 and 2541 -> 2455).
+template <int DT, bool TOGETHER>
 __global__ __launch_bounds__(256) void k_permute_search_round(const uint8_t* __restrict__ A, int32_t* perm, int64_t M, int64_t K,
                                                               int64_t lda_bytes, int bit)
 {
@@ -144,7 +150,13 @@ __global__ __launch_bounds__(256) void k_permute_search_round(const uint8_t* __r
         sum_t x[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) x[i] = search_magnitude<DT>(bits[i]);
+        if (TOGETHER && m - threadIdx.x + 256 <= M) __syncthreads();      // (every lane has such a row)
         if (m + 256 < M) load_row(m + 256);
+        // the arithmetic is 343 instructions of eight bytes: a row took 5 - 13 % longer where they lay across eight-byte
+        // boundaries (32768 x 64 8-bit floats 563 against 637 us a sweep)
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile(".p2align 3");
+        __builtin_amdgcn_sched_barrier(0);
         sum_t pair[8][8];
 #pragma unroll
         for (int i = 0; i < 8; ++i)
@@ -226,6 +238,10 @@ sp24_status launch_permute_search(const void* A, int32_t* perm, int64_t M, int64
     const int es = esize_of(t);
     const dim3 block(256);
     const uint8_t* a = static_cast<const uint8_t*>(A);
+    // 256 rows of 8 KiB are half an L2; with fewer rows, or shorter ones, the barrier costs a sweep from the order of memory
+    // more than it gives the others (4096 x 11008 bf16 1788 -> 1961 us, 8192 x 4096 8-bit floats 886 -> 1044).  Not for int8,
+    // whose sums are 32-bit (8192 x 8192 from an arbitrary order 6430 -> 7255).
+    const bool together = M >= 8192 && K * es >= 8192;
     for (int sweep = 0; sweep < sweeps; ++sweep)
         for (int r = 0; r < rounds; ++r) {
             // the pairs of the round, one for each group below G with bit r set.  No more workgroups than that: each XCD has an
@@ -233,10 +249,11 @@ sp24_status launch_permute_search(const void* A, int32_t* perm, int64_t M, int64
             // (4096 x 11008 int8 2066 -> 1402 us a sweep, bf16 2836 -> 1788)
             const int64_t pairs = ((G >> (r + 1)) << r) + std::max<int64_t>(0, (G & (((int64_t)2 << r) - 1)) - ((int64_t)1 << r));
             const dim3 grid((unsigned)pairs);
-            if (t == SP24_F16) k_permute_search_round<SP24_F16><<<grid, block, 0, st>>>(a, perm, M, K, lda * es, r);
-            else if (t == SP24_BF16) k_permute_search_round<SP24_BF16><<<grid, block, 0, st>>>(a, perm, M, K, lda * es, r);
-            else if (t == SP24_F8) k_permute_search_round<SP24_F8><<<grid, block, 0, st>>>(a, perm, M, K, lda * es, r);
-            else k_permute_search_round<SP24_I8><<<grid, block, 0, st>>>(a, perm, M, K, lda * es, r);
+            auto run = [&](auto kernel) { kernel<<<grid, block, 0, st>>>(a, perm, M, K, lda * es, r); };
+            if (t == SP24_F16) together ? run(k_permute_search_round<SP24_F16, true>) : run(k_permute_search_round<SP24_F16, false>);
+            else if (t == SP24_BF16) together ? run(k_permute_search_round<SP24_BF16, true>) : run(k_permute_search_round<SP24_BF16, false>);
+            else if (t == SP24_F8) together ? run(k_permute_search_round<SP24_F8, true>) : run(k_permute_search_round<SP24_F8, false>);
+            else run(k_permute_search_round<SP24_I8, false>);
             if (hipGetLastError() != hipSuccess) return SP24_ERR_LAUNCH;
         }
     return SP24_OK;

@@ -162,6 +162,24 @@ def test_permute_search_on_group_counts_that_are_no_power_of_two(K):
     assert np.array_equal(got.cpu().numpy(), oracle.permute_search(A, dtype, sweeps=2))
 
 
+@pytest.mark.parametrize("dtype,K", [("bf16", 4096), ("f16", 4112), ("i8", 8192), ("f8", 8192)])
+def test_permute_search_of_a_large_matrix_from_any_order(dtype, K):
+    """Rows enough for the form of the kernel whose wavefronts go through them together, the last pass over the rows a
+    partial one.  Rows of zeros add nothing to any sum: the oracle gets the others, each at its place modulo the 256 lanes."""
+    M = 8200
+    if dtype == "f8":
+        A = synth.f64_to_f8_bits(np.random.default_rng(201).standard_normal((520, K)))
+    else:
+        A = synth.make(NAME_OF[dtype], M=520, N=16, K=K, seed=201)[0]
+    Ad = to_gpu(A, dtype)
+    big = torch.zeros((M, K), dtype=Ad.dtype, device="cuda")
+    big.view(torch.uint8)[:512], big.view(torch.uint8)[8192:] = Ad.view(torch.uint8)[:512], Ad.view(torch.uint8)[512:]
+    start = np.random.default_rng(202).permutation(K).astype(np.int32)
+    got = sp24.sp24_permute_search(big, perm=dev_perm(start))
+    torch.cuda.synchronize()
+    assert np.array_equal(got.cpu().numpy(), oracle.permute_search(A, dtype, sweeps=1, perm=start))
+
+
 def test_permute_search_starts_from_a_given_order_and_takes_pitched_rows():
     dtype, M, K = "bf16", 500, 96
     A = synth.make(NAME_OF[dtype], M=M, N=16, K=K, seed=181)[0]
