@@ -328,6 +328,12 @@ static bool tiled_before_streaming(const MmArgs& a)
 static bool stream_first(const MmArgs& a)
 {
     if (!a.sparse || a.conv.on || a.bo != SP24_B_KMAJOR || a.N > 512) return false;
+    // Few steps of an 8-bit operand: a wavefront has one at most, and the partial step at the end of K comes behind it.  With
+    // N <= 32 the streaming kernel is 5 - 17 % ahead below four whole steps, and below eight where the last is a partial one
+    // (33 - 8192 rows, replayed: K = 64 2.6 - 3.0 us against 3.0 - 3.5, 192 2.7 - 3.1 against 3.0 - 3.4, 576 2.9 - 3.6 against
+    // 3.3 - 3.7; at 512 level in the tiled layout, 10 % behind in the canonical one).  16-bit types are level or behind there,
+    // and wider products within 5 %.
+    if (a.N <= 32 && esize_of(a.in) == 1 && a.K < (a.K % 128 == 0 ? 512 : 1024)) return false;
     return stream_workgroups(a) <= 256 || (a.N <= 32 && esize_of(a.in) == 2 && a.M < 11008);
 }
 
