@@ -510,12 +510,14 @@ static sp24_status mm_splitk(const MmArgs& a, void* workspace, size_t workspace_
         for (int x = 3; x <= most; ++x)
             if (steps_ns / x + x * image_ns < steps_ns / n + n * image_ns) n = x;
         // With more than 32 columns the plan's eight slices, which tiles of 128 x 128 leave room for, win where a slice is
-        // long.  Measured over 16 - 512 steps a slice: one slice (an unsplit product) is level or up to 40 % ahead until 128
-        // steps, and from 160 on level at best (8192 x 64 x 16384 bf16 48.9 against 36.2 us, 2560 x 128 x 32768 76.0 against
-        // 39.7); two slices are 16 % ahead to 5 % behind until 96 and from 112 on 8 % ahead to 10 % behind (512 x 333 x 16384 19.8
-        // against 17.8); three and more are level or ahead until 128.  The tiled kernels are slower on a canonical operand: two
-        // slices of it stay 14 % and more ahead as far as measured (1000 x 200 x 20480 bf16 29.8 against 37.6).
-        const int64_t longest = a.N <= 32 ? steps : n == 1 ? 128 : a.layout == SP24_LAYOUT_CANONICAL ? 256 : n == 2 ? 104 : 128;
+        // long.  Measured over 16 - 512 steps a slice, operands from HBM: one slice (an unsplit product) is 3 - 40 % ahead until
+        // 80 steps, 9 % behind to 3 % ahead at 96 and 5 - 20 % behind at 128 (8192 x 64 x 8192 bf16 26.8 against 23.5 us); two
+        // slices are level until 64 or up to 15 % ahead, at 96 13 % behind to 5 % ahead (4096 x 64 x 12288 24.9 against 21.6);
+        // three and more stay ahead until 128 (7 % behind to 27 %).  Operands in the last-level cache favour the kernel by some
+        // 10 % more.  The tiled kernels are slower on a canonical operand: one slice of it is level at 128 steps, and two stay
+        // 9 % and more ahead as far as measured (1000 x 200 x 20480 bf16 29.8 against 37.6).
+        const bool canonical = a.layout == SP24_LAYOUT_CANONICAL;
+        const int64_t longest = a.N <= 32 ? steps : n == 1 ? (canonical ? 128 : 104) : canonical ? 256 : n == 2 ? 88 : 128;
         if (steps <= longest * n) {
             if (n == 1) return mm_dispatch(a, st);
             part.k_slices = n;
