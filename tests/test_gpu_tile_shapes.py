@@ -12,9 +12,12 @@ from test_gpu_splitk import test_split_products_match_oracle_and_the_unsplit_pro
 pytestmark = pytest.mark.gpu
 
 # K ends in the middle of a step: a partial step alone, behind one and behind a ring that wraps; ragged M and N.  Tiles of
-# 64 x 64 (65 of 128 x 128, N <= 64) and 64 x 128 (few of them), 128 x 128 with six (144 of them) and three stages (306),
+# 64 x 64 (few of them with not one whole step; 65 of 128 x 128, N <= 64) and 64 x 128 (few of them), 128 x 128 with six (144 of them) and three stages (306),
 # 256 x 256 (144)
 PARTIAL = [
+    ("i8", "i32", 224, 60, 96),
+    ("i8", "i32", 64, 64, 64),
+    ("bf16", "f32", 100, 33, 32),
     ("i8", "i32", 8231, 50, 160),
     ("bf16", "bf16", 8256, 61, 352),
     ("i8", "i32", 224, 700, 960),
@@ -59,7 +62,7 @@ def test_n_major_at_any_address_on_two_row_blocks(case):
 # 64 columns a tile, seven wavefronts of two stages: less than a step, a step for each wavefront, one more, rings that wrap,
 # a partial step for the first and for another wavefront; columns around a tile; one row
 WIDE_STREAM = [
-    ("i8", "i32", 32, 33, 64),
+    ("i8", "i32", 32, 66, 64),
     ("i8", "i32", 65, 64, 896),
     ("i8", "i32", 96, 65, 1056),
     ("i8", "i32", 160, 511, 2144),
