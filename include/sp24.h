@@ -34,8 +34,16 @@
  *     element type and any leading dimension that covers a row.  Otherwise
  *     SP24_ERR_ALIGN.  (The fastest product kernels are chosen when B rows are
  *     16-byte aligned too -- for N-major B also N * element size a multiple of
- *     16.  An N-major B at any other alignment has a kernel of its own, a
- *     K-major one runs a general kernel.)
+ *     16.  At any other alignment an N-major B, and a K-major one of a sparse
+ *     product, have kernels of their own; dense products with a K-major one run a
+ *     general kernel.)
+ *   - Which kernel runs depends on sizes, types, layout and alignment, and with it
+ *     the order in which binary32 sums are formed.  A product gives the same bits
+ *     each time.  Integer results are exact whichever way they are asked for;
+ *     float results of two ways to the same product (another layout or order of
+ *     B, a convolution and the product written out, a split and an unsplit
+ *     product, other numbers of rows or columns) agree up to the order of the
+ *     additions, unless a function's comment says more.
  *   - K must be a multiple of 16 for 16-bit types and of 32 for the 8-bit types
  *     (the dimension rule of Sec. 3.2 / Sec. 4.2, applied to the inner
  *     dimension), else SP24_ERR_SHAPE.  M and N may be any positive value; a
@@ -87,7 +95,7 @@ typedef enum {
  * SP24_LAYOUT_CANONICAL  V row-major [M][K/2]; meta bytes [M][K/8], the even
  *     group of a byte in bits 0..3.  Interchange format.
  *
- *     Every product accepts it; the tiled layout below is 1.2-1.5x faster.
+ *     Every product accepts it; the tiled layout below is up to 1.5x faster.
  *
  * SP24_LAYOUT_TILED  the same codes and values permuted so that one wavefront
  *     loads the operands of a 32x32 sparse-MFMA tile with contiguous 16-byte

@@ -321,10 +321,13 @@ static bool tiled_before_streaming(const MmArgs& a)
 // splits K across a workgroup's wavefronts.  One workgroup's rings fill a unit's LDS, so a second round costs the whole
 // time again: measured against the tiled and the streaming kernel, up to 256 workgroups 1.05 - 2.4 times as fast
 // (1024 x 128 x 4096 bf16 16.7 -> 9.9 us, 8192 x 32 x 8192 25.1 -> 14.0, 8192 x 16 x 8192 18.1 -> 13.3; 4096 x 1 x 1024
-// level), past that 0.4 - 1.0 times -- except for 16-bit inputs with N <= 32 up to the 11008 rows from which the tiled
-// kernels take them (9216 x 16 x 4096 17.0 -> 12.3 us in two rounds).
-// More than 512 columns stay with the tiled kernels whatever their number: such products with few rows are convolutions
-// written out, whose results are those of the implicit convolution bit for bit as long as K is summed in one piece.
+// level; with the compressed operand from HBM 8192 x 16 x 8192 19.3 -> 16.4, 8192 x 64 x 8192 32.3 -> 27.8), past that 0.4 -
+// 1.0 times -- except for 16-bit inputs with N <= 32 up to the 11008 rows from which the tiled kernels take them
+// (9216 x 16 x 4096 17.0 -> 12.3 us in two rounds).
+// The limit of 512 columns is not one of speed: 32 - 512 rows on 513 - 2048 columns would run 1.3 - 2.0 times as fast here
+// (128 x 1000 x 4096 bf16 16.9 -> 9.8 us).  It keeps wide products of 16-bit types with few rows, convolutions written out
+// among them, on the kernel that adds K in the order of the implicit convolution with one chunk of channels, so that the two
+// agree bit for bit; narrower ones have not agreed since this kernel takes them, and the interface promises neither.
 static bool stream_first(const MmArgs& a)
 {
     if (!a.sparse || a.conv.on || a.bo != SP24_B_KMAJOR || a.N > 512) return false;
@@ -351,7 +354,8 @@ static bool staged_before_ksplit(const MmArgs& a)
     return ((a.M + 127) / 128) * ((a.N + 127) / 128) > 64;
 }
 
-// The kernel for a checked product: streaming (N <= 32), tiled, or general.
+// The kernel for a checked product: few columns or few tiles (K split across wavefronts), streaming (N <= 32), tiled, and for
+// operands those cannot fetch the staged and the K-splitting ones; the general kernel takes what is left.
 static sp24_status mm_dispatch(const MmArgs& a, hipStream_t st)
 {
     bool handled = false;

@@ -9,6 +9,8 @@
 // wavefront has; the time is the latency of one patch in and one tile out, so what counts is how many workgroups
 // share a compute unit: four with the 192-pixel patch, three with the 256-pixel one.  A of a whole chunk (nine steps, 45
 // registers) is loaded ahead of the barrier, under the patch's own latency.
+// (Four workgroups mean 128 registers: the 192-pixel instances that need more keep 20 bytes a lane, int8 to int8, or 24 - 84,
+// 8-bit floats, in scratch memory.)
 // Patch rows are 80 bytes apart: sixteen consecutive rows fall into sixteen different 16-byte columns of LDS.
 //
 // Measured with the quantised epilogue to int8, against the general kernel that took these layers before (us, operands

@@ -53,7 +53,8 @@ struct MmArgs {
     int k_slices, slice_steps;
 };
 
-// General kernel: any M, N; both layouts; both B orders.  One wavefront per 32x32 tile of D.
+// General kernel: any M, N; both layouts; both B orders.  One wavefront per 32x32 tile of D.  Of the sparse products only
+// those past the other kernels' index ranges come here.
 sp24_status launch_mm_simple(const MmArgs& a, hipStream_t st);
 
 // N-major B at any alignment, K split across the wavefronts of a workgroup; false in *handled for other problems.

@@ -1,7 +1,11 @@
 // General matrix-multiply kernel: one wavefront per 32x32 tile of D, operands
 // gathered element by element with bounds checks.  It accepts every legal
-// shape, both compressed layouts and both orders of B; the tiled kernels take
-// over for the large aligned shapes.  Sparse (Sec. 3.2, Fig. 2: the metadata
+// shape, both compressed layouts and both orders of B.  What comes here: dense
+// products with K-major rows that are not 16-byte aligned, dense convolutions
+// whose pixels are no whole 128-byte steps, and anything past the index ranges
+// of the other kernels (2^30 rows, columns or columns of A, 2^30 tiles).  Sparse
+// operands come for the last reason alone; their half stays compiled so that
+// every size the interface takes has a kernel.  Sparse (Sec. 3.2, Fig. 2: the metadata
 // selects the rows of B that meet kept values of A) and dense variants share
 // the operand gather and the store.
 #include "common.hpp"

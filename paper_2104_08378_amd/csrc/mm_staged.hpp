@@ -18,7 +18,7 @@
 // Bound by the latency and the issue of those loads: a tile moves the same bytes per product as a 128 x 128 tile of the
 // tiled kernels.  Measured against the general and the K-splitting kernels that took these before (us): sparse 3x3
 // convolution, 43 images of 28x28, 96 -> 192 channels, bf16 417 -> 32; 93 images of 15x15, 96 -> 96, 121 -> 15;
-// 18624 x 552 x 5392 bf16 canonical 4667 -> 245; 2304 x 1411 x 400 f16 canonical 135 -> 11; N-major 6784 x 939 x 6464 bf16
+// 18624 x 552 x 5392 bf16 canonical 4667 -> 245 (217 with an earlier form of the loop, slower for N-major B); 2304 x 1411 x 400 f16 canonical 135 -> 11; N-major 6784 x 939 x 6464 bf16
 // 193 -> 90, 4096 x 4095 x 4096 bf16 125, int8 83.
 #pragma once
 #include "mm_operands.hpp"

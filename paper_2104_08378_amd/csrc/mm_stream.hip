@@ -9,8 +9,9 @@
 // Why through LDS: the matrix instruction wants 16 bytes of each of 32 rows of B per half wavefront, and a load of that
 // shape touches 32 cache lines for 1 KiB -- the address path, not the memory, then sets the pace.  A transfer has
 // eight lanes to a row (a whole line), and for a canonical A four lanes to a row's 64 bytes of a step.
-// A unit brings in about 105 GB/s this way (64-column tiles; 8192 x 64 x 8192 bf16 18.2 us = 4.6 TB/s of operands from
-// HBM, and as many again from the L2).  Measured and not kept: the compressed operand marked as passing once (nt), which
+// 8192 x 64 x 8192 bf16: 76.5 MB of operands in 27.8 us from HBM (2.8 TB/s), in 18.4 us where they are still in the last-level
+// cache (4.2 TB/s); every workgroup reads all of B besides, 268 MB from the L2, so that a unit brings in 48 and 73 GB/s.
+// 8192 x 16 x 8192: 76 MB in 16.4 us from HBM (4.6 TB/s).  Measured and not kept: the compressed operand marked as passing once (nt), which
 // helps loads into registers, costs these transfers 10 - 60 % (512 x 16 x 16384: 13.2 -> 21.2 us).
 #include "mm_operands.hpp"
 

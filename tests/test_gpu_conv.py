@@ -30,10 +30,10 @@ def make_inputs(dtype, M, n_img, H, W, C, K, seed):
 
 CASES = [
     # dtype, out, M, n_img, H, W, C, R, S, pad, stride, layout        -- kernel that serves it
-    ("f16", "f32", 40, 2, 6, 5, 16, 3, 3, (1, 1), (1, 1), "canonical"),     # general
-    ("bf16", "bf16", 64, 1, 7, 9, 32, 3, 2, (0, 1), (2, 1), "tiled"),      # general (N = 27 < 32)
-    ("i8", "i32", 33, 3, 5, 5, 32, 3, 3, (1, 1), (1, 1), "canonical"),      # general, ragged M
-    ("i8", "i32", 64, 2, 6, 6, 64, 3, 3, (2, 2), (1, 1), "tiled"),          # general (C*1 = 64 bytes < a step), pad > needed
+    ("f16", "f32", 40, 2, 6, 5, 16, 3, 3, (1, 1), (1, 1), "canonical"),     # B staged through registers (dense: general)
+    ("bf16", "bf16", 64, 1, 7, 9, 32, 3, 2, (0, 1), (2, 1), "tiled"),      # staged; N = 27 (dense: general)
+    ("i8", "i32", 33, 3, 5, 5, 32, 3, 3, (1, 1), (1, 1), "canonical"),      # staged, ragged M (dense: general)
+    ("i8", "i32", 64, 2, 6, 6, 64, 3, 3, (2, 2), (1, 1), "tiled"),          # 64-channel chunks (pad > needed: staged); dense: general
     ("f16", "f16", 128, 3, 12, 12, 64, 3, 3, (1, 1), (1, 1), "tiled"),      # 3x3 patch kernel (sparse), one chunk of channels, ragged N = 432
     ("f16", "f16", 96, 5, 9, 11, 192, 3, 3, (1, 1), (1, 1), "tiled"),       # patch kernel: three chunks, ragged M (three row blocks), N = 495
     ("bf16", "f32", 160, 40, 4, 4, 256, 3, 3, (1, 1), (1, 1), "tiled"),     # patch kernel: four chunks, a tile spans eight images, ragged M
@@ -50,7 +50,7 @@ CASES = [
     ("bf16", "f32", 192, 2, 11, 13, 128, 2, 3, (1, 0), (2, 1), "tiled"),    # tiled, two steps per tap, strides, ragged N = 132
     ("i8", "i32", 256, 4, 10, 10, 128, 3, 3, (1, 1), (1, 1), "tiled"),      # patch kernel int8, one chunk (dense: tiled, 9 steps)
     ("f16", "f32", 128, 2, 8, 8, 256, 1, 1, (0, 0), (1, 1), "tiled"),       # pointwise: the plain product's kernels (N = 128: tiled)
-    ("i8", "i32", 64, 1, 4, 4, 256, 1, 1, (0, 0), (1, 1), "tiled"),         # pointwise on 16 pixels: the streaming kernel
+    ("i8", "i32", 64, 1, 4, 4, 256, 1, 1, (0, 0), (1, 1), "tiled"),         # pointwise on 16 pixels: the streaming kernel (few steps)
     ("bf16", "bf16", 256, 8, 16, 16, 512, 1, 1, (0, 0), (1, 1), "canonical"),  # pointwise, 2048 pixels, canonical layout
     ("f16", "f16", 128, 2, 9, 9, 128, 1, 1, (0, 0), (2, 2), "tiled"),       # 1x1 with stride 2: still a gather
     ("bf16", "bf16", 64, 5, 9, 7, 64, 5, 3, (2, 1), (3, 2), "tiled"),       # 5x3 filter, stride 3x2

@@ -67,8 +67,8 @@ def test_f8_prune_compress_decompress_bit_exact(kind):
             assert np.array_equal(to_bits(sp24.sp24_compress_masked(Wd, mt, layout="tiled")), wantVm)
 
 
-# M, N, K, layout, b_order: the general kernel (ragged), the streaming kernel, 128x128 tiles, 256x256 tiles (more than
-# 200 of them), a ragged K tail on the tiled kernel, an N-major second operand
+# M, N, K, layout, b_order: few columns (ragged, tiled), few tiles (sparse; dense 128x128), 256x256 tiles (more than
+# 200 of them), a ragged K tail on few tiles, an N-major second operand (test_gpu_tile_shapes.py has the other tiles)
 PRODUCTS = [
     (33, 17, 96, "canonical", "k"),
     (64, 16, 512, "tiled", "k"),

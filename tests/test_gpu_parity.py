@@ -171,8 +171,8 @@ MM_CASES = [
 
 
 def unaligned_rows(B):
-    """The same matrix as a view whose rows start K + 4 elements apart: no 16-byte alignment, so the products run
-    the general kernel."""
+    """The same matrix as a view whose rows start K + 4 elements apart: no 16-byte alignment, so the dense products run
+    the general kernel and the sparse ones that which stages B through registers."""
     wide = torch.zeros((B.shape[0], B.shape[1] + 4), dtype=B.dtype, device=B.device)
     wide[:, :B.shape[1]] = B
     return wide[:, :B.shape[1]]
@@ -294,7 +294,7 @@ NMAJOR_CASES = [
     ("bf16", "bf16", 3328, 4096, 448),
     ("f16", "f16", 4096, 3320, 128),      # ragged N on the eight-wavefront shape
     ("i8", "i32", 4352, 4000, 384),
-    ("i8", "i32", 320, 300, 256),         # N not a whole number of chunks: the general kernel
+    ("i8", "i32", 320, 300, 256),         # N not a whole number of chunks: K split across a workgroup's wavefronts
 ]
 
 
@@ -345,14 +345,15 @@ def test_spmm_canonical_layout_on_the_tiled_kernels(case):
 
 
 RAGGED_K_CASES = [
-    # K not a whole number of 128-byte steps: the last step is filled up with zeros
+    # K not a whole number of 128-byte steps: the last step is filled up with zeros (K-major sparse products this small split K
+    # across wavefronts; test_gpu_tile_shapes.py has the tiled kernels')
     ("i8", "i32", 256, 320, 192, "tiled"),        # half a step (one 64-column tile)
     ("i8", "i32", 4096, 3328, 320, "tiled"),      # the same on 256x256 tiles
     ("i8", "i32", 160, 200, 160, "canonical"),    # a quarter step, ragged M and N
     ("i8", "i32", 128, 128, 96, "canonical"),     # a single, partial step
     ("bf16", "bf16", 256, 264, 96, "canonical"),  # 16-bit: K % 64 = 32
     ("f16", "f32", 192, 128, 224, "canonical"),
-    ("f16", "f16", 128, 256, 208, "canonical"),   # K % 32 = 16: sparse runs the general kernel, dense the tiled one
+    ("f16", "f16", 128, 256, 208, "canonical"),   # K % 32 = 16: sparse stages B through registers, dense runs the tiled kernel
 ]
 
 
@@ -407,7 +408,7 @@ def test_empty_problem_is_a_no_op():
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("out", ["f32", "f16", "bf16"])
-@pytest.mark.parametrize("shape", [(64, 64, 64, True), (64, 64, 64, False), (256, 320, 128, False)])   # the general kernel (B rows unaligned), the tiled kernel
+@pytest.mark.parametrize("shape", [(64, 64, 64, True), (64, 64, 64, False), (256, 320, 128, False)])   # B rows unaligned (general, staged), few tiles
 def test_special_values_reach_the_output_as_ieee_conversion_gives_them(dtype, out, shape):
     """Small integers (sums exact in any order), a NaN weight, infinities and sums beyond the 16-bit ranges: the stored
     result is the exact sum converted once, round to nearest even -- NaN stays NaN, overflow becomes infinity."""
@@ -442,7 +443,7 @@ def test_special_values_reach_the_output_as_ieee_conversion_gives_them(dtype, ou
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
-@pytest.mark.parametrize("shape", [(64, 64, 64, True), (64, 16, 128, False), (256, 320, 128, False)])   # general (B rows unaligned), skinny and tiled kernels
+@pytest.mark.parametrize("shape", [(64, 64, 64, True), (64, 16, 128, False), (256, 320, 128, False)])   # B rows unaligned, few columns, few tiles
 def test_removed_positions_take_no_part_in_the_sum(dtype, shape):
     """Sec. 3.2: the products with removed weights are skipped, not computed -- an infinity in B opposite a removed
     position leaves the result finite (the dense product of the pruned matrix has 0 * inf = NaN there)."""
@@ -469,7 +470,7 @@ def test_removed_positions_take_no_part_in_the_sum(dtype, shape):
 
 def test_int8_product_with_minus_128_in_both_operands():
     """-128 has no positive counterpart in int8: its products (+16384 with itself, -16256 with 127) must come out of
-    the integer matrix instructions exactly, in the general, the streaming and both tiled kernels."""
+    the integer matrix instructions exactly, with B rows at any alignment, few columns, few tiles and large ones."""
     rng = np.random.default_rng(91)
     pool = np.array([-128, -128, -127, 127, -1, 0, 1, 64], dtype=np.int8)
     for M, N, K, layout, general in ((33, 17, 64, "canonical", True), (33, 17, 64, "canonical", False), (64, 16, 256, "tiled", False),

@@ -1,5 +1,6 @@
 """Results whose rows are not whole, aligned 16-byte chunks: the tiled kernels' stores start at any address and the last
-chunk of a row is cut to its columns.  Bit-exact against the same product into an aligned buffer, and nothing outside
+chunk of a row is cut to its columns (2057 columns here, and test_gpu_tile_shapes.py), the kernels for few tiles store by
+element.  Bit-exact against the same product into an aligned buffer, and nothing outside
 the result is written."""
 import pytest
 import torch

@@ -58,7 +58,8 @@ def test_int8_output_is_bit_exact(case, sparse):
 
 @pytest.mark.parametrize("sparse", [True, False])
 def test_int8_output_from_the_general_kernel_is_bit_exact(sparse):
-    """Rows of B that are not 16-byte aligned (a view with a leading dimension of K + 4): the general kernel."""
+    """Rows of B that are not 16-byte aligned (a view with a leading dimension of K + 4): the general kernel for the dense
+    product, B staged through registers for the sparse one."""
     M, N, K = 45, 70, 96
     A, Bt, w_scale, bias, x_scale = make(M, N, K, 6)
     Pn = oracle.prune(A, "i8")
@@ -114,7 +115,7 @@ def test_unit_scales_reproduce_the_clamped_integer_product():
 
 @pytest.mark.parametrize("geom", [
     # M, n_img, H, W, C, R, S, pad, stride, layout
-    (33, 3, 5, 5, 32, 3, 3, (1, 1), (1, 1), "canonical"),      # general kernel
+    (33, 3, 5, 5, 32, 3, 3, (1, 1), (1, 1), "canonical"),      # staged (dense: general)
     (256, 4, 10, 10, 128, 3, 3, (1, 1), (1, 1), "tiled"),      # tiled kernel, implicit gather
     (128, 2, 9, 9, 128, 3, 3, (0, 1), (2, 1), "tiled"),
 ])

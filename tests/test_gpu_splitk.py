@@ -29,7 +29,7 @@ CASES = [
     ("bf16", "bf16", 320, 40, 4096, "canonical", "k"),  # ragged M and N
     ("i8", "i32", 32, 256, 4096, "tiled", "k"),         # one row block: two tiles with 96 rows never stored
     ("f16", "f32", 8, 200, 4096, "canonical", "n"),     # fewer rows than a row block
-    # N <= 32: the streaming kernel, slices of whole 64-column tiles
+    # N <= 32: slices of whole 128-byte steps (dense: the streaming kernel, whole 64-column tiles)
     ("bf16", "bf16", 1024, 16, 8192, "tiled", "k"),     # 32 row blocks, 4 slices
     ("i8", "i32", 512, 32, 16384, "canonical", "k"),    # 16 row blocks, 8 slices
     ("f16", "f32", 96, 7, 8192, "canonical", "k"),      # ragged N; 3 row blocks

@@ -1,5 +1,5 @@
-"""GPU parity of the sparse products that split K across a workgroup's wavefronts, each with an LDS ring of its own (the
-criteria of test_gpu_parity.py)."""
+"""GPU parity of the sparse products with few columns: those that split K across a workgroup's wavefronts, each with an LDS
+ring of its own, and the streaming kernel's (the criteria of test_gpu_parity.py)."""
 import pytest
 
 from test_gpu_parity import run_mm_case
