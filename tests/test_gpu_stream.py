@@ -29,14 +29,22 @@ def test_products_match_oracle(case):
         run_mm_case(*case, layout="tiled", b_order="k", sparse=True, seed=62)
 
 
-# 8-bit operands with more row blocks than compute units and N <= 32: the streaming kernel, whole tiles and K ending in the
-# middle of one (an instantiation of its own), fewer tiles than wavefronts, one row past a block
+# N <= 32 and more row blocks than compute units: 8-bit operands on the streaming kernel, fewer tiles than wavefronts, one row past
+# a block; K ending in half a tile: the tiled kernels; in a quarter of one: B staged through registers or, with a longer K, the
+# streaming kernel's form for it; 16-bit operands in two rounds of workgroups and past them
 MANY_ROWS = [
     ("i8", "i32", 8224, 1, 64),
     ("i8", "i32", 8225, 7, 1024),
     ("i8", "i32", 8224, 16, 96),
     ("i8", "i32", 8255, 3, 1184),
     ("i8", "i32", 8193, 31, 2080),
+    ("f16", "f16", 8225, 3, 48),
+    ("bf16", "bf16", 8200, 9, 1040),
+    ("f16", "f32", 77, 5, 144),
+    ("bf16", "f32", 9098, 17, 96),
+    ("bf16", "bf16", 8250, 2, 1056),
+    ("f16", "f16", 10880, 1, 128),
+    ("f16", "f32", 10881, 16, 192),
 ]
 
 
