@@ -322,8 +322,10 @@ static bool tiled_before_streaming(const MmArgs& a)
 // time again: measured against the tiled and the streaming kernel, up to 256 workgroups 1.05 - 2.4 times as fast
 // (1024 x 128 x 4096 bf16 16.7 -> 9.9 us, 8192 x 32 x 8192 25.1 -> 14.0, 8192 x 16 x 8192 18.1 -> 13.3; 4096 x 1 x 1024
 // level; with the compressed operand from HBM 8192 x 16 x 8192 19.3 -> 16.4, 8192 x 64 x 8192 32.3 -> 27.8), past that 0.4 -
-// 1.0 times -- except for 16-bit inputs with N <= 32 up to the 11008 rows from which the tiled kernels take them
-// (9216 x 16 x 4096 17.0 -> 12.3 us in two rounds).
+// 1.0 times -- except for 16-bit inputs with N <= 32 up to the 86 tiles of 128 rows from which the tiled kernels take them
+// (9216 x 16 x 4096 17.0 -> 12.3 us in two rounds; 10976 x 16 x 1024, 86 tiles, 5.7 us on the tiled kernels against 6.6).  Where
+// K has few steps and a partial one behind them, two rounds are 5 - 20 % behind the tiled kernels too (9098 x 17 x 288 4.8 us
+// against 5.6).
 // The limit of 512 columns is not one of speed: 32 - 512 rows on 513 - 2048 columns would run 1.3 - 2.0 times as fast here
 // (128 x 1000 x 4096 bf16 16.9 -> 9.8 us).  It keeps wide products of 16-bit types with few rows, convolutions written out
 // among them, on the kernel that adds K in the order of the implicit convolution with one chunk of channels, so that the two
@@ -340,7 +342,7 @@ static bool stream_first(const MmArgs& a)
     // Not one whole step, 33 - 64 columns: tiles of 64 x 64, one to a workgroup of two wavefronts (64 - 4096 rows 2.8 - 3.5 us
     // against 3.2 - 4.4; wider products are level or up to 12 % behind).
     if (a.N > 32 && a.N <= 64 && a.K * esize_of(a.in) < 128) return false;
-    return stream_workgroups(a) <= 256 || (a.N <= 32 && esize_of(a.in) == 2 && a.M < 11008);
+    return stream_workgroups(a) <= 256 || (a.N <= 32 && esize_of(a.in) == 2 && (a.M + 127) / 128 < 86 && (a.K % 64 == 0 || a.K >= 1024));
 }
 
 // Sparse products that the tiled kernels do not take: tiles of their shape with B staged through registers, or (N-major,
