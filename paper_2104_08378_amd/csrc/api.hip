@@ -339,9 +339,9 @@ static bool stream_first(const MmArgs& a)
     // 3.3 - 3.7; at 512 level in the tiled layout, 10 % behind in the canonical one).  16-bit types are level or behind there,
     // and wider products within 5 %.
     if (a.N <= 32 && esize_of(a.in) == 1 && a.K < (a.K % 128 == 0 ? 512 : 1024)) return false;
-    // Not one whole step, 33 - 64 columns: tiles of 64 x 64, one to a workgroup of two wavefronts (64 - 4096 rows 2.8 - 3.5 us
-    // against 3.2 - 4.4; wider products are level or up to 12 % behind).
-    if (a.N > 32 && a.N <= 64 && a.K * esize_of(a.in) < 128) return false;
+    // Not one whole step, up to 64 columns: tiles of 64 x 64, one to a workgroup of two wavefronts (33 - 64 columns, 64 - 4096 rows
+    // 2.8 - 3.5 us against 3.2 - 4.4; fewer 2.7 - 3.1 against 3.0 - 3.4; wider products are level or up to 12 % behind).
+    if (a.N <= 64 && a.K * esize_of(a.in) < 128) return false;
     return stream_workgroups(a) <= 256 || (a.N <= 32 && esize_of(a.in) == 2 && (a.M + 127) / 128 < 86 && (a.K % 64 == 0 || a.K >= 1024));
 }
 
