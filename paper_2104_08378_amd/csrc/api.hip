@@ -336,9 +336,9 @@ static bool stream_first(const MmArgs& a)
     // Few steps of an 8-bit operand: a wavefront has one at most, and the partial step at the end of K comes behind it.  With
     // N <= 32 the streaming kernel is 5 - 17 % ahead below four whole steps, and below eight where the last is a partial one
     // (33 - 8192 rows, replayed: K = 64 2.6 - 3.0 us against 3.0 - 3.5, 192 2.7 - 3.1 against 3.0 - 3.4, 576 2.9 - 3.6 against
-    // 3.3 - 3.7; at 512 level in the tiled layout, 10 % behind in the canonical one).  16-bit types are level or behind there,
-    // and wider products within 5 %.
-    if (a.N <= 32 && esize_of(a.in) == 1 && a.K < (a.K % 128 == 0 ? 512 : 1024)) return false;
+    // 3.3 - 3.7; at 512 level in the tiled layout, 10 % behind in the canonical one).  Half a tile of 64 columns at the end costs
+    // it more (32 x 16 x 288 3.2 here against 2.9).  16-bit types are level or behind there, and wider products within 5 %.
+    if (a.N <= 32 && esize_of(a.in) == 1 && a.K % 64 == 0 && a.K < (a.K % 128 == 0 ? 512 : 1024)) return false;
     // Not one whole step, up to 64 columns: tiles of 64 x 64, one to a workgroup of two wavefronts (33 - 64 columns, 64 - 4096 rows
     // 2.8 - 3.5 us against 3.2 - 4.4; fewer 2.7 - 3.1 against 3.0 - 3.4; wider products are level or up to 12 % behind).
     if (a.N <= 64 && a.K * esize_of(a.in) < 128) return false;

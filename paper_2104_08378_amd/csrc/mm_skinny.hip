@@ -25,7 +25,7 @@ namespace sp24 {
 constexpr int kSkinnyWaves = 8;
 constexpr int kSkinnyUnroll = 4;   // tiles whose loads are in flight together, per wavefront
 
-// PARTIAL: a canonical operand whose K is no multiple of 32 ends in a partial tile.  A form of its own: with its look at
+// PARTIAL: a canonical operand whose K is no multiple of 64 ends in a partial tile.  A form of its own: with its look at
 // every piece, and a branch around the loads, in the one kernel, the whole tiles of an 8-bit canonical operand took
 // 15 - 30 % longer (128256 x 8 x 1024: 28.9 -> 37.9 us).
 template <int DT, int OUT, bool SPARSE, bool PARTIAL>
@@ -191,12 +191,19 @@ sp24_status launch_mm_skinny(const MmArgs& a, hipStream_t st, bool* handled)
     const int es = esize_of(a.in);
     bool ok = a.N <= 32 && a.bo == SP24_B_KMAJOR && (reinterpret_cast<uintptr_t>(a.B) & 15u) == 0 && (a.ldb * es) % 16 == 0 &&
               a.M >= 32 && (a.M + 31) / 32 < ((int64_t)1 << 31);
-    // A canonical K of whole 32-column words that ends in half a tile is the tiled kernels' (9098 x 1 x 32 bf16 3.1 us against
-    // 5.7, 10880 x 17 x 96 4.2 against 6.2).  One that ends in a quarter they do not take: the check at every piece is worth it
-    // from K = 128 on, past 256 row blocks from some 1000 (against B staged through registers: 8192 x 17 x 80 3.7 us there,
-    // 3.9 here, x 144 4.2 and 4.0; 33333 x 1 x 48 4.4 and 12.9, x 560 16.7 and 17.0, x 1072 29.8 and 18.8).
-    if (a.sparse && a.layout == SP24_LAYOUT_CANONICAL)
-        ok = ok && (a.K % 64 == 0 || (a.K % 32 != 0 && a.K >= ((a.M + 31) / 32 <= 256 ? 128 : 1024)));
+    // A canonical K that ends inside a tile of 64 columns; the check at every piece is not always worth it.
+    //  * Half a tile, 16-bit: the tiled kernels are ahead (9098 x 1 x 32 bf16 3.1 us against 5.7, 10880 x 17 x 96 4.2 against 6.2).
+    //  * Half a tile, 8-bit, up to 128 tiles of 128 rows (the tiled kernels' 64-row tiles): those are up to 9 % ahead at K = 96,
+    //    7 - 30 % behind from 160 to 1568, within 7 % at 2080 and up to 30 % ahead past that (12000 x 8 x 544 5.2 us there, 4.5
+    //    here; x 6176 17 and 22).  Up to 384 tiles they are ahead below K = 512 and 5 - 70 % behind from there (33333 x 1 x 4128
+    //    49.9 and 29.9; level again for 203 tiles past 3104), with more behind from some 1000 on, where N <= 8 (10 - 40 %).
+    //  * A quarter of a tile, which they do not take, against B staged through registers: 8192 x 17 x 80 3.7 us there, 3.9 here,
+    //    x 144 4.2 and 4.0; past 256 row blocks 33333 x 1 x 48 4.4 and 12.9, x 560 16.7 and 17.0, x 1072 29.8 and 18.8.
+    if (a.sparse && a.layout == SP24_LAYOUT_CANONICAL && a.K % 64 != 0) {
+        const int64_t tiles = (a.M + 127) / 128;
+        if (a.K % 32 != 0) ok = ok && a.K >= ((a.M + 31) / 32 <= 256 ? 128 : 1024);
+        else ok = ok && es == 1 && (tiles <= 128 ? a.K > 128 && a.K < 2048 : tiles <= 384 ? a.K >= 512 : a.K >= 1024 && a.N <= 8);
+    }
     if (!ok) return SP24_OK;
     *handled = true;
     if (a.in == SP24_I8) {

@@ -30,14 +30,18 @@ def test_products_match_oracle(case):
 
 
 # N <= 32 and more row blocks than compute units: 8-bit operands on the streaming kernel, fewer tiles than wavefronts, one row past
-# a block; K ending in half a tile: the tiled kernels; in a quarter of one: B staged through registers or, with a longer K, the
-# streaming kernel's form for it; 16-bit operands in two rounds of workgroups and past them
+# a block; K ending in half a tile: the tiled kernels for 16-bit operands, and for 8-bit ones the streaming kernel's form for it but
+# for a short K, or a long one on few tiles; in a quarter of one: B staged through registers or, with a longer K, that form; 16-bit
+# operands in two rounds of workgroups and past them
 MANY_ROWS = [
     ("i8", "i32", 8224, 1, 64),
     ("i8", "i32", 8225, 7, 1024),
     ("i8", "i32", 8224, 16, 96),
     ("i8", "i32", 8255, 3, 1184),
     ("i8", "i32", 8193, 31, 2080),
+    ("i8", "i32", 9000, 7, 160),
+    ("i8", "i32", 16385, 16, 544),
+    ("i8", "i32", 49153, 1, 1056),
     ("f16", "f16", 8225, 3, 48),
     ("bf16", "bf16", 8200, 9, 1040),
     ("f16", "f32", 77, 5, 144),

@@ -91,7 +91,8 @@ F8 = [
     (2048, 509, 640, "tiled", "n"),
     (2100, 701, 160, "canonical", "n"),
     (45, 100, 1056, "canonical", "k"),      # few tiles of 64 columns
-    (8225, 5, 96, "canonical", "k"),        # the streaming kernel
+    (8225, 5, 96, "canonical", "k"),        # tiles of 64 x 64, a partial step
+    (8225, 5, 288, "canonical", "k"),       # the streaming kernel, half a tile
 ]
 
 
