@@ -521,12 +521,20 @@ static sp24_status mm_splitk(const MmArgs& a, void* workspace, size_t workspace_
         // With more than 32 columns the plan's eight slices, which tiles of 128 x 128 leave room for, win where a slice is
         // long.  Measured over 16 - 512 steps a slice, operands from HBM: one slice (an unsplit product) is 3 - 40 % ahead until
         // 80 steps, 9 % behind to 3 % ahead at 96 and 5 - 20 % behind at 128 (8192 x 64 x 8192 bf16 26.8 against 23.5 us); two
-        // slices are level until 64 or up to 15 % ahead, at 96 13 % behind to 5 % ahead (4096 x 64 x 12288 24.9 against 21.6);
-        // three and more stay ahead until 128 (7 % behind to 27 %).  Operands in the last-level cache favour the kernel by some
-        // 10 % more.  The tiled kernels are slower on a canonical operand: one slice of it is level at 128 steps, and two stay
-        // 9 % and more ahead as far as measured (1000 x 200 x 20480 bf16 29.8 against 37.6).
+        // slices are level until 64 or up to 15 % ahead, at 96 13 % behind to 5 % ahead (4096 x 64 x 12288 24.9 against 21.6), with
+        // up to 64 columns 9 - 11 % behind at 80 already; three stay ahead with more than 64 columns (144 - 320 steps a slice: 4 - 18
+        // %), with fewer until 80 (2400 x 64 x 15360 21.6 against 22.0, x 18432 24.4 against 23.9, x 24576 29.8 against 27.7); four
+        // and more always (256 x 500 x 40960 1.41 times as fast, 128 x 512 2.1 times).
+        // Operands in the last-level cache favour the kernel at one and two slices by some 10 % more.  The tiled kernels are slower
+        // on a canonical operand: one slice of it is level at 128 steps, and two stay 9 % and more ahead as far as measured
+        // (1000 x 200 x 20480 bf16 29.8 against 37.6).
         const bool canonical = a.layout == SP24_LAYOUT_CANONICAL;
-        const int64_t longest = a.N <= 32 ? steps : n == 1 ? (canonical ? 128 : 104) : canonical ? 256 : n == 2 ? 88 : 128;
+        int64_t longest = steps;
+        if (a.N > 32 && n <= (a.N <= 64 ? 3 : 2)) {
+            if (n == 1) longest = canonical ? 128 : 104;
+            else if (canonical) longest = 256;
+            else longest = n == 3 ? 96 : a.N <= 64 ? 72 : 88;
+        }
         if (steps <= longest * n) {
             if (n == 1) return mm_dispatch(a, st);
             part.k_slices = n;
