@@ -77,14 +77,28 @@ __device__ __forceinline__ KRange k_range_of_workgroup(MmArgs& a, int total_step
     return {first, min(a.slice_steps, total_steps - first), slice == a.k_slices - 1 ? tail : 0};
 }
 
+// The transfers of a step, dealt out evenly: transfer x of wavefront `wave` is number id(wave, x) of the N.  Where N is no
+// multiple of NW the last wavefronts fetch the last one again, the same bytes to the same place, which keeps every
+// wavefront's count the same.
+template <int N, int NW>
+struct deal {
+    static constexpr int each = (N + NW - 1) / NW;
+    __device__ static __forceinline__ int id(int wave, int x)
+    {
+        const int i = wave * each + x;
+        if constexpr (N % NW != 0) return min(i, N - 1);
+        else return i;
+    }
+};
+
 // Transfer ROWS rows x 128 bytes (row r of the stage = global row min(row0 + r, limit - 1)) into a stage.
-// Offsets of the ROWS/8/NW transfer instructions (8 rows each) of one of NW wavefronts, relative to the first row.
+// Offsets of the transfer instructions (8 rows each) of one of NW wavefronts, relative to the first row.
 template <int ROWS, int NW>
-__device__ __forceinline__ void dma_offsets(int64_t row0, int64_t limit, int64_t ld_bytes, int wave, int lane, uint32_t (&off)[ROWS / 8 / NW])
+__device__ __forceinline__ void dma_offsets(int64_t row0, int64_t limit, int64_t ld_bytes, int wave, int lane, uint32_t (&off)[deal<ROWS / 8, NW>::each])
 {
 #pragma unroll
-    for (int j = 0; j < ROWS / 8 / NW; ++j) {
-        const int row = (wave * (ROWS / 8 / NW) + j) * 8 + (lane >> 3);
+    for (int j = 0; j < deal<ROWS / 8, NW>::each; ++j) {
+        const int row = deal<ROWS / 8, NW>::id(wave, j) * 8 + (lane >> 3);
         int64_t g = row0 + row;
         if (g >= limit) g = limit - 1;                       // ragged edge: fetch a valid row, never stored
         const int piece = (lane & 7) ^ ((row >> 1) & 7);
@@ -148,13 +162,13 @@ __device__ __forceinline__ void lds_dma_tail(const uint8_t* base, uint32_t off, 
 template <int ROWS, int NW>
 __device__ __forceinline__ bool past_k_kmajor(int j, int wave, int lane, int tail)
 {
-    const int row = (wave * (ROWS / 8 / NW) + j) * 8 + (lane >> 3);
+    const int row = deal<ROWS / 8, NW>::id(wave, j) * 8 + (lane >> 3);
     return (((lane & 7) ^ ((row >> 1) & 7)) << 4) >= tail;
 }
 template <int BN, int NW, int ES>
 __device__ __forceinline__ bool past_k_nmajor(int j, int wave, int lane, int tail)
 {
-    const int p = (wave * (BN / 8 / NW) + j) * 1024 + lane * 16;
+    const int p = deal<BN / 8, NW>::id(wave, j) * 1024 + lane * 16;
     return (p / (BN * ES)) * ES >= tail;
 }
 
@@ -182,14 +196,14 @@ struct ConvTap {
 // coordinates of tap (0, 0) and the byte offset of that (possibly virtual) pixel, swizzle piece included.
 template <int ROWS, int NW, int ES>
 struct conv_rows {
-    static constexpr int NJ = ROWS / 8 / NW;
+    static constexpr int NJ = deal<ROWS / 8, NW>::each;
     int iy0[NJ], ix0[NJ];
     int32_t off[NJ];
     __device__ __forceinline__ void init(const ConvGeom& g, int64_t n0, int64_t N, int wave, int lane)
     {
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-            const int row = (wave * NJ + j) * 8 + (lane >> 3);
+            const int row = deal<ROWS / 8, NW>::id(wave, j) * 8 + (lane >> 3);
             const int piece = (lane & 7) ^ ((row >> 1) & 7);
             const int64_t n = n0 + row;
             if (n < N) {
@@ -214,7 +228,7 @@ struct conv_rows {
         const uint64_t mask = (uint64_t)0 - inside;
         const uint64_t pixel = reinterpret_cast<uint64_t>(X) + (uint32_t)(off[j] + tap_off);
         const uint64_t src = (pixel & mask) | (reinterpret_cast<uint64_t>(k_zero_row) & ~mask);
-        lds_dma16_addr(reinterpret_cast<const uint8_t*>(src), stage + (wave * NJ + j) * 1024);
+        lds_dma16_addr(reinterpret_cast<const uint8_t*>(src), stage + deal<ROWS / 8, NW>::id(wave, j) * 1024);
     }
 };
 
@@ -242,14 +256,14 @@ __device__ __forceinline__ int nmajor_swizzle(int k, int chunks)
 // LDS position p of the B region <- row p / row_bytes, chunk (p % row_bytes) / 16 ^ swizzle(row); chunks past the
 // last column of the matrix are replaced by the last valid one (never stored).
 template <int BN, int NW, int ES>
-__device__ __forceinline__ void dma_offsets_nmajor(int64_t col0, int64_t N, int64_t ld_bytes, int wave, int lane, uint32_t (&off)[BN / 8 / NW])
+__device__ __forceinline__ void dma_offsets_nmajor(int64_t col0, int64_t N, int64_t ld_bytes, int wave, int lane, uint32_t (&off)[deal<BN / 8, NW>::each])
 {
     constexpr int kRowB = BN * ES, kChunks = kRowB / 16;
     const int64_t left = (N - col0) * ES / 16;
     const int valid = left < kChunks ? (int)left : kChunks;
 #pragma unroll
-    for (int j = 0; j < BN / 8 / NW; ++j) {
-        const int p = (wave * (BN / 8 / NW) + j) * 1024 + lane * 16;
+    for (int j = 0; j < deal<BN / 8, NW>::each; ++j) {
+        const int p = deal<BN / 8, NW>::id(wave, j) * 1024 + lane * 16;
         const int row = p / kRowB;
         int c = ((p % kRowB) >> 4) ^ nmajor_swizzle<ES>(row, kChunks);
         if (c >= valid) c = valid - 1;
@@ -299,10 +313,10 @@ struct nmajor_frags {
 };
 
 template <int ROWS, int NW>
-__device__ __forceinline__ void dma_rows(const uint8_t* base, const uint32_t (&off)[ROWS / 8 / NW], uint8_t* stage, int wave)
+__device__ __forceinline__ void dma_rows(const uint8_t* base, const uint32_t (&off)[deal<ROWS / 8, NW>::each], uint8_t* stage, int wave)
 {
 #pragma unroll
-    for (int j = 0; j < ROWS / 8 / NW; ++j) lds_dma16(base, off[j], stage + (wave * (ROWS / 8 / NW) + j) * 1024);
+    for (int j = 0; j < deal<ROWS / 8, NW>::each; ++j) lds_dma16(base, off[j], stage + deal<ROWS / 8, NW>::id(wave, j) * 1024);
 }
 
 // Epilogue of the tiled kernels.  A wavefront's accumulators hold, per 32x32 tile, 32 consecutive columns of
@@ -470,10 +484,10 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_spmm_pipe(MmArgs a, int til
     constexpr int NW = WM * WN;
     constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN;
     constexpr int RB = BM / 32;               // row blocks per workgroup tile
-    constexpr int NJB = BN / 8 / NW;          // B transfers per wavefront and step (1 KiB each)
-    constexpr int NJV = RB * 2 / NW;          // V transfers (1 KiB each)
-    constexpr int NJM = RB * T64 / NW;        // metadata transfers (256 B each)
-    static_assert(RB * T64 % NW == 0 && BN % (8 * NW) == 0, "transfers must divide evenly over the wavefronts");
+    using deal_b = deal<BN / 8, NW>;          // B transfers of a step (1 KiB each)
+    using deal_v = deal<RB * 2, NW>;          // V transfers (1 KiB each)
+    using deal_m = deal<RB * T64, NW>;        // metadata transfers (256 B each)
+    constexpr int NJB = deal_b::each, NJV = deal_v::each, NJM = deal_m::each;
     constexpr int NV = NJB + NJV + NJM;
     constexpr int kVOff = BN * kRowBytes, kMOff = kVOff + RB * 2048;
     constexpr int kStageBytes = kMOff + RB * T64 * 256;
@@ -506,8 +520,8 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_spmm_pipe(MmArgs a, int til
     if constexpr (CONV) b_conv.init(a.conv, (int64_t)tn * BN, a.N, wave, lane);
     else if constexpr (NMAJ) dma_offsets_nmajor<BN, NW, ES>((int64_t)tn * BN, a.N, ldb_bytes, wave, lane, b_off);
     else dma_offsets<BN, NW>((int64_t)tn * BN, a.N, ldb_bytes, wave, lane, b_off);
-    // V: transfer x of this wavefront is 1 KiB number (wave*NJV + x) of the RB*2 of a step: row block /2, half %2.
-    // metadata: transfer x is 256-byte tile number (wave*NJM + x) of the RB*T64 of a step.
+    // V: transfer x of this wavefront is 1 KiB number deal_v::id(wave, x) of the RB*2 of a step: row block /2, half %2.
+    // metadata: transfer x is 256-byte tile number deal_m::id(wave, x) of the RB*T64 of a step.
     // From the tiled layout a transfer is one contiguous run, already in the order of the lanes that will read it.  From the
     // canonical one it takes whole runs of rows of the row-major arrays (Sec. 3.1: their position follows from the row
     // and column alone): four lanes to the 64 bytes of values of a row and step, the 16-byte pieces rotated by the row
@@ -524,7 +538,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_spmm_pipe(MmArgs a, int til
         const int64_t vrow = a.K / 2 * ES, mrow = a.K / 8, row0 = (int64_t)tm * BM;
 #pragma unroll
         for (int x = 0; x < NJV; ++x) {
-            const int id = wave * NJV + x, in_block = CONV ? lane & 31 : (id & 1) * 16 + (lane >> 2);
+            const int id = deal_v::id(wave, x), in_block = CONV ? lane & 31 : (id & 1) * 16 + (lane >> 2);
             int64_t row = row0 + (id >> 1) * 32 + in_block;
             if (row >= a.M) row = a.M - 1;                 // ragged M: a valid row, never stored
             v_base[x] = wave_uniform(reinterpret_cast<const uint8_t*>(a.A) + row0 * vrow);
@@ -533,7 +547,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_spmm_pipe(MmArgs a, int til
         }
 #pragma unroll
         for (int x = 0; x < NJM; ++x) {
-            const int id = wave * NJM + x;
+            const int id = deal_m::id(wave, x);
             int64_t row = row0 + (id / T64) * 32 + (CONV ? lane & 31 : (id % T64) * 16 + lane / (2 * T64));
             if (row >= a.M) row = a.M - 1;
             m_base[x] = wave_uniform(reinterpret_cast<const uint8_t*>(a.meta) + row0 * mrow);
@@ -542,7 +556,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_spmm_pipe(MmArgs a, int til
     } else {
 #pragma unroll
         for (int x = 0; x < NJV; ++x) {
-            const int id = wave * NJV + x;
+            const int id = deal_v::id(wave, x);
             int64_t rb = (int64_t)tm * RB + (id >> 1);
             if (rb >= rb_total) rb = rb_total - 1;         // ragged M: compute on a valid row block, never stored
             v_base[x] = wave_uniform(reinterpret_cast<const uint8_t*>(a.A) + rb * KB64 * (1024 * ES) + (id & 1) * 1024);
@@ -550,7 +564,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_spmm_pipe(MmArgs a, int til
         }
 #pragma unroll
         for (int x = 0; x < NJM; ++x) {
-            const int id = wave * NJM + x;
+            const int id = deal_m::id(wave, x);
             int64_t rb = (int64_t)tm * RB + id / T64;
             if (rb >= rb_total) rb = rb_total - 1;
             m_base[x] = wave_uniform(reinterpret_cast<const uint8_t*>(a.meta) + (rb * KB64 + id % T64) * 256);
@@ -574,14 +588,14 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_spmm_pipe(MmArgs a, int til
         }
 #pragma unroll
         for (int x = 0; x < NJV; ++x) {
-            const int id = wave * NJV + x;
+            const int id = deal_v::id(wave, x);
             // (canonical: the piece's place in the 64 value bytes of a row and step)
             const bool p = canonical ? canonical_piece((id & 1) * 16 + (lane >> 2), lane & 3) * 16 >= tail / 2 : ((ES == 1) ? 64 * (id & 1) >= tail : false);
             past_k |= (uint32_t)p << (NJB + x);
         }
 #pragma unroll
         for (int x = 0; x < NJM; ++x) {
-            const int id = wave * NJM + x;
+            const int id = deal_m::id(wave, x);
             const bool p = canonical ? (lane % (2 * T64)) * 32 * ES >= tail : 64 * ES * (id % T64) >= tail;
             past_k |= (uint32_t)p << (NJB + NJV + x);
         }
@@ -597,16 +611,16 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_spmm_pipe(MmArgs a, int til
         constexpr bool partial = decltype(partial_tag)::value && !CONV;
         const bool pk = (past_k >> x) & 1u;
         if (x < NJB) {
-            uint8_t* dst = stg + (wave * NJB + x) * 1024;
+            uint8_t* dst = stg + deal_b::id(wave, x) * 1024;
             if constexpr (CONV) b_conv.issue(x, reinterpret_cast<const uint8_t*>(a.B), a.conv, tap, stg, wave);
             else if (partial) lds_dma_tail<false>(b_blk + (int64_t)step * b_step, b_off[x], pk, dst);
             else lds_dma16(b_blk + (int64_t)step * b_step, b_off[x], dst);
         } else if (x < NJB + NJV) {
-            uint8_t* dst = stg + kVOff + (wave * NJV + x - NJB) * 1024;
+            uint8_t* dst = stg + kVOff + deal_v::id(wave, x - NJB) * 1024;
             if (partial) lds_dma_tail<false>(v_base[x - NJB] + (int64_t)step * v_step, v_off[x - NJB], pk, dst);
             else lds_dma16(v_base[x - NJB] + (int64_t)step * v_step, v_off[x - NJB], dst);
         } else {
-            uint8_t* dst = stg + kMOff + (wave * NJM + x - NJB - NJV) * 256;
+            uint8_t* dst = stg + kMOff + deal_m::id(wave, x - NJB - NJV) * 256;
             if (partial) lds_dma_tail<true>(m_base[x - NJB - NJV] + (int64_t)step * m_step, m_off[x - NJB - NJV], pk, dst);
             else lds_dma4(m_base[x - NJB - NJV] + (int64_t)step * m_step, m_off[x - NJB - NJV], dst);
         }
@@ -808,7 +822,9 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_gemm_pipe(MmArgs a, int til
     constexpr int BK = kRowBytes / ES;
     constexpr int NW = WM * WN;
     constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN;
-    constexpr int NJA = BM / 8 / NW, NJB = BN / 8 / NW;
+    using deal_a = deal<BM / 8, NW>;
+    using deal_b = deal<BN / 8, NW>;
+    constexpr int NJA = deal_a::each, NJB = deal_b::each;
     constexpr int kStageBytes = (BM + BN) * kRowBytes;
     using acc_t = typename acc_of<DT>::type;
     constexpr int kEpiBytes = NW * epilogue_geometry<OUT, TN>::kWaveBytes;
@@ -854,12 +870,12 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_gemm_pipe(MmArgs a, int til
 #pragma unroll
             for (int j = 0; j < NJA; ++j)
                 lds_dma_tail<false>(a_blk + (int64_t)step * kRowBytes, a_off[j], past_k_kmajor<BM, NW>(j, wave, lane, tail),
-                                    stage_ptr(u) + (wave * NJA + j) * 1024);
+                                    stage_ptr(u) + deal_a::id(wave, j) * 1024);
 #pragma unroll
             for (int j = 0; j < NJB; ++j)
                 lds_dma_tail<false>(b_blk + (int64_t)step * b_step, b_off[j],
                                     NMAJ ? past_k_nmajor<BN, NW, ES>(j, wave, lane, tail) : past_k_kmajor<BN, NW>(j, wave, lane, tail),
-                                    stage_ptr(u) + BM * kRowBytes + (wave * NJB + j) * 1024);
+                                    stage_ptr(u) + BM * kRowBytes + deal_b::id(wave, j) * 1024);
         }
     };
     auto dma = [&](int step, const ConvTap& tap, int u) {
@@ -926,9 +942,9 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_gemm_pipe(MmArgs a, int til
     constexpr int kBehindBarrier = TM * TN * NV / kSlots;       // transfers issued in sub-step 3
     constexpr int kWaitAndReads = waitcnt_vm((NS - 2) * NV) & ~(15 << 8);
     auto dma_one = [&](int step, const ConvTap& tap, int u, int x) {
-        if (x < NJA) lds_dma16(a_blk + (int64_t)step * kRowBytes, a_off[x], stage_ptr(u) + (wave * NJA + x) * 1024);
+        if (x < NJA) lds_dma16(a_blk + (int64_t)step * kRowBytes, a_off[x], stage_ptr(u) + deal_a::id(wave, x) * 1024);
         else if constexpr (CONV) b_conv.issue(x - NJA, reinterpret_cast<const uint8_t*>(a.B), a.conv, tap, stage_ptr(u) + BM * kRowBytes, wave);
-        else lds_dma16(b_blk + (int64_t)step * b_step, b_off[x - NJA], stage_ptr(u) + BM * kRowBytes + (wave * NJB + x - NJA) * 1024);
+        else lds_dma16(b_blk + (int64_t)step * b_step, b_off[x - NJA], stage_ptr(u) + BM * kRowBytes + deal_b::id(wave, x - NJA) * 1024);
     };
     auto dma_slot = [&](int m, int u) {
         if (m < kSlots) {
@@ -1015,61 +1031,87 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_gemm_pipe(MmArgs a, int til
 // ---------------------------------------------------------------------------
 // Host side.
 // ---------------------------------------------------------------------------
-// NSS / NSD: pipeline stages of the sparse / dense kernel; CONVS: whether the tile shape serves convolutions too
-// (a shape that never does is not compiled for them)
-template <int DT, int OUT, int WM, int WN, int TM, int TN, int NSS, int NSD, bool CONVS = true>
+// NSS / NSD: pipeline stages of the sparse / dense kernel; USES: which problems the tile shape serves (it is not compiled
+// for others)
+enum { kSparse = 1, kDense = 2, kSparseConv = 4, kDenseConv = 8, kProducts = kSparse | kDense, kConvs = kSparseConv | kDenseConv };
+
+template <int DT, int OUT, int WM, int WN, int TM, int TN, int NSS, int NSD, int USES>
 static sp24_status run_pipe(const MmArgs& a, hipStream_t st)
 {
     constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN;
     const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (int)((a.N + BN - 1) / BN);
     const dim3 grid((unsigned)(tiles_m * tiles_n), (unsigned)(a.k_slices > 1 ? a.k_slices : 1)), block(64 * WM * WN);
-    if constexpr (!CONVS) {
-        if (a.conv.on) return SP24_ERR_LAUNCH;
-        if (a.sparse) {
+    bool known = false;
+    if constexpr ((USES & kSparseConv) != 0) {
+        if (a.sparse && a.conv.on) {
+            known = true;
+            k_spmm_pipe<DT, OUT, WM, WN, TM, TN, NSS, 1><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
+        }
+    }
+    if constexpr ((USES & kSparse) != 0) {
+        if (a.sparse && !a.conv.on) {
+            known = true;
             if (a.bo == SP24_B_NMAJOR) k_spmm_pipe<DT, OUT, WM, WN, TM, TN, NSS, 2><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
             else k_spmm_pipe<DT, OUT, WM, WN, TM, TN, NSS, 0><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
-        } else {
+        }
+    }
+    if constexpr ((USES & kDenseConv) != 0) {
+        if (!a.sparse && a.conv.on) {
+            known = true;
+            k_gemm_pipe<DT, OUT, WM, WN, TM, TN, NSD, 1><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
+        }
+    }
+    if constexpr ((USES & kDense) != 0) {
+        if (!a.sparse && !a.conv.on) {
+            known = true;
             if (a.bo == SP24_B_NMAJOR) k_gemm_pipe<DT, OUT, WM, WN, TM, TN, NSD, 2><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
             else k_gemm_pipe<DT, OUT, WM, WN, TM, TN, NSD, 0><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
         }
-        return hipGetLastError() == hipSuccess ? SP24_OK : SP24_ERR_LAUNCH;
     }
-    if (a.sparse) {
-        if (a.conv.on) k_spmm_pipe<DT, OUT, WM, WN, TM, TN, NSS, 1><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
-        else if (a.bo == SP24_B_NMAJOR) k_spmm_pipe<DT, OUT, WM, WN, TM, TN, NSS, 2><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
-        else k_spmm_pipe<DT, OUT, WM, WN, TM, TN, NSS, 0><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
-    } else {
-        if (a.conv.on) k_gemm_pipe<DT, OUT, WM, WN, TM, TN, NSD, 1><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
-        else if (a.bo == SP24_B_NMAJOR) k_gemm_pipe<DT, OUT, WM, WN, TM, TN, NSD, 2><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
-        else k_gemm_pipe<DT, OUT, WM, WN, TM, TN, NSD, 0><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
-    }
-    return hipGetLastError() == hipSuccess ? SP24_OK : SP24_ERR_LAUNCH;
+    return known && hipGetLastError() == hipSuccess ? SP24_OK : SP24_ERR_LAUNCH;
 }
 
 template <int DT, int OUT>
 static sp24_status pick_tile_general(const MmArgs& a, hipStream_t st)
 {
+    // What sets the pace of a product whose tiles make one round of workgroups is the bytes a compute unit brings in, a step
+    // of 80 per row and 128 per column (dense: 128 and 128) at some 60 - 70 GB/s from HBM and 110 - 150 from the last-level
+    // cache and the L2, whatever the number of units (a unit has only so many lines on their way: eight times the
+    // transfers in flight do not change it).  So: the smallest tile whose workgroups still find a unit each.
+    const int64_t cols = (a.N + 127) / 128, small = ((a.M + 127) / 128) * cols;
+    // More than 256 tiles of 128x128, two and three workgroups to some units: tiles of 192 rows (six wavefronts) or 256 (eight)
+    // where those are at most 256.  Against 128x128 (16-bit dense: 256x256), us: 11008 x 333 x 4096 bf16, 258 tiles, 192
+    // rows 35.6 -> 26.5 (from HBM 41.5 -> 34.0); 4096 x 2048 x 4096 bf16, 512 tiles, 256 rows 43.6 -> 37.0 (53.2 -> 41.3),
+    // int8 29.2 -> 26.3 (36.3 -> 28.6); dense 4096 x 1152 x 4096 bf16 80 -> 41, 4096 x 2048 x 4096 77 -> 57, int8
+    // 38.1 -> 36.0.  192 rows are 10 - 17 % ahead of 256 from HBM and level with them in the cache.
+    // A sparse product of few steps spends its time in the stores, which two workgroups to a unit overlap: the line
+    // lies where both are level (16-bit results 0.94 - 1.01 times as fast at 8 steps, 1.04 - 1.21 at 12; 32-bit
+    // results 0.94 - 1.01 at 8 and 1.00 - 1.24 at 16 on 192 rows, 0.85 - 1.01 at 16 and 0.99 - 1.15 at 24 on 256; dense
+    // ones 0.97 - 1.9 throughout).
+    // Convolutions gather B, whose cost halves per product with 256 rows (1.09 - 1.21 times as fast, int8 0.96 - 1.15) and
+    // not with 192.
+    const int64_t steps = a.K * (is8<DT> ? 1 : 2) / kRowBytes;
+    constexpr bool kWideOut = out_size<OUT>() == 4;
+    if (small > 256 && !a.conv.on && ((a.M + 191) / 192) * cols <= 256 && (!a.sparse || steps >= (kWideOut ? 16 : 12)))
+        return run_pipe<DT, OUT, 3, 2, 2, 2, 5, 3, kProducts>(a, st);
+    if (small > 256 && ((a.M + 255) / 256) * cols <= 256 && (!a.sparse || steps >= (a.conv.on ? 4 : kWideOut ? 24 : 12)))
+        return run_pipe<DT, OUT, 4, 2, 2, 2, 4, 3, kProducts | kConvs>(a, st);
     // 256x256 tiles when there are enough of them for half the chip, else 128x128
     const int64_t big = ((a.M + 255) / 256) * ((a.N + 255) / 256);
     // one workgroup of eight wavefronts of 64x128 each per compute unit (its wavefronts sit two to a SIMD, so that
     // one computes while the other waits).  The large tile moves half the operand bytes per product through the
-    // L2 and LDS, and that outweighs idle compute units well below a full chip.  Measured on 100 - 192 large tiles,
-    // K from 512 to 8192, operands from HBM: up to 128 large tiles the 512 small ones run in one round, two
-    // workgroups to a unit, and the two shapes are level (the small one ahead by 10 - 17 % at K <= 1024); from
-    // there on the small tiles need a second round and the large tile wins by 10 - 26 % (sparse), 3 - 38 % (dense).
-    // The 16-bit dense product, the one that moves the most bytes per instruction, gains 7 - 14 % from 100 tiles on.
-    // Convolutions follow the general rule (dense 16-bit at 108 tiles: the large tile 40 % slower; at 154 - 196: 7 - 20 %
-    // faster, strided sparse ones 25 - 28 %).
+    // L2 and LDS, and that outweighs idle compute units well below a full chip: past 256 tiles of 256x128, 145 - 192
+    // large ones, K from 512 to 8192, operands from HBM, it is 10 - 26 % (sparse) and 3 - 38 % (dense) ahead of 128x128.
+    // Convolutions follow the general rule (at 154 - 196: 7 - 20 % faster, strided sparse ones 25 - 28 %).
     // -- unless the large tile would be mostly padding: rows and columns it covers beyond M and N are computed all the
     // same, and per product computed the small tile (two workgroups to a unit) costs about a third more
     const int64_t enough = (!a.conv.on && !is8<DT> && !a.sparse) ? 100 : 129;
     const double cover_big = (double)(((a.M + 255) / 256) * 256) * (double)(((a.N + 255) / 256) * 256);
     const double cover_small = (double)(((a.M + 127) / 128) * 128) * (double)(((a.N + 127) / 128) * 128);
-    if (big >= enough && cover_big <= 1.35 * cover_small) return run_pipe<DT, OUT, 4, 2, 2, 4, 3, 2>(a, st);
+    if (big >= enough && cover_big <= 1.35 * cover_small) return run_pipe<DT, OUT, 4, 2, 2, 4, 3, 2, kProducts | kConvs>(a, st);
     // 128x128 tiles, four wavefronts.  With few tiles one workgroup per compute unit is all there is, and a short
     // step (a quarter of the large tile's arithmetic) hides little latency: six (dense: four) stages, transfers
     // five (three) steps ahead.  With many tiles three (two) stages leave room for two workgroups per compute unit.
-    const int64_t small = ((a.M + 127) / 128) * ((a.N + 127) / 128);
     // At most 128 of them: tiles of 64 rows, two wavefronts, put twice as many compute units to work.  Such a product
     // is bound by what one unit can keep in flight (its LDS ring against the latency of the L2 and of HBM), not
     // by arithmetic; the smaller stages also allow a deeper ring, and with N <= 64 a 64-column tile does not fetch
@@ -1080,11 +1122,11 @@ static sp24_status pick_tile_general(const MmArgs& a, hipStream_t st)
     // (Not for a product already split along K, whose slices fill the chip; not for convolutions, where the gather of
     // B is the cost and doubles with it: strided 3x3 layers with 13 - 98 tiles were 20 - 30 % slower.)
     if (small <= 128 && !a.conv.on && a.k_slices <= 1 && (a.sparse || a.N <= 128)) {
-        if (a.N <= 64) return run_pipe<DT, OUT, 2, 1, 1, 2, 9, 9, false>(a, st);
-        return run_pipe<DT, OUT, 2, 1, 1, 4, 7, 6, false>(a, st);
+        if (a.N <= 64) return run_pipe<DT, OUT, 2, 1, 1, 2, 9, 9, kProducts>(a, st);
+        return run_pipe<DT, OUT, 2, 1, 1, 4, 7, 6, kProducts>(a, st);
     }
-    if (small <= 256) return run_pipe<DT, OUT, 2, 2, 2, 2, 6, 4>(a, st);
-    return run_pipe<DT, OUT, 2, 2, 2, 2, 3, 2>(a, st);
+    if (small <= 256) return run_pipe<DT, OUT, 2, 2, 2, 2, 6, 4, kProducts | kConvs>(a, st);
+    return run_pipe<DT, OUT, 2, 2, 2, 2, 3, 2, kProducts | kConvs>(a, st);
 }
 
 } // namespace sp24

@@ -1,0 +1,53 @@
+"""GPU parity of the tiled products on tiles of 192 and 256 rows by 128 columns (the criteria of test_gpu_parity.py and
+test_gpu_conv.py): more than 256 tiles of 128 x 128 and at most 256 of these."""
+import pytest
+
+from test_gpu_conv import run_case as run_conv_case
+from test_gpu_parity import run_mm_case
+
+pytestmark = pytest.mark.gpu
+
+# one whole tile and one that ends inside each of its row blocks and columns; whole and partial last steps; for the sparse
+# products the fewest steps that take these tiles (12; 16 and 24 for results of 32 bits)
+SPARSE = [
+    ("bf16", "bf16", 300, 11007, 800, "canonical"),     # 192 rows
+    ("f16", "f32", 320, 11001, 1024, "tiled"),
+    ("i8", "i32", 384, 10990, 2112, "tiled"),
+    ("f16", "f16", 200, 16500, 800, "canonical"),       # 256 rows
+    ("bf16", "bf16", 256, 16400, 832, "tiled"),
+    ("f16", "f32", 160, 16401, 1536, "tiled"),
+]
+# a single step, fewer than the ring holds, a partial one alone and behind others
+DENSE = [
+    ("bf16", "f32", 300, 11007, 96),
+    ("i8", "i32", 384, 10990, 128),
+    ("i8", "i32", 300, 11000, 480),
+    ("f16", "f16", 200, 16500, 32),
+    ("bf16", "bf16", 256, 16400, 352),
+    ("i8", "i32", 160, 16401, 640),
+]
+# strided ones: four steps and nine, ragged rows and pixels
+CONVS = [
+    ("bf16", "bf16", 200, 22, 55, 56, 256, 1, 1, (0, 0), (2, 2), "canonical"),
+    ("i8", "i32", 256, 43, 40, 40, 128, 3, 3, (1, 1), (2, 2), "tiled"),
+]
+
+
+@pytest.mark.parametrize("case", SPARSE)
+def test_sparse_products(case):
+    dtype, out, M, N, K, layout = case
+    run_mm_case(dtype, out, M, N, K, layout=layout, b_order="k", sparse=True, seed=81)
+    run_mm_case(dtype, out, M, N // 16 * 16, K, layout=layout, b_order="n", sparse=True, seed=82)
+
+
+@pytest.mark.parametrize("case", DENSE)
+def test_dense_products(case):
+    dtype, out, M, N, K = case
+    run_mm_case(dtype, out, M, N, K, layout=None, b_order="k", sparse=False, seed=83)
+    run_mm_case(dtype, out, M, N // 16 * 16, K, layout=None, b_order="n", sparse=False, seed=84)
+
+
+@pytest.mark.parametrize("case", CONVS)
+@pytest.mark.parametrize("sparse", [True, False])
+def test_strided_convolutions(case, sparse):
+    run_conv_case(*case, sparse=sparse, seed=85)
