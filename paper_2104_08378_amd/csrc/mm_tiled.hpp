@@ -1109,22 +1109,33 @@ static sp24_status pick_tile_general(const MmArgs& a, hipStream_t st)
     const double cover_big = (double)(((a.M + 255) / 256) * 256) * (double)(((a.N + 255) / 256) * 256);
     const double cover_small = (double)(((a.M + 127) / 128) * 128) * (double)(((a.N + 127) / 128) * 128);
     if (big >= enough && cover_big <= 1.35 * cover_small) return run_pipe<DT, OUT, 4, 2, 2, 4, 3, 2, kProducts | kConvs>(a, st);
+    // At most 128 tiles of 128x128: twice as many of 128x64 (64x128), four wavefronts of 32x64 each.  A row of the compressed
+    // operand costs 80 bytes a step and a column 128, so the tall tile is the cheaper of the two (18.4 against 21.5 KB), and
+    // four wavefronts, one to a SIMD, issue a step's reads and transfers in half the time that two need: against 64x128
+    // on two wavefronts (dense, N > 128: 128x128), 16 shapes per type, K 512 / 1024 / 4096, times as fast: bf16 1.12 - 1.24 /
+    // 1.07 - 1.29 / 1.09 - 1.38 (2048 x 1024 x 4096 19.1 -> 16.8 us, from HBM 26.6 -> 21.4), int8 1.05 - 1.2 / 1.07 - 1.27 /
+    // 1.08 - 1.35; dense bf16 1.13 - 1.31 / 1.09 - 1.39 / 1.02 - 1.38, int8 1.07 - 1.23 / 1.1 - 1.3 / 1.04 - 1.51.
+    //  * An 8-bit N-major B, whose rows would be half a cache line in 64 columns: 64x128 (from HBM, K = 4096: 1.06 - 1.27 times
+    //    as fast as before, the tall tile 0.81 - 1.08).
+    //  * A canonical operand, whose 64 bytes of a row are half a line too: 64x128 (8-bit 1.01 - 1.23, 16-bit N-major 0.94 - 1.18;
+    //    the tall tile 0.58 - 1.2).  16-bit K-major ones stay on two wavefronts (four: 1.05 - 1.14 at K = 544, but 0.84 - 0.93 where
+    //    rows are a power of two).
+    //  * N <= 64: tiles of 64x64, two wavefronts (128x64 0.74 - 0.99 times as fast), which do not fetch rows of B that do not
+    //    exist (sparse 28 - 31 % ahead of 64x128, 8192 x 64 x 8192 bf16: 43.8 -> 31.5 us).
+    // (Not for a product already split along K, whose slices fill the chip; not for convolutions, where the gather of
+    // B is the cost and doubles with it: strided 3x3 layers with 13 - 98 tiles were 20 - 30 % slower.)
+    if (small <= 128 && !a.conv.on && a.k_slices <= 1) {
+        const bool canonical = a.sparse && a.layout == SP24_LAYOUT_CANONICAL, nmajor = a.bo == SP24_B_NMAJOR;
+        if (a.N <= 64) return run_pipe<DT, OUT, 2, 1, 1, 2, 9, 9, kProducts>(a, st);
+        if constexpr (!is8<DT>) {
+            if (canonical && !nmajor) return run_pipe<DT, OUT, 2, 1, 1, 4, 7, 0, kSparse>(a, st);
+        }
+        if (canonical || (is8<DT> && nmajor)) return run_pipe<DT, OUT, 2, 2, 1, 2, 7, 6, kProducts>(a, st);
+        return run_pipe<DT, OUT, 4, 1, 1, 2, 8, 6, kProducts>(a, st);
+    }
     // 128x128 tiles, four wavefronts.  With few tiles one workgroup per compute unit is all there is, and a short
     // step (a quarter of the large tile's arithmetic) hides little latency: six (dense: four) stages, transfers
     // five (three) steps ahead.  With many tiles three (two) stages leave room for two workgroups per compute unit.
-    // At most 128 of them: tiles of 64 rows, two wavefronts, put twice as many compute units to work.  Such a product
-    // is bound by what one unit can keep in flight (its LDS ring against the latency of the L2 and of HBM), not
-    // by arithmetic; the smaller stages also allow a deeper ring, and with N <= 64 a 64-column tile does not fetch
-    // B rows that do not exist.  Measured on 16 shapes per type, operands from HBM: the sparse product 28 - 31 %
-    // faster at N <= 64 (8192 x 64 x 8192 bf16: 43.8 -> 31.5 us), 6 - 17 % at N = 96 .. 128, 5 - 14 % on small
-    // squarish shapes; the dense one 23 - 34 % and 15 - 25 % in a single column of tiles, but 10 - 15 % (16-bit)
-    // slower with several, where halving the rows doubles the traffic of B: it keeps 128 rows there.
-    // (Not for a product already split along K, whose slices fill the chip; not for convolutions, where the gather of
-    // B is the cost and doubles with it: strided 3x3 layers with 13 - 98 tiles were 20 - 30 % slower.)
-    if (small <= 128 && !a.conv.on && a.k_slices <= 1 && (a.sparse || a.N <= 128)) {
-        if (a.N <= 64) return run_pipe<DT, OUT, 2, 1, 1, 2, 9, 9, kProducts>(a, st);
-        return run_pipe<DT, OUT, 2, 1, 1, 4, 7, 6, kProducts>(a, st);
-    }
     if (small <= 256) return run_pipe<DT, OUT, 2, 2, 2, 2, 6, 4, kProducts | kConvs>(a, st);
     return run_pipe<DT, OUT, 2, 2, 2, 2, 3, 2, kProducts | kConvs>(a, st);
 }

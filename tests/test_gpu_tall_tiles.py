@@ -1,5 +1,6 @@
 """GPU parity of the tiled products on tiles of 192 and 256 rows by 128 columns (the criteria of test_gpu_parity.py and
-test_gpu_conv.py): more than 256 tiles of 128 x 128 and at most 256 of these."""
+test_gpu_conv.py): more than 256 tiles of 128 x 128 and at most 256 of these; and, at most 128 tiles of 128 x 128, on tiles of
+128 x 64 and 64 x 128 with four wavefronts."""
 import pytest
 
 from test_gpu_conv import run_case as run_conv_case
@@ -51,3 +52,27 @@ def test_dense_products(case):
 @pytest.mark.parametrize("sparse", [True, False])
 def test_strided_convolutions(case, sparse):
     run_conv_case(*case, sparse=sparse, seed=85)
+
+
+# 128 x 64 (a canonical or 8-bit N-major operand: 64 x 128): a step, as many as the ring holds, one and several more, a partial
+# one alone and behind others; one row, a row and a column past a tile
+FEW = [
+    ("bf16", "bf16", 1, 601, 64, "canonical"),
+    ("f16", "f32", 129, 577, 512, "canonical"),
+    ("i8", "i32", 160, 515, 1024, "tiled"),
+    ("bf16", "f32", 288, 530, 576, "tiled"),
+    ("i8", "i32", 129, 700, 1184, "canonical"),
+    ("f16", "f16", 96, 1000, 1152, "tiled"),
+    ("i8", "i32", 416, 641, 32, "canonical"),
+    ("bf16", "bf16", 65, 650, 1568, "canonical"),
+    ("i8", "i32", 64, 515, 1216, "tiled"),
+]
+
+
+@pytest.mark.parametrize("case", FEW)
+def test_few_tiles(case):
+    dtype, out, M, N, K, layout = case
+    for n, b_order in ((N, "k"), (N // 16 * 16, "n")):
+        run_mm_case(dtype, out, M, n, K, layout=layout, b_order=b_order, sparse=True, seed=86)
+        run_mm_case(dtype, out, M, n, K, layout=None, b_order=b_order, sparse=False, seed=87)
+    run_mm_case(dtype, out, M, 80, K, layout=layout, b_order="n", sparse=True, seed=88)
