@@ -1133,10 +1133,19 @@ static sp24_status pick_tile_general(const MmArgs& a, hipStream_t st)
         if (canonical || (is8<DT> && nmajor)) return run_pipe<DT, OUT, 2, 2, 1, 2, 7, 6, kProducts>(a, st);
         return run_pipe<DT, OUT, 4, 1, 1, 2, 8, 6, kProducts>(a, st);
     }
-    // 128x128 tiles, four wavefronts.  With few tiles one workgroup per compute unit is all there is, and a short
-    // step (a quarter of the large tile's arithmetic) hides little latency: six (dense: four) stages, transfers
-    // five (three) steps ahead.  With many tiles three (two) stages leave room for two workgroups per compute unit.
-    if (small <= 256) return run_pipe<DT, OUT, 2, 2, 2, 2, 6, 4, kProducts | kConvs>(a, st);
+    // 128x128 tiles.  With at most 256 one workgroup per compute unit is all there is: six (dense: four) stages, transfers five
+    // (three) steps ahead.  The dense product and the convolutions, whose steps are the longer to issue (twice the bytes of A;
+    // the gather of B), run on eight wavefronts of 32x64, two to a SIMD: against four of 64x64, times as fast, dense bf16 1.0 -
+    // 1.19 (2048 x 2048 x 1024 13.7 -> 13.0 us), int8 0.96 - 1.18, strided and 5x5 convolutions, sparse 1.03 - 1.14 (256 -> 256
+    // channels, 28x28, stride 2, 64 images f16 17.9 -> 17.2 us), dense 1.04 - 1.18 (20.4 -> 19.1).  The sparse product, whose A
+    // is read twice as often from LDS with half the rows to a wavefront, is level with eight (0.92 - 1.1), and an 8-bit
+    // dense one with an N-major B 3 - 6 % slower.
+    if (small <= 256) {
+        if (a.sparse && !a.conv.on) return run_pipe<DT, OUT, 2, 2, 2, 2, 6, 0, kSparse>(a, st);
+        if (!a.sparse && is8<DT> && a.bo == SP24_B_NMAJOR) return run_pipe<DT, OUT, 2, 2, 2, 2, 0, 4, kDense>(a, st);
+        return run_pipe<DT, OUT, 4, 2, 1, 2, 6, 4, kDense | kConvs>(a, st);
+    }
+    // more of them: three (two) stages leave room for two workgroups per compute unit
     return run_pipe<DT, OUT, 2, 2, 2, 2, 3, 2, kProducts | kConvs>(a, st);
 }
 

@@ -1,6 +1,6 @@
 """GPU parity of the tiled products on tiles of 192 and 256 rows by 128 columns (the criteria of test_gpu_parity.py and
 test_gpu_conv.py): more than 256 tiles of 128 x 128 and at most 256 of these; and, at most 128 tiles of 128 x 128, on tiles of
-128 x 64 and 64 x 128 with four wavefronts."""
+128 x 64 and 64 x 128 with four wavefronts, and the dense ones and the convolutions on 128 x 128 with eight."""
 import pytest
 
 from test_gpu_conv import run_case as run_conv_case
@@ -76,3 +76,30 @@ def test_few_tiles(case):
         run_mm_case(dtype, out, M, n, K, layout=layout, b_order=b_order, sparse=True, seed=86)
         run_mm_case(dtype, out, M, n, K, layout=None, b_order=b_order, sparse=False, seed=87)
     run_mm_case(dtype, out, M, 80, K, layout=layout, b_order="n", sparse=True, seed=88)
+
+
+# 129 - 256 tiles of 128 x 128 (N-major: 16-bit types; 8-bit ones on four wavefronts): no whole step, one, as many as the ring
+# holds, more, partial ones behind them
+EIGHT_DENSE = [
+    ("bf16", "f32", 1450, 1411, 32),
+    ("f16", "f16", 1409, 1410, 96),
+    ("i8", "i32", 1440, 1500, 512),
+    ("bf16", "bf16", 2000, 1281, 352),
+]
+EIGHT_CONVS = [
+    ("f16", "f32", 130, 13, 20, 32, 64, 5, 1, (2, 0), (1, 1), "canonical"),
+    ("i8", "i32", 96, 43, 40, 40, 128, 3, 3, (1, 1), (2, 2), "tiled"),
+]
+
+
+@pytest.mark.parametrize("case", EIGHT_DENSE)
+def test_dense_products_on_eight_wavefronts(case):
+    dtype, out, M, N, K = case
+    run_mm_case(dtype, out, M, N, K, layout=None, b_order="k", sparse=False, seed=89)
+    run_mm_case(dtype, out, M, N // 16 * 16, K, layout=None, b_order="n", sparse=False, seed=90)
+
+
+@pytest.mark.parametrize("case", EIGHT_CONVS)
+@pytest.mark.parametrize("sparse", [True, False])
+def test_convolutions_on_eight_wavefronts(case, sparse):
+    run_conv_case(*case, sparse=sparse, seed=91)
