@@ -1122,16 +1122,19 @@ static sp24_status pick_tile_general(const MmArgs& a, hipStream_t st)
     //    rows are a power of two).
     //  * N <= 64: tiles of 64x64, two wavefronts (128x64 0.74 - 0.99 times as fast), which do not fetch rows of B that do not
     //    exist (sparse 28 - 31 % ahead of 64x128, 8192 x 64 x 8192 bf16: 43.8 -> 31.5 us).
-    // (Not for a product already split along K, whose slices fill the chip; not for convolutions, where the gather of
-    // B is the cost and doubles with it: strided 3x3 layers with 13 - 98 tiles were 20 - 30 % slower.)
-    if (small <= 128 && !a.conv.on && a.k_slices <= 1) {
+    //  * Convolutions: 128x64 throughout, which leaves the gather of B per product as it is (against 128x128 on eight wavefronts
+    //    1.06 - 1.31 times as fast: 512 channels, 14x14, 3x3, stride 2, 32 images f16 24.6 -> 18.9 us, dense 26.6 -> 21.6; tiles of
+    //    64 rows, which double it, had been 20 - 30 % slower than 128).
+    // (Not for a product already split along K, whose slices fill the chip.)
+    if (small <= 128 && a.conv.on) return run_pipe<DT, OUT, 4, 1, 1, 2, 8, 6, kProducts | kConvs>(a, st);
+    if (small <= 128 && a.k_slices <= 1) {
         const bool canonical = a.sparse && a.layout == SP24_LAYOUT_CANONICAL, nmajor = a.bo == SP24_B_NMAJOR;
         if (a.N <= 64) return run_pipe<DT, OUT, 2, 1, 1, 2, 9, 9, kProducts>(a, st);
         if constexpr (!is8<DT>) {
             if (canonical && !nmajor) return run_pipe<DT, OUT, 2, 1, 1, 4, 7, 0, kSparse>(a, st);
         }
         if (canonical || (is8<DT> && nmajor)) return run_pipe<DT, OUT, 2, 2, 1, 2, 7, 6, kProducts>(a, st);
-        return run_pipe<DT, OUT, 4, 1, 1, 2, 8, 6, kProducts>(a, st);
+        return run_pipe<DT, OUT, 4, 1, 1, 2, 8, 6, kProducts | kConvs>(a, st);
     }
     // 128x128 tiles.  With at most 256 one workgroup per compute unit is all there is: six (dense: four) stages, transfers five
     // (three) steps ahead.  The dense product and the convolutions, whose steps are the longer to issue (twice the bytes of A;

@@ -103,3 +103,17 @@ def test_dense_products_on_eight_wavefronts(case):
 @pytest.mark.parametrize("sparse", [True, False])
 def test_convolutions_on_eight_wavefronts(case, sparse):
     run_conv_case(*case, sparse=sparse, seed=91)
+
+
+# few tiles of 128 x 64: fewer steps than the ring holds and more, ragged rows and pixels, padding
+FEW_CONVS = [
+    ("f16", "f32", 130, 3, 20, 13, 64, 3, 3, (1, 1), (2, 1), "canonical"),
+    ("i8", "i32", 96, 5, 11, 12, 128, 5, 1, (2, 0), (1, 1), "tiled"),
+    ("bf16", "bf16", 257, 2, 9, 8, 192, 1, 1, (0, 0), (2, 2), "canonical"),
+]
+
+
+@pytest.mark.parametrize("case", FEW_CONVS)
+@pytest.mark.parametrize("sparse", [True, False])
+def test_convolutions_on_few_tiles(case, sparse):
+    run_conv_case(*case, sparse=sparse, seed=92)
