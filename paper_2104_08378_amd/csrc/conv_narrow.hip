@@ -7,14 +7,17 @@
 // Such layers have few filters and large images: a tile is 64 filters x 128 pixels (a 128-row tile would be half
 // padding), four wavefronts of 32 x 64.  With one chunk, nine steps of two instructions are all the arithmetic a
 // wavefront has; the time is the latency of one patch in and one tile out, so what counts is how many workgroups
-// share a compute unit: four with the 192-pixel patch, three with the 256-pixel one.  A of a whole chunk (nine steps, 45
-// registers) is loaded ahead of the barrier, under the patch's own latency.
-// (Four workgroups mean 128 registers: the 192-pixel instances that need more keep 20 bytes a lane, int8 to int8, or 24 - 84,
-// 8-bit floats, in scratch memory.)
+// share a compute unit.  A of a whole chunk (nine steps, 45 registers) is loaded ahead of the barrier, under the patch's own
+// latency.  ONE: inputs with one chunk, which need one patch buffer and no registers for a next one: four workgroups to a
+// unit with either size of patch, where two buffers of 256 pixels leave room for three (56 x 56, 64 -> 64, 32 images, int8: 784
+// tiles on 768 places took 11.2 us, 8.7 on 1024; one image 5.0 -> 4.5, 28 x 28, 64 -> 128, 64 images 8.5 -> 8.2; 8-bit floats 7 -
+// 29 % faster throughout).  With several chunks four with the 192-pixel patch, three with the 256-pixel one.
+// (Four workgroups mean 128 registers: the 192-pixel instances for several chunks that need more keep 20 bytes a lane, int8
+// to int8, or 24 - 84, 8-bit floats, in scratch memory.)
 // Patch rows are 80 bytes apart: sixteen consecutive rows fall into sixteen different 16-byte columns of LDS.
 //
 // Measured with the quantised epilogue to int8, against the general kernel that took these layers before (us, operands
-// rotating): 56 x 56, 64 -> 64 channels, 32 images 188 -> 11.1; 28 x 28, 64 -> 128, 32 images 107 -> 9.8; 14 x 14,
+// rotating): 56 x 56, 64 -> 64 channels, 32 images 188 -> 8.7; 28 x 28, 64 -> 128, 32 images 107 -> 9.8; 14 x 14,
 // 192 -> 192, 64 images 183 -> 10.5.  (Below 10 us it is the rate of the calls that is measured.)
 #include "conv_patch.hpp"
 
@@ -22,8 +25,8 @@ namespace sp24 {
 
 constexpr int kNarrowPitch = 80;
 
-template <int DT, int OUT, int kPatchRows>
-__global__ __launch_bounds__(256, kPatchRows <= kPatchRowsSmall ? 4 : 3) void k_conv_patch_narrow(MmArgs a, int tiles_m, int tiles_n)
+template <int DT, int OUT, int kPatchRows, bool ONE>
+__global__ __launch_bounds__(256, ONE || kPatchRows <= kPatchRowsSmall ? 4 : 3) void k_conv_patch_narrow(MmArgs a, int tiles_m, int tiles_n)
 {
     static_assert(is8<DT>, "a step is one instruction of 64 one-byte columns");
     constexpr int CB = 64;                             // channels (bytes) of a chunk
@@ -32,7 +35,8 @@ __global__ __launch_bounds__(256, kPatchRows <= kPatchRowsSmall ? 4 : 3) void k_
     constexpr int XP = kPatchRows * (CB / 16) / 256;   // 16-byte pieces of a patch per lane
     constexpr int kPatchBytes = (kPatchRows + 1) * kPitch, kZeroOff = kPatchRows * kPitch;
     constexpr int kEpiBytes = 4 * epilogue_geometry<OUT, TN>::kWaveBytes;
-    constexpr int kLdsBytes = 2 * kPatchBytes > kEpiBytes ? 2 * kPatchBytes : kEpiBytes;
+    constexpr int kBuffers = ONE ? 1 : 2;
+    constexpr int kLdsBytes = kBuffers * kPatchBytes > kEpiBytes ? kBuffers * kPatchBytes : kEpiBytes;
     using acc_t = typename acc_of<DT>::type;
     __shared__ __attribute__((aligned(1024))) uint8_t lds_all[kLdsBytes];
 
@@ -43,7 +47,7 @@ __global__ __launch_bounds__(256, kPatchRows <= kPatchRowsSmall ? 4 : 3) void k_
     const int wm = wave / WN, wn = wave % WN;
     const int r = lane & 31, q = lane >> 5;
     const ConvGeom g = a.conv;
-    const int nchunks = g.C / CB;
+    const int nchunks = ONE ? 1 : g.C / CB;
     const uint8_t* X = reinterpret_cast<const uint8_t*>(a.B);
     const int64_t n_pixels = (a.N / ((int64_t)g.OH * g.OW)) * g.H * g.W;      // input pixels in all images
 
@@ -121,7 +125,7 @@ __global__ __launch_bounds__(256, kPatchRows <= kPatchRowsSmall ? 4 : 3) void k_
 #pragma unroll
     for (int nj = 0; nj < TN; ++nj) acc[0][nj] = acc_t{};
 
-    if (tid < 2 * (kPitch / 4)) reinterpret_cast<uint32_t*>(lds_all + kZeroOff + (tid / (kPitch / 4)) * kPatchBytes)[tid % (kPitch / 4)] = 0u;
+    if (tid < kBuffers * (kPitch / 4)) reinterpret_cast<uint32_t*>(lds_all + kZeroOff + (tid / (kPitch / 4)) * kPatchBytes)[tid % (kPitch / 4)] = 0u;
     store_patch(0);
     if (nchunks > 1) load_patch(1);
     __syncthreads();
@@ -155,8 +159,10 @@ static sp24_status run_narrow(const MmArgs& a, hipStream_t st)
 {
     const int tiles_m = (int)((a.M + 63) / 64), tiles_n = (int)((a.N + 127) / 128);
     const dim3 grid((unsigned)(tiles_m * tiles_n)), block(256);
-    if (conv_patch_span(a) <= kPatchRowsSmall) k_conv_patch_narrow<DT, OUT, kPatchRowsSmall><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
-    else k_conv_patch_narrow<DT, OUT, kPatchRowsLarge><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
+    auto run = [&](auto kernel) { kernel<<<grid, block, 0, st>>>(a, tiles_m, tiles_n); };
+    const bool small = conv_patch_span(a) <= kPatchRowsSmall;
+    if (a.conv.C == 64) small ? run(k_conv_patch_narrow<DT, OUT, kPatchRowsSmall, true>) : run(k_conv_patch_narrow<DT, OUT, kPatchRowsLarge, true>);
+    else small ? run(k_conv_patch_narrow<DT, OUT, kPatchRowsSmall, false>) : run(k_conv_patch_narrow<DT, OUT, kPatchRowsLarge, false>);
     return hipGetLastError() == hipSuccess ? SP24_OK : SP24_ERR_LAUNCH;
 }
 
