@@ -2,7 +2,7 @@
 // straight into registers (Sec. 3.2: convolutions are GEMM-like with the sparse tensor first; Sec. 4.2: inner
 // dimension C x R x S; Sec. 3.1: the compressed operand needs no indirection and is read with full-width accesses).
 //
-// The kernel was written for outputs with too few tiles for the 256 x 256 shape: 128 x 128 tiles, one workgroup of
+// The kernel was written for outputs with too few tiles for the 256 x 256 shape: 128 x 128 tiles (smaller ones came later), one workgroup of
 // four wavefronts per compute unit, i.e. ONE wavefront per SIMD (it serves larger outputs too: it turned out no
 // slower per product than the 256 x 256 kernels).  A lone wavefront issues at most one instruction every
 // four clocks, and the 8 matrix instructions of a step (16-bit inputs) occupy the matrix core for 256 clocks: a
@@ -16,7 +16,7 @@
 //     one short run of the NHWC input: output pixel n = (img, oy, ox) meets, for tap (r, s), the input pixel with
 //     linear index lin0(n) + r*W + s, lin0(n) = (img*H + oy - pad_h)*W + ox - pad_w, and lin0 grows with n when
 //     the output is no larger than the input.  Per chunk of channels (one 128-byte step of K) that run -- the
-//     patch, at most 192 or 256 pixels x 128 bytes -- is put into LDS once per chunk, and every tap reads its B
+//     patch, at most 128 to 256 pixels x 128 bytes -- is put into LDS once per chunk, and every tap reads its B
 //     fragments from it at a row offset of r*W + s.  Rows are 144 bytes apart, which keeps 16-byte reads of
 //     consecutive rows on distinct banks without an address swizzle, so the 8 fragments of a step sit at
 //     immediate offsets from one row address per output pixel; taps in the padding read a row of zeros;
@@ -40,7 +40,7 @@
 
 namespace sp24 {
 
-constexpr int kPatchRowsSmall = 192, kPatchRowsLarge = 256;   // pixels a patch holds: two sizes of the kernel
+constexpr int kPatchRowsTiny = 128, kPatchRowsSmall = 192, kPatchRowsLarge = 256;   // pixels a patch holds: the kernel's sizes
 constexpr int kPatchPitch = 144;                   // bytes from one patch row to the next in LDS
 
 // f(integral_constant<int, I>) for every I of the sequence, in order: a loop whose index is a constant in its body
@@ -50,42 +50,45 @@ __device__ __forceinline__ void for_each_index(std::integer_sequence<int, I...>,
     (f(std::integral_constant<int, I>{}), ...);
 }
 
-// The pixels a tile's patch may span if the patch kernel can take this convolution, else 0.  (The caller has checked
-// what the tiled kernels need.)
-inline int64_t conv_patch_span(const MmArgs& a)
+// The pixels that the patch of a tile of `pixels` outputs may span if the patch kernel can take this convolution, else 0.
+// (The caller has checked what the tiled kernels need.)
+inline int64_t conv_patch_span(const MmArgs& a, int pixels = 128)
 {
     const ConvGeom& g = a.conv;
     if (!g.on || !a.sparse || a.layout != SP24_LAYOUT_TILED) return 0;
     if (g.R != 3 || g.S != 3 || g.stride_h != 1 || g.stride_w != 1 || g.OH > g.H || g.OW > g.W) return 0;
     // the compressed rows of one wavefront's two row blocks, as a buffer load's 32-bit offset
     if (a.K * 64 >= (int64_t)1 << 31) return 0;
-    // rows a tile's patch spans at most: 128 consecutive output pixels, the extra input pixels at every change of
+    // rows a tile's patch spans at most: that many consecutive output pixels, the extra input pixels at every change of
     // output row and image among them, and the reach of the filter
-    const int64_t row_changes = 127 / g.OW + 1, img_changes = 127 / ((int64_t)g.OH * g.OW) + 1;
-    const int64_t span = 128 + row_changes * (g.W - g.OW) + img_changes * (int64_t)(g.H - g.OH) * g.W + (int64_t)(g.R - 1) * g.W + g.S - 1;
+    const int64_t row_changes = (pixels - 1) / g.OW + 1, img_changes = (pixels - 1) / ((int64_t)g.OH * g.OW) + 1;
+    const int64_t span = pixels + row_changes * (g.W - g.OW) + img_changes * (int64_t)(g.H - g.OH) * g.W + (int64_t)(g.R - 1) * g.W + g.S - 1;
     return span <= kPatchRowsLarge ? span : 0;
 }
 
-template <int DT, int OUT, int kPatchRows>
-__global__ __launch_bounds__(256, kPatchRows <= kPatchRowsSmall ? 2 : 1) void k_conv_patch(MmArgs a, int tiles_m, int tiles_n)
+// TM, TN: row blocks and 32-pixel blocks of each of the 2 x 2 wavefronts.  ONE: the input has one chunk of channels: one
+// buffer, and nothing is loaded for a next chunk.
+template <int DT, int OUT, int kPatchRows, int TM, int TN, bool ONE>
+__global__ __launch_bounds__(256, TM * TN == 1 && ONE ? 4 : TM * TN == 2 && ONE ? 3 : kPatchRows <= kPatchRowsSmall ? 2 : 1) void k_conv_patch(MmArgs a, int tiles_m, int tiles_n)
 {
     constexpr int ES = is8<DT> ? 1 : 2;
     constexpr int BK = kRowBytes / ES;                 // K elements (channels) per step
     constexpr int T64 = BK / 64;
-    constexpr int WN = 2, TM = 2, TN = 2, BM = 128, BN = 128, RB = BM / 32;
+    constexpr int WN = 2, BM = 64 * TM, BN = 64 * TN, RB = BM / 32;
     constexpr int NF = 2 * TN;                         // B fragments of a step: instruction j = f / TN, block nj = f % TN
     constexpr int XP = kPatchRows / 8 / 4;             // 1 KiB parts (8 pixels) of a patch per wavefront
     constexpr int kLoadsA = TM * (is8<DT> ? 4 : 3);    // loads of a step's A per wavefront: values twice, codes once (twice for 8-bit)
     constexpr int TAPS = 9, PF = 3;                    // PF: steps of A in registers, the one in use and two ahead; divides TAPS
     constexpr int kPitch = kPatchPitch;
     // LDS: two buffers, each the patch's rows and behind them a row of zeros: a row address is formed for buffer 0
-    // and reaches buffer 1 by an immediate offset, whichever row it is.  55 KiB with the smaller patch, so that two
-    // workgroups share a compute unit where the grid has them; 74 KiB with the larger
+    // and reaches buffer 1 by an immediate offset, whichever row it is.  55 KiB with patches of 192 pixels, so that two
+    // workgroups share a compute unit where the grid has them; 74 KiB with 256 (one buffer: half of that, 2 - 7 % faster on
+    // 128 x 128 tiles, with patches of 256 pixels and 8-bit inputs 43 - 48 %)
     constexpr int kPatchBytes = (kPatchRows + 1) * kPitch;
     constexpr int kZeroOff = kPatchRows * kPitch;
-    constexpr int kLdsBytes = 2 * kPatchBytes;
+    constexpr int kBuffers = ONE ? 1 : 2, kEpiBytes = 4 * epilogue_geometry<OUT, TN>::kWaveBytes;
+    constexpr int kLdsBytes = kBuffers * kPatchBytes > kEpiBytes ? kBuffers * kPatchBytes : kEpiBytes;
     using acc_t = typename acc_of<DT>::type;
-    static_assert(4 * epilogue_geometry<OUT, TN>::kWaveBytes <= kLdsBytes, "store scratch");
     static_assert(kPatchBytes + 96 + 16 <= 65536 && kLdsBytes <= 160 * 1024, "the second buffer and a fragment's place in a row as a 16-bit immediate");
     __shared__ __attribute__((aligned(1024))) uint8_t lds_all[kLdsBytes];
 
@@ -96,7 +99,7 @@ __global__ __launch_bounds__(256, kPatchRows <= kPatchRowsSmall ? 2 : 1) void k_
     const int wm = wave / WN, wn = wave % WN;
     const int r = lane & 31, q = lane >> 5;
     const ConvGeom g = a.conv;
-    const int nchunks = g.C / BK;
+    const int nchunks = ONE ? 1 : g.C / BK;
     const uint8_t* X = reinterpret_cast<const uint8_t*>(a.B);
     const int64_t pixel_bytes = (int64_t)g.C * ES;
     const int64_t n_pixels = (a.N / ((int64_t)g.OH * g.OW)) * g.H * g.W;      // input pixels in all images
@@ -188,7 +191,7 @@ __global__ __launch_bounds__(256, kPatchRows <= kPatchRowsSmall ? 2 : 1) void k_
     if (rb0 >= rb_total) rb0 = rb_total - 1;            // ragged M: a valid row block, never stored
     const uint8_t* v_base = reinterpret_cast<const uint8_t*>(a.A) + rb0 * KB64 * (1024 * ES);
     const uint8_t* m_base = reinterpret_cast<const uint8_t*>(a.meta) + rb0 * KB64 * 256;
-    const int rbs = rb0 + 1 < rb_total ? 2 : 1;         // row blocks from rb0 on that exist
+    const int rbs = TM > 1 && rb0 + 1 < rb_total ? 2 : 1;    // row blocks from rb0 on that exist
     const __amdgpu_buffer_rsrc_t v_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(wave_uniform(v_base)), 0, __builtin_amdgcn_readfirstlane((int)(rbs * KB64 * (1024 * ES))), 0x00020000);
     const __amdgpu_buffer_rsrc_t m_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(wave_uniform(m_base)), 0, __builtin_amdgcn_readfirstlane((int)(rbs * KB64 * 256)), 0x00020000);
     int v_off[TM], m_off[TM];
@@ -215,11 +218,11 @@ __global__ __launch_bounds__(256, kPatchRows <= kPatchRowsSmall ? 2 : 1) void k_
         for (int j = 0; j < TN; ++j) acc[i][j] = acc_t{};
 
     // ---- prologue: the row of zeros, the first patch, the second patch in flight, A of steps 0 and 1, B of step 0 ----
-    if (tid < 2 * (kPitch / 4)) reinterpret_cast<uint32_t*>(lds_all + kZeroOff + (tid / (kPitch / 4)) * kPatchBytes)[tid % (kPitch / 4)] = 0u;
+    if (tid < kBuffers * (kPitch / 4)) reinterpret_cast<uint32_t*>(lds_all + kZeroOff + (tid / (kPitch / 4)) * kPatchBytes)[tid % (kPitch / 4)] = 0u;
     Patch pp;
     load_patch(0, pp);
     store_patch(pp, 0);
-    load_patch(nchunks > 1 ? 1 : 0, pp);
+    if constexpr (!ONE) load_patch(nchunks > 1 ? 1 : 0, pp);
     AOps ao[PF];
 #pragma unroll
     for (int u = 0; u < PF - 1; ++u) load_a(u * nchunks, ao[u]);              // steps (tap u, chunk 0)
@@ -235,27 +238,27 @@ __global__ __launch_bounds__(256, kPatchRows <= kPatchRowsSmall ? 2 : 1) void k_
         constexpr int PAR = decltype(par_c)::value;
         for_each_index(std::make_integer_sequence<int, TAPS>{}, [&](auto t_c) {
             constexpr int t = decltype(t_c)::value;
-            if (t == 0) {
+            if (!ONE && t == 0) {
                 // the patch of chunk c + 1 goes into the buffer chunk c - 1 used: everybody passed the barrier in that
                 // chunk's last step, after its last reads
                 store_patch(pp, PAR ^ 1);
             }
-            if (t == 6) load_patch(c + 2 < nchunks ? c + 2 : nchunks - 1, pp);
-            if (t == TAPS - 1) {
+            if (!ONE && t == 6) load_patch(c + 2 < nchunks ? c + 2 : nchunks - 1, pp);
+            if (!ONE && t == TAPS - 1) {
                 // the next step's fragments come from the patch of chunk c + 1, written by all wavefronts in this
                 // chunk's first step; and whoever passes here has finished the reads of this chunk's earlier steps
                 __builtin_amdgcn_s_waitcnt(waitcnt_vm(63) & ~(15 << 8));
                 __builtin_amdgcn_s_barrier();
             }
             __builtin_amdgcn_sched_barrier(0);
-            {
+            if constexpr (!ONE || t + PF - 1 < TAPS) {
                 // A of the step two ahead, (tap, chunk) = (t + 2, c) or (t + 2 - 9, c + 1); past the last chunk that is
                 // a step of the matrix all the same (tap 0 or 1 of "chunk nchunks" is K step nchunks or 2*nchunks), unused
                 constexpr int t2 = (t + PF - 1) % TAPS;
                 const int c2 = t + PF - 1 < TAPS ? c : c + 1;
                 load_a(t2 * nchunks + c2, ao[(t + PF - 1) % PF]);
             }
-            {
+            if constexpr (!ONE || t + 1 < TAPS) {
                 constexpr int t1 = (t + 1) % TAPS;
                 constexpr int buf1 = t + 1 < TAPS ? PAR : PAR ^ 1;
                 read_b(std::integral_constant<int, buf1>{}, b_row[t1], bo[(9 * PAR + t + 1) & 1]);
@@ -277,13 +280,17 @@ __global__ __launch_bounds__(256, kPatchRows <= kPatchRowsSmall ? 2 : 1) void k_
 #pragma unroll
             for (int k = 0; k < NF * TM; ++k) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);               // one matrix instruction
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);               // one LDS read
-                if (k < kLoadsA) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // one load
+                if (!ONE || t + 1 < TAPS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);    // one LDS read
+                if (k < kLoadsA && (!ONE || t + PF - 1 < TAPS)) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // one load
             }
             __builtin_amdgcn_sched_barrier(0);
         });
     };
     int c = 0;
+    if constexpr (ONE) {
+        do_chunk(std::integral_constant<int, 0>{}, c);
+        c = nchunks;
+    }
     for (; c + 2 <= nchunks; c += 2) {
         do_chunk(std::integral_constant<int, 0>{}, c);
         do_chunk(std::integral_constant<int, 1>{}, c + 1);
@@ -301,11 +308,32 @@ __global__ __launch_bounds__(256, kPatchRows <= kPatchRowsSmall ? 2 : 1) void k_
 template <int DT, int OUT>
 static sp24_status run_conv_patch(const MmArgs& a, hipStream_t st)
 {
-    const int tiles_m = (int)((a.M + 127) / 128), tiles_n = (int)((a.N + 127) / 128);
-    const dim3 grid((unsigned)(tiles_m * tiles_n)), block(256);
-    if (conv_patch_span(a) <= kPatchRowsSmall) k_conv_patch<DT, OUT, kPatchRowsSmall><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
-    else k_conv_patch<DT, OUT, kPatchRowsLarge><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
-    return hipGetLastError() == hipSuccess ? SP24_OK : SP24_ERR_LAUNCH;
+    auto run = [&](auto kernel, int bm, int bn) {
+        const int tiles_m = (int)((a.M + bm - 1) / bm), tiles_n = (int)((a.N + bn - 1) / bn);
+        kernel<<<dim3((unsigned)(tiles_m * tiles_n)), dim3(256), 0, st>>>(a, tiles_m, tiles_n);
+        return hipGetLastError() == hipSuccess ? SP24_OK : SP24_ERR_LAUNCH;
+    };
+    // The time of a tile is its steps, whose length goes with the bytes of A that a unit brings in and with its matrix
+    // instructions, and 5 us around them: smaller tiles while every one finds a unit.  Against 128 x 128, times as fast: 64 x 64
+    // on up to 256 tiles 1.28 - 1.66 (14 x 14, 256 -> 256, 8 images f16 10.5 -> 6.5 us, int8 8.5 -> 5.4; 7 x 7, 512 -> 512, 32
+    // images f16 19.4 -> 15.0), 64 x 128 where those are at most 256 1.12 - 1.43 (256 channels, 14 x 14, 32 images 11.0 -> 9.0).  Past
+    // that a unit with two of them takes as long as with one of 128 x 128, or longer (0.76 - 1.0) -- except for up to 64
+    // filters, half of such a tile (56 x 56, 64 -> 64, 32 images f16 16.8 -> 9.9 us, 16 images 8.3 -> 6.3), and inputs with one chunk
+    // on more than 512 tiles of 128 x 128, of which three workgroups share a unit instead of two (28 x 28, 64 -> 128, 128
+    // images f16 17.1 -> 15.5, 128 -> 128 int8 20.1 -> 18.7; on 392 tiles 0.87 - 0.96).
+    const bool one = a.conv.C * esize_of(a.in) == kRowBytes, small = conv_patch_span(a) <= kPatchRowsSmall;
+    const int64_t blocks = (a.M + 63) / 64, cols = (a.N + 127) / 128;
+    if (blocks * ((a.N + 63) / 64) <= 256) {
+        const bool tiny = conv_patch_span(a, 64) <= kPatchRowsTiny;
+        if (one) return tiny ? run(k_conv_patch<DT, OUT, kPatchRowsTiny, 1, 1, true>, 64, 64) : run(k_conv_patch<DT, OUT, kPatchRowsSmall, 1, 1, true>, 64, 64);
+        return tiny ? run(k_conv_patch<DT, OUT, kPatchRowsTiny, 1, 1, false>, 64, 64) : run(k_conv_patch<DT, OUT, kPatchRowsSmall, 1, 1, false>, 64, 64);
+    }
+    if (a.M <= 64 || blocks * cols <= 256 || (one && ((a.M + 127) / 128) * cols > 512)) {
+        if (one) return small ? run(k_conv_patch<DT, OUT, kPatchRowsSmall, 1, 2, true>, 64, 128) : run(k_conv_patch<DT, OUT, kPatchRowsLarge, 1, 2, true>, 64, 128);
+        return small ? run(k_conv_patch<DT, OUT, kPatchRowsSmall, 1, 2, false>, 64, 128) : run(k_conv_patch<DT, OUT, kPatchRowsLarge, 1, 2, false>, 64, 128);
+    }
+    if (one) return small ? run(k_conv_patch<DT, OUT, kPatchRowsSmall, 2, 2, true>, 128, 128) : run(k_conv_patch<DT, OUT, kPatchRowsLarge, 2, 2, true>, 128, 128);
+    return small ? run(k_conv_patch<DT, OUT, kPatchRowsSmall, 2, 2, false>, 128, 128) : run(k_conv_patch<DT, OUT, kPatchRowsLarge, 2, 2, false>, 128, 128);
 }
 
 // The tiled kernel for a problem: the patch kernel for every sparse convolution it fits -- measured against the general
