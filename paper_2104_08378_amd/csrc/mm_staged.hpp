@@ -275,11 +275,16 @@ static sp24_status run_staged_from(const MmArgs& a, hipStream_t st)
         kernel<<<dim3((unsigned)(tiles_m * tiles_n)), dim3(256), 0, st>>>(a, tiles_m, tiles_n);
         return hipGetLastError() == hipSuccess ? SP24_OK : SP24_ERR_LAUNCH;
     };
-    // As many rows as there are; tiles of 64 rows also while the large ones would not give every compute unit one.  Two by two
-    // wavefronts also there: side by side (1 x 4), each would load the same rows of A again, and the address path is the
-    // bound (4096 x 509 x 4096 N-major bf16 34 -> 27 us, 4096 x 509 x 1024 12.8 -> 10.6).  From 256 tiles on the large ones
-    // are 20 - 50 % faster (4096 x 4095 x 4096: 185 -> 125), convolutions and 8-bit gathers within 15 % either way.
+    // The smallest tile whose workgroups find a unit each, 64 x 64 on up to 256 of them: against 64 x 128 (32 x 128 up to 32 rows),
+    // times as fast, convolutions 1.12 - 1.52 (96 -> 96 channels, 5x5, 4 images of 7x7 f16 24.5 -> 16.1 us, int8 15.4 -> 11.7), K a multiple of
+    // 16 1.15 - 1.43 (1024 x 509 x 1040 bf16 9.4 -> 7.1), N-major 1.18 - 1.22 (3000 x 301 x 4096 bf16 42.9 -> 35.1); on 392 of
+    // them 0.92 - 1.09, and 0.8 - 0.92 for products.  Past that as many rows as there are; tiles of 64 rows also while the large ones
+    // would not give every compute unit one.  Two by two wavefronts also there: side by side (1 x 4), each would load
+    // the same rows of A again, and the address path is the bound (4096 x 509 x 4096 N-major bf16 34 -> 27 us, 4096 x 509 x 1024
+    // 12.8 -> 10.6).  From 256 tiles on the large ones are 20 - 50 % faster (4096 x 4095 x 4096: 185 -> 125), convolutions and
+    // 8-bit gathers within 15 % either way.
     const int64_t large = ((a.M + 127) / 128) * ((a.N + 127) / 128);
+    if (((a.M + 63) / 64) * ((a.N + 63) / 64) <= 256) return run(k_spmm_staged<DT, BSRC, 2, 2, 1, 1>, 64, 64);
     if (a.M <= 32) return run(k_spmm_staged<DT, BSRC, 1, 4, 1, 1>, 32, 128);
     if (a.M <= 64 || large < 256) return run(k_spmm_staged<DT, BSRC, 2, 2, 1, 2>, 64, 128);
     return run(k_spmm_staged<DT, BSRC, 2, 2, 2, 2>, 128, 128);
