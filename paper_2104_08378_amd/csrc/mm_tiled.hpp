@@ -1138,15 +1138,18 @@ static sp24_status pick_tile_general(const MmArgs& a, hipStream_t st)
     }
     // 128x128 tiles.  With at most 256 one workgroup per compute unit is all there is: six (dense: four) stages, transfers five
     // (three) steps ahead.  The dense product and the convolutions, whose steps are the longer to issue (twice the bytes of A;
-    // the gather of B), run on eight wavefronts of 32x64, two to a SIMD: against four of 64x64, times as fast, dense bf16 1.0 -
-    // 1.19 (2048 x 2048 x 1024 13.7 -> 13.0 us), int8 0.96 - 1.18, strided and 5x5 convolutions, sparse 1.03 - 1.14 (256 -> 256
-    // channels, 28x28, stride 2, 64 images f16 17.9 -> 17.2 us), dense 1.04 - 1.18 (20.4 -> 19.1).  The sparse product, whose A
-    // is read twice as often from LDS with half the rows to a wavefront, is level with eight (0.92 - 1.1), and an 8-bit
-    // dense one with an N-major B 3 - 6 % slower.
+    // the gather of B), run on eight wavefronts of 32x64, two to a SIMD, while about two thirds of the chip take part: against four
+    // of 64x64, times as fast from the L2 / the last-level cache / HBM, dense bf16 on 132 - 176 tiles 1.01 - 1.16 / 0.99 -
+    // 1.09 / 1.01 - 1.08 (2048 x 1152 x 1024 9.9 -> 8.6 us), int8 on 132 - 160 1.02 - 1.13 / 1.03 - 1.08 / 1.01 - 1.09;
+    // convolutions (5x5, strided) on 154 - 210 tiles, sparse 0.99 - 1.08 (256 -> 256 channels, 28x28, stride 2, 55 images f16 17.4 -> 16.3 us), dense 1.0 -
+    // 1.12 (20.1 -> 18.2).  Beyond, eight wavefronts on nearly every unit run into what looks like the power limit: int8
+    // 2048 x 2048 x 1024 9.9 -> 16.5 us (on 176 tiles 8.1 -> 9.9 now and then), bf16 0.92 - 1.05, convolutions on 227 - 256 0.85 - 1.05.  The sparse
+    // product, whose A is read twice as often from LDS with half the rows to a wavefront, is level with eight (0.92 - 1.1), and an
+    // 8-bit dense one with an N-major B 3 - 6 % slower.
     if (small <= 256) {
-        if (a.sparse && !a.conv.on) return run_pipe<DT, OUT, 2, 2, 2, 2, 6, 0, kSparse>(a, st);
-        if (!a.sparse && is8<DT> && a.bo == SP24_B_NMAJOR) return run_pipe<DT, OUT, 2, 2, 2, 2, 0, 4, kDense>(a, st);
-        return run_pipe<DT, OUT, 4, 2, 1, 2, 6, 4, kDense | kConvs>(a, st);
+        const bool eight = a.conv.on ? small <= 210 : !a.sparse && (is8<DT> ? small <= 160 && a.bo != SP24_B_NMAJOR : small <= 176);
+        if (eight) return run_pipe<DT, OUT, 4, 2, 1, 2, 6, 4, kDense | kConvs>(a, st);
+        return run_pipe<DT, OUT, 2, 2, 2, 2, 6, 4, kProducts | kConvs>(a, st);
     }
     // more of them: three (two) stages leave room for two workgroups per compute unit
     return run_pipe<DT, OUT, 2, 2, 2, 2, 3, 2, kProducts | kConvs>(a, st);

@@ -78,8 +78,8 @@ def test_few_tiles(case):
     run_mm_case(dtype, out, M, 80, K, layout=layout, b_order="n", sparse=True, seed=88)
 
 
-# 129 - 256 tiles of 128 x 128 (N-major: 16-bit types; 8-bit ones on four wavefronts): no whole step, one, as many as the ring
-# holds, more, partial ones behind them
+# 129 - 176 tiles of 128 x 128 (8-bit types: to 160, N-major ones on four wavefronts; convolutions to 210): no whole step, one, as
+# many as the ring holds, more, partial ones behind them
 EIGHT_DENSE = [
     ("bf16", "f32", 1450, 1411, 32),
     ("f16", "f16", 1409, 1410, 96),
