@@ -1146,6 +1146,7 @@ static sp24_status pick_tile_general(const MmArgs& a, hipStream_t st)
     // 2048 x 2048 x 1024 9.9 -> 16.5 us (on 176 tiles 8.1 -> 9.9 now and then), bf16 0.92 - 1.05, convolutions on 227 - 256 0.85 - 1.05.  The sparse
     // product, whose A is read twice as often from LDS with half the rows to a wavefront, is level with eight (0.92 - 1.1), and an
     // 8-bit dense one with an N-major B 3 - 6 % slower.
+    // Dense products split along K, whose slices fill the chip with few tiles, are 0.98 - 1.1 times as fast with eight.
     if (small <= 256) {
         const bool eight = a.conv.on ? small <= 210 : !a.sparse && (is8<DT> ? small <= 160 && a.bo != SP24_B_NMAJOR : small <= 176);
         if (eight) return run_pipe<DT, OUT, 4, 2, 1, 2, 6, 4, kDense | kConvs>(a, st);
