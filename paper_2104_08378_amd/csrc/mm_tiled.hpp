@@ -1142,13 +1142,17 @@ static sp24_status pick_tile_general(const MmArgs& a, hipStream_t st)
     // of 64x64, times as fast from the L2 / the last-level cache / HBM, dense bf16 on 132 - 176 tiles 1.01 - 1.16 / 0.99 -
     // 1.09 / 1.01 - 1.08 (2048 x 1152 x 1024 9.9 -> 8.6 us), int8 on 132 - 160 1.02 - 1.13 / 1.03 - 1.08 / 1.01 - 1.09;
     // convolutions (5x5, strided) on 154 - 210 tiles, sparse 0.99 - 1.08 (256 -> 256 channels, 28x28, stride 2, 55 images f16 17.4 -> 16.3 us), dense 1.0 -
-    // 1.12 (20.1 -> 18.2).  Beyond, eight wavefronts on nearly every unit run into what looks like the power limit: int8
-    // 2048 x 2048 x 1024 9.9 -> 16.5 us (on 176 tiles 8.1 -> 9.9 now and then), bf16 0.92 - 1.05, convolutions on 227 - 256 0.85 - 1.05.  The sparse
+    // 1.12 (20.1 -> 18.2).  Beyond, eight wavefronts on nearly every unit cost clock: int8 2048 x 2048 x 1024 took 9.9 -> 16.5 us on
+    // some devices (on 176 tiles 8.1 -> 9.9 now and then), bf16 0.92 - 1.05, convolutions on 227 - 256 0.85 - 1.05.  The sparse
     // product, whose A is read twice as often from LDS with half the rows to a wavefront, is level with eight (0.92 - 1.1), and an
     // 8-bit dense one with an N-major B 3 - 6 % slower.
-    // Dense products split along K, whose slices fill the chip with few tiles, are 0.98 - 1.1 times as fast with eight.
+    // Dense products split along K make several workgroups of a tile: eight wavefronts are 1.0 - 1.1 times as fast on up to 192
+    // workgroups; on 240 and 256, four devices, int8 K-major 0.80 - 1.03 (on average 0.93; 1024 x 1024 x 16384 in four slices 31.6 us on
+    // four, 38.8 on eight), bf16 0.83 - 1.18 (0.98).
     if (small <= 256) {
-        const bool eight = a.conv.on ? small <= 210 : !a.sparse && (is8<DT> ? small <= 160 && a.bo != SP24_B_NMAJOR : small <= 176);
+        const bool split = a.k_slices > 1;
+        const int64_t groups = split ? small * a.k_slices : small, dense_most = split ? 192 : is8<DT> ? 160 : 176;
+        const bool eight = a.conv.on ? small <= 210 : !a.sparse && groups <= dense_most && !(is8<DT> && a.bo == SP24_B_NMAJOR);
         if (eight) return run_pipe<DT, OUT, 4, 2, 1, 2, 6, 4, kDense | kConvs>(a, st);
         return run_pipe<DT, OUT, 2, 2, 2, 2, 6, 4, kProducts | kConvs>(a, st);
     }
