@@ -1089,13 +1089,20 @@ static sp24_status pick_tile_general(const MmArgs& a, hipStream_t st)
     // results 0.94 - 1.01 at 8 and 1.00 - 1.24 at 16 on 192 rows, 0.85 - 1.01 at 16 and 0.99 - 1.15 at 24 on 256; dense
     // ones 0.97 - 1.9 throughout).
     // Convolutions gather B, whose cost halves per product with 256 rows (1.09 - 1.21 times as fast, int8 0.96 - 1.15) and
-    // not with 192.
-    const int64_t steps = a.K * (is8<DT> ? 1 : 2) / kRowBytes;
+    // not with 192 -- except sparse 8-bit ones of few steps on more than three quarters of the units (1x1, stride 2, 512 -> 1024
+    // channels, 14x14, 4 steps: 0.95 - 1.0 / 0.97 - 1.01 / 0.92 - 0.95 from the L2 / the last-level cache / HBM on three devices;
+    // 9 and 18 steps 0.97 - 1.01 / 1.0 / 1.04 - 1.17 on average).
+    // 8-bit products there run at the power limit: 4096 x 2048 x 4096 int8 takes 34.6 thousand clocks at 1.4 GHz on random operands
+    // and 39 thousand at 2.3 GHz on zeros.  How the tiles compare then depends on the device, most of all with few steps: 256 rows
+    // against 128x128, averages over seven devices, dense int8 with 32-bit results 0.98 / 1.01 / 1.04 at 12 steps (one device 0.73 -
+    // 1.02), 1.0 / 1.0 / 1.07 at 16, 1.04 / 1.05 / 1.11 at 24; sparse int8 with them 1.0 / 1.01 / 1.18 at 24 (one device 0.76 - 1.1 in the
+    // caches), sparse 8-bit floats with 16-bit results 1.0 / 0.95 / 1.2 at 12 and 16 (three devices, 0.79 - 1.15 in the caches).
+    const int64_t steps = a.K * (is8<DT> ? 1 : 2) / kRowBytes, tall = ((a.M + 255) / 256) * cols;
     constexpr bool kWideOut = out_size<OUT>() == 4;
     if (small > 256 && !a.conv.on && ((a.M + 191) / 192) * cols <= 256 && (!a.sparse || steps >= (kWideOut ? 16 : 12)))
         return run_pipe<DT, OUT, 3, 2, 2, 2, 5, 3, kProducts>(a, st);
-    if (small > 256 && ((a.M + 255) / 256) * cols <= 256 && (!a.sparse || steps >= (a.conv.on ? 4 : kWideOut ? 24 : 12)))
-        return run_pipe<DT, OUT, 4, 2, 2, 2, 4, 3, kProducts | kConvs>(a, st);
+    const int64_t fewest = !a.sparse ? 0 : a.conv.on ? (is8<DT> && tall > 192 ? 8 : 4) : kWideOut ? 24 : 12;
+    if (small > 256 && tall <= 256 && steps >= fewest) return run_pipe<DT, OUT, 4, 2, 2, 2, 4, 3, kProducts | kConvs>(a, st);
     // 256x256 tiles when there are enough of them for half the chip, else 128x128
     const int64_t big = ((a.M + 255) / 256) * ((a.N + 255) / 256);
     // one workgroup of eight wavefronts of 64x128 each per compute unit (its wavefronts sit two to a SIMD, so that

@@ -117,3 +117,15 @@ FEW_CONVS = [
 @pytest.mark.parametrize("sparse", [True, False])
 def test_convolutions_on_few_tiles(case, sparse):
     run_conv_case(*case, sparse=sparse, seed=92)
+
+
+# sparse 8-bit convolutions on more than 192 tiles of 256 rows: eight steps, and seven on 128 x 128
+MOST_UNITS_CONVS = [
+    ("i8", "i32", 160, 10, 50, 51, 128, 4, 2, (2, 0), (1, 1), "tiled"),
+    ("i8", "i32", 150, 10, 50, 51, 128, 7, 1, (3, 0), (1, 1), "canonical"),
+]
+
+
+@pytest.mark.parametrize("case", MOST_UNITS_CONVS)
+def test_convolutions_on_most_units(case):
+    run_conv_case(*case, sparse=True, seed=93)
