@@ -1124,9 +1124,11 @@ static sp24_status pick_tile_general(const MmArgs& a, hipStream_t st)
     // 1.08 - 1.35; dense bf16 1.13 - 1.31 / 1.09 - 1.39 / 1.02 - 1.38, int8 1.07 - 1.23 / 1.1 - 1.3 / 1.04 - 1.51.
     //  * An 8-bit N-major B, whose rows would be half a cache line in 64 columns: 64x128 (from HBM, K = 4096: 1.06 - 1.27 times
     //    as fast as before, the tall tile 0.81 - 1.08).
-    //  * A canonical operand, whose 64 bytes of a row are half a line too: 64x128 (8-bit 1.01 - 1.23, 16-bit N-major 0.94 - 1.18;
-    //    the tall tile 0.58 - 1.2).  16-bit K-major ones stay on two wavefronts (four: 1.05 - 1.14 at K = 544, but 0.84 - 0.93 where
-    //    rows are a power of two).
+    //  * A canonical operand, whose 64 bytes of a row are half a line too: 64x128 (8-bit 1.01 - 1.23; the tall tile 0.58 - 1.2).
+    //    16-bit K-major ones stay on two wavefronts (four: 1.05 - 1.14 at K = 544, but 0.84 - 0.93 where rows are a power of two), and
+    //    N-major ones from 48 steps on (four from the L2 / the last-level cache / HBM 1.02 - 1.05 / 1.0 - 1.05 / 1.0 - 1.05 at 8 steps,
+    //    0.97 - 0.99 / 0.99 - 1.02 / 0.97 - 1.03 at 32, 0.93 - 1.02 / 0.97 - 1.02 / 0.95 - 1.03 at 64, 0.96 - 1.01 / 0.93 - 1.0 / 0.94 - 1.03
+    //    at 128; 4096 x 128 x 4096 bf16 19.1 us on two, 20.4 on four).
     //  * N <= 64: tiles of 64x64, two wavefronts (128x64 0.74 - 0.99 times as fast), which do not fetch rows of B that do not
     //    exist (sparse 28 - 31 % ahead of 64x128, 8192 x 64 x 8192 bf16: 43.8 -> 31.5 us).
     //  * Convolutions: 128x64 throughout, which leaves the gather of B per product as it is (against 128x128 on eight wavefronts
@@ -1138,7 +1140,7 @@ static sp24_status pick_tile_general(const MmArgs& a, hipStream_t st)
         const bool canonical = a.sparse && a.layout == SP24_LAYOUT_CANONICAL, nmajor = a.bo == SP24_B_NMAJOR;
         if (a.N <= 64) return run_pipe<DT, OUT, 2, 1, 1, 2, 9, 9, kProducts>(a, st);
         if constexpr (!is8<DT>) {
-            if (canonical && !nmajor) return run_pipe<DT, OUT, 2, 1, 1, 4, 7, 0, kSparse>(a, st);
+            if (canonical && (!nmajor || steps >= 48)) return run_pipe<DT, OUT, 2, 1, 1, 4, 7, 0, kSparse>(a, st);
         }
         if (canonical || (is8<DT> && nmajor)) return run_pipe<DT, OUT, 2, 2, 1, 2, 7, 6, kProducts>(a, st);
         return run_pipe<DT, OUT, 4, 1, 1, 2, 8, 6, kProducts | kConvs>(a, st);

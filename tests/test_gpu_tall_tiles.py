@@ -129,3 +129,15 @@ MOST_UNITS_CONVS = [
 @pytest.mark.parametrize("case", MOST_UNITS_CONVS)
 def test_convolutions_on_most_units(case):
     run_conv_case(*case, sparse=True, seed=93)
+
+
+# 16-bit canonical operands, N-major: 48 steps on two wavefronts, 47 on four, a partial one behind them
+CANONICAL_N_MAJOR = [
+    ("bf16", "f32", 130, 640, 3104),
+    ("f16", "f16", 200, 592, 3040),
+]
+
+
+@pytest.mark.parametrize("case", CANONICAL_N_MAJOR)
+def test_canonical_n_major_products(case):
+    run_mm_case(*case, layout="canonical", b_order="n", sparse=True, seed=94)
