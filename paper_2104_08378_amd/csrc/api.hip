@@ -403,7 +403,7 @@ static sp24_status mm_common(const MmArgs& a, hipStream_t st, size_t x_bytes = 0
 //  * N > 32 (tiled kernels, 128x128 tiles; rows past M are computed on a valid row and never stored): 1 .. min(8, compute units / tiles, steps / 4) slices of whole
 //    128-byte steps; a launch takes 5 us plus 400 ns per step of its workgroups (fitted to measurements of both
 //    types at 16 - 128 steps, operands from HBM); the unsplit product it is compared with runs shorter steps when it
-//    has at most 128 tiles (tiles of 64 rows).
+//    has at most 128 tiles (smaller ones are taken then).
 //  * N <= 32, M >= 32 (streaming kernel, one workgroup per 32 rows): 1 .. min(8, compute units / row blocks,
 //    tiles / 32) slices of whole 64-column tiles; a workgroup takes 130 ns (16-bit) or 80 ns (8-bit) per tile of
 //    its 32 rows (measured at K = 16384: latency-bound, the same whether 16 or 128 workgroups run).
@@ -437,8 +437,11 @@ static SplitPlan split_plan(int64_t M, int64_t N, int64_t K, sp24_dtype in)
         fixed_ns = 3000;
     }
     if (most > 8) most = 8;
-    // the unsplit tiled product on at most 128 tiles runs on tiles of 64 rows, with shorter steps (215 ns when they are
-    // 64 columns wide, 325 ns else: fitted to the sparse products of both types at 64 and 128 steps)
+    // The unsplit tiled product on at most 128 tiles runs on smaller ones, with shorter steps: 215 ns where they are 64 columns
+    // wide, else 325 ns, which is 64x128 on two wavefronts (both fitted to the sparse products of both types at 64 and 128 steps).
+    // Most operands now take 128x64 on four wavefronts, 1.07 - 1.38 times as fast.  From HBM the plan is right all the same
+    // (against the unsplit product 1.0 - 3.4 times as fast dense, 1.1 - 4 canonical, 0.93 - 3 in the tiled layout), and
+    // callers have been told its workspace; where a sparse operand in the tiled layout is better off unsplit, mm_splitk does not split.
     int64_t unsplit_unit_ns = unit_ns;
     if (!p.streaming && ((M + 127) / 128) * ((N + 127) / 128) <= 128) unsplit_unit_ns = N <= 64 ? 215 : 325;
     int64_t best_ns = (base_ns + units * unsplit_unit_ns) * 9 / 10, best = 1, best_per = units;
@@ -543,6 +546,13 @@ static sp24_status mm_splitk(const MmArgs& a, void* workspace, size_t workspace_
             if (handled) return launch_splitk_reduce(workspace, part.k_slices, a.M, a.N, plan.ldw, a.D, a.ldd, a.in == SP24_I8, a.out, st);
             part.k_slices = plan.slices;
         }
+    } else if (a.sparse && a.layout == SP24_LAYOUT_TILED && a.N > 64 && (es == 2 || a.bo == SP24_B_KMAJOR)) {
+        // The tiled layout has the shortest steps unsplit (128x64 tiles on four wavefronts).  The plan's cut against it, time over time
+        // from the L2 / the last-level cache / HBM: K-major, both types, 1.5 / 1.37 / 1.04 at 32 steps, 1.4 / 1.17 / 0.9 at 40, 1.3 / 1.13 /
+        // 0.85 at 48, 1.16 / 1.06 / 0.79 at 64; in two slices 1.12 / 1.12 / 1.05 at 96, 1.1 / 1.1 / 1.0 at 128, 1.02 / 1.02 / 0.95 at 160.
+        // N-major bf16 1.36 / 1.33 / 1.05 at 32 and 1.24 / 1.2 / 0.9 at 40; int8 (tiles of 64x128) 1.29 / 1.11 / 0.82 at 32 already.
+        const int64_t steps = a.K * es / 128;
+        if (steps <= (a.bo == SP24_B_KMAJOR && plan.slices == 2 ? 128 : 32)) return mm_dispatch(a, st);
     }
     s = plan.streaming ? launch_mm_skinny(part, st, &handled) : launch_mm_tiled(part, st, &handled);
     if (!handled) return mm_dispatch(a, st);             // operands that kernel does not take: not split

@@ -173,3 +173,37 @@ def test_long_slices_take_the_planned_cut(case):
         if out == "f32":
             scale = np.abs(oracle.to_double(Prows, dtype)) @ np.abs(oracle.to_double(Bcols, dtype))
             assert (np.abs(out_to_f64(got) - ref) <= K * 2.0 ** -24 * scale + 1e-30).all()
+
+
+# sparse operands in the tiled layout whose unsplit product is the faster one: up to 32 steps (in two slices 128), and one step
+# more; an 8-bit N-major B is split with 32 too
+SHORT = [
+    ("bf16", "bf16", 256, 640, 2048, "k", False),
+    ("bf16", "bf16", 256, 640, 2112, "k", True),
+    ("i8", "i32", 128, 1024, 4160, "k", False),          # 32 steps and half a step
+    ("i8", "i32", 128, 1024, 4224, "k", True),
+    ("f16", "f32", 1024, 192, 2048, "n", False),
+    ("f16", "f32", 1024, 192, 2112, "n", True),
+    ("i8", "i32", 1024, 192, 4096, "n", True),
+    ("bf16", "f32", 1536, 1024, 8192, "k", False),       # two slices
+    ("bf16", "f32", 1536, 1024, 8256, "k", True),
+]
+
+
+@pytest.mark.parametrize("case", SHORT)
+def test_short_products_in_the_tiled_layout_are_not_split(case):
+    dtype, out, M, N, K, b_order, split = case
+    need = sp24.sp24_splitk_workspace_bytes(M, N, K, IN_DT[dtype])
+    assert need > 0
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")          # NaN bit patterns / -1
+    A, Bt = synth.make(NAME_OF[dtype], M=M, N=N, K=K, seed=26)
+    Bd = to_gpu(Bt if b_order == "k" else np.ascontiguousarray(Bt.T), dtype)
+    V, meta = sp24.sp24_compress(to_gpu(A, dtype), layout="tiled")
+    D = sp24.sp24_spmm_splitk(V, meta, Bd, OUT_DT[out], b_order=b_order, layout="tiled", workspace=ws)
+    U = sp24.sp24_spmm(V, meta, Bd, OUT_DT[out], b_order=b_order, layout="tiled")
+    torch.cuda.synchronize()
+    assert bool((ws == 0xFF).all()) != split
+    if split and dtype != "i8":
+        assert rel_err(out_to_f64(D), out_to_f64(U)) <= REL_TOL
+    else:
+        assert torch.equal(D.view(torch.uint8), U.view(torch.uint8))
