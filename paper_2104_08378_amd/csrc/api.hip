@@ -347,13 +347,18 @@ static bool stream_first(const MmArgs& a)
 
 // Sparse products that the tiled kernels do not take: tiles of their shape with B staged through registers, or (N-major,
 // few tiles) K split across the wavefronts of a workgroup, which the former leaves idle.  Measured on N-major products
-// with an odd N: up to 64 tiles of 128 x 128 the K-splitting kernel is ahead by 10 - 90 % (2048 x 509 x 2048 bf16 12.3
-// against 16.7 us, 512 x 511 x 8192 25.5 against 47.5), from 80 on the staged one by 10 - 50 % (2560 x 509 x 2048 17.3
-// against 20.7, 4096 x 509 x 1024 10.6 against 15.7, 4096 x 257 x 4096 25.7 against 31.6).
+// with an odd N: up to 64 tiles of 128 x 128 the K-splitting kernel is ahead with many steps, from 72 on the staged one throughout
+// (1.0 - 1.6 times as fast; 2560 x 509 x 2048 bf16 12.6 us against 16.3, 4096 x 257 x 4096 21.1 against 30.5).
+// Between 257 workgroups of 32 x 64, past which the K-splitting kernel takes two row blocks to a workgroup, and 64 tiles the staged
+// one is ahead with few steps.  Its time over the other's from the L2 / the last-level cache / HBM: tiled layout 0.73 - 0.87 /
+// 0.72 - 0.86 / 0.72 - 0.87 up to 4 steps, 0.82 - 0.93 / 0.87 - 0.99 / 0.93 - 1.02 at 16, 0.87 - 0.94 / 0.91 - 1.04 / 0.96 - 1.07 at 20;
+// canonical 0.9 - 1.0 / 0.91 - 1.03 / 0.91 - 1.03 at 4, 1.0 - 1.1 at 8.  (2048 x 509 x 1024 int8 6.3 us against 7.8.)
 static bool staged_before_ksplit(const MmArgs& a)
 {
     if (a.conv.on || a.bo == SP24_B_KMAJOR) return true;      // the K-splitting kernel does not take them anyway
-    return ((a.M + 127) / 128) * ((a.N + 127) / 128) > 64;
+    if (((a.M + 127) / 128) * ((a.N + 127) / 128) > 64) return true;
+    const int64_t steps = a.K * esize_of(a.in) / 128;
+    return ((a.M + 31) / 32) * ((a.N + 63) / 64) > 256 && steps <= (a.layout == SP24_LAYOUT_TILED ? 16 : 4);
 }
 
 // The kernel for a checked product: few columns or few tiles (K split across wavefronts), streaming (N <= 32), tiled, and for

@@ -4,6 +4,7 @@ and test_gpu_ragged_output.py), and of the wider forms of the kernels that split
 import pytest
 import torch
 
+from paper_2104_08378_amd import sp24
 from test_gpu_f8 import test_f8_products_against_the_oracle as run_f8
 from test_gpu_parity import run_mm_case
 from test_gpu_ragged_output import test_every_column_and_nothing_else as run_ragged
@@ -120,3 +121,41 @@ def test_split_products_with_many_columns(case):
 @pytest.mark.parametrize("M,N", [(224, 701), (96, 1033), (32, 515), (1440, 1502)])
 def test_quantised_results_with_odd_rows(out, M, N):
     run_ragged("i8", out, M, N)
+
+
+# N-major rows at odd addresses on more than 256 tiles of 32 x 64 and at most 64 of 128 x 128, sparse: up to 16 steps in the tiled
+# layout (canonical 4) with B staged through registers, from 17 (5) on wavefronts that split K over two row blocks; partial steps
+FEW_STEPS = [
+    ("i8", "i32", 2048, 509, 2112, "tiled"),
+    ("i8", "i32", 2048, 509, 2176, "tiled"),
+    ("bf16", "bf16", 1408, 333, 1024, "tiled"),
+    ("f16", "f32", 8192, 65, 1088, "tiled"),
+    ("i8", "i32", 2017, 509, 608, "canonical"),
+    ("bf16", "f32", 1999, 511, 304, "canonical"),
+    ("f16", "f16", 1153, 509, 320, "canonical"),
+]
+
+
+@pytest.mark.parametrize("case", FEW_STEPS)
+def test_n_major_at_any_address_with_few_steps(case):
+    dtype, out, M, N, K, layout = case
+    run_mm_case(dtype, out, M, N, K, layout=layout, b_order="n", sparse=True, seed=78)
+
+
+@pytest.mark.parametrize("K", [2048, 2240])
+def test_8_bit_floats_n_major_at_any_address_with_few_steps(K):
+    run_f8((1536, 509, K, "tiled", "n"), torch.float32)
+
+
+@pytest.mark.parametrize("out", ["i8", "bf16"])
+def test_quantised_results_n_major_at_any_address_with_few_steps(out):
+    g = torch.Generator(device="cuda").manual_seed(79)
+    M, N, K = 2048, 509, 1024
+    dt = torch.int8 if out == "i8" else torch.bfloat16
+    V, meta = sp24.sp24_compress(torch.randint(-127, 128, (M, K), generator=g, device="cuda", dtype=torch.int8), layout="tiled")
+    B = torch.randint(-127, 128, (K, 512), generator=g, device="cuda", dtype=torch.int8)
+    scale = torch.rand(M, generator=g, device="cuda") * 1e-3
+    want = sp24.sp24_spmm_i8_scaled(V, meta, B, dt, scale, 0.1, b_order="n", layout="tiled")[:, :N]       # the tiled kernels
+    got = sp24.sp24_spmm_i8_scaled(V, meta, B[:, :N].contiguous(), dt, scale, 0.1, b_order="n", layout="tiled")
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
