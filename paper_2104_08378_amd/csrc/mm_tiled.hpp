@@ -1033,7 +1033,8 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_gemm_pipe(MmArgs a, int til
 // ---------------------------------------------------------------------------
 // NSS / NSD: pipeline stages of the sparse / dense kernel; USES: which problems the tile shape serves (it is not compiled
 // for others)
-enum { kSparse = 1, kDense = 2, kSparseConv = 4, kDenseConv = 8, kProducts = kSparse | kDense, kConvs = kSparseConv | kDenseConv };
+enum { kSparseK = 1, kSparseN = 2, kDenseK = 4, kDenseN = 8, kSparseConv = 16, kDenseConv = 32,      // K- and N-major products, convolutions
+       kProducts = kSparseK | kSparseN | kDenseK | kDenseN, kConvs = kSparseConv | kDenseConv };
 
 template <int DT, int OUT, int WM, int WN, int TM, int TN, int NSS, int NSD, int USES>
 static sp24_status run_pipe(const MmArgs& a, hipStream_t st)
@@ -1041,34 +1042,18 @@ static sp24_status run_pipe(const MmArgs& a, hipStream_t st)
     constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN;
     const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (int)((a.N + BN - 1) / BN);
     const dim3 grid((unsigned)(tiles_m * tiles_n), (unsigned)(a.k_slices > 1 ? a.k_slices : 1)), block(64 * WM * WN);
-    bool known = false;
-    if constexpr ((USES & kSparseConv) != 0) {
-        if (a.sparse && a.conv.on) {
-            known = true;
-            k_spmm_pipe<DT, OUT, WM, WN, TM, TN, NSS, 1><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
-        }
-    }
-    if constexpr ((USES & kSparse) != 0) {
-        if (a.sparse && !a.conv.on) {
-            known = true;
-            if (a.bo == SP24_B_NMAJOR) k_spmm_pipe<DT, OUT, WM, WN, TM, TN, NSS, 2><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
-            else k_spmm_pipe<DT, OUT, WM, WN, TM, TN, NSS, 0><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
-        }
-    }
-    if constexpr ((USES & kDenseConv) != 0) {
-        if (!a.sparse && a.conv.on) {
-            known = true;
-            k_gemm_pipe<DT, OUT, WM, WN, TM, TN, NSD, 1><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
-        }
-    }
-    if constexpr ((USES & kDense) != 0) {
-        if (!a.sparse && !a.conv.on) {
-            known = true;
-            if (a.bo == SP24_B_NMAJOR) k_gemm_pipe<DT, OUT, WM, WN, TM, TN, NSD, 2><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
-            else k_gemm_pipe<DT, OUT, WM, WN, TM, TN, NSD, 0><<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
-        }
-    }
-    return known && hipGetLastError() == hipSuccess ? SP24_OK : SP24_ERR_LAUNCH;
+    const int use = a.conv.on ? (a.sparse ? kSparseConv : kDenseConv)
+                              : a.bo == SP24_B_NMAJOR ? (a.sparse ? kSparseN : kDenseN) : (a.sparse ? kSparseK : kDenseK);
+    auto run = [&](auto u, auto kernel) {
+        if (use == decltype(u)::value) kernel<<<grid, block, 0, st>>>(a, tiles_m, tiles_n);
+    };
+    if constexpr ((USES & kSparseConv) != 0) run(std::integral_constant<int, kSparseConv>{}, k_spmm_pipe<DT, OUT, WM, WN, TM, TN, NSS, 1>);
+    if constexpr ((USES & kSparseK) != 0) run(std::integral_constant<int, kSparseK>{}, k_spmm_pipe<DT, OUT, WM, WN, TM, TN, NSS, 0>);
+    if constexpr ((USES & kSparseN) != 0) run(std::integral_constant<int, kSparseN>{}, k_spmm_pipe<DT, OUT, WM, WN, TM, TN, NSS, 2>);
+    if constexpr ((USES & kDenseConv) != 0) run(std::integral_constant<int, kDenseConv>{}, k_gemm_pipe<DT, OUT, WM, WN, TM, TN, NSD, 1>);
+    if constexpr ((USES & kDenseK) != 0) run(std::integral_constant<int, kDenseK>{}, k_gemm_pipe<DT, OUT, WM, WN, TM, TN, NSD, 0>);
+    if constexpr ((USES & kDenseN) != 0) run(std::integral_constant<int, kDenseN>{}, k_gemm_pipe<DT, OUT, WM, WN, TM, TN, NSD, 2>);
+    return (USES & use) != 0 && hipGetLastError() == hipSuccess ? SP24_OK : SP24_ERR_LAUNCH;
 }
 
 template <int DT, int OUT>
@@ -1112,10 +1097,9 @@ static sp24_status pick_tile_general(const MmArgs& a, hipStream_t st)
     // Convolutions follow the general rule (at 154 - 196: 7 - 20 % faster, strided sparse ones 25 - 28 %).
     // -- unless the large tile would be mostly padding: rows and columns it covers beyond M and N are computed all the
     // same, and per product computed the small tile (two workgroups to a unit) costs about a third more
-    const int64_t enough = (!a.conv.on && !is8<DT> && !a.sparse) ? 100 : 129;
     const double cover_big = (double)(((a.M + 255) / 256) * 256) * (double)(((a.N + 255) / 256) * 256);
     const double cover_small = (double)(((a.M + 127) / 128) * 128) * (double)(((a.N + 127) / 128) * 128);
-    if (big >= enough && cover_big <= 1.35 * cover_small) return run_pipe<DT, OUT, 4, 2, 2, 4, 3, 2, kProducts | kConvs>(a, st);
+    if (big >= 129 && cover_big <= 1.35 * cover_small) return run_pipe<DT, OUT, 4, 2, 2, 4, 3, 2, kProducts | kConvs>(a, st);
     // At most 128 tiles of 128x128: twice as many of 128x64 (64x128), four wavefronts of 32x64 each.  A row of the compressed
     // operand costs 80 bytes a step and a column 128, so the tall tile is the cheaper of the two (18.4 against 21.5 KB), and
     // four wavefronts, one to a SIMD, issue a step's reads and transfers in half the time that two need: against 64x128
@@ -1135,15 +1119,16 @@ static sp24_status pick_tile_general(const MmArgs& a, hipStream_t st)
     //    1.06 - 1.31 times as fast: 512 channels, 14x14, 3x3, stride 2, 32 images f16 24.6 -> 18.9 us, dense 26.6 -> 21.6; tiles of
     //    64 rows, which double it, had been 20 - 30 % slower than 128).
     // (Not for a product already split along K, whose slices fill the chip.)
-    if (small <= 128 && a.conv.on) return run_pipe<DT, OUT, 4, 1, 1, 2, 8, 6, kProducts | kConvs>(a, st);
+    constexpr int kTallUses = kConvs | (is8<DT> ? kSparseK | kDenseK : kProducts);
+    if (small <= 128 && a.conv.on) return run_pipe<DT, OUT, 4, 1, 1, 2, 8, 6, kTallUses>(a, st);
     if (small <= 128 && a.k_slices <= 1) {
         const bool canonical = a.sparse && a.layout == SP24_LAYOUT_CANONICAL, nmajor = a.bo == SP24_B_NMAJOR;
         if (a.N <= 64) return run_pipe<DT, OUT, 2, 1, 1, 2, 9, 9, kProducts>(a, st);
         if constexpr (!is8<DT>) {
-            if (canonical && (!nmajor || steps >= 48)) return run_pipe<DT, OUT, 2, 1, 1, 4, 7, 0, kSparse>(a, st);
+            if (canonical && (!nmajor || steps >= 48)) return run_pipe<DT, OUT, 2, 1, 1, 4, 7, 0, kSparseK | kSparseN>(a, st);
         }
-        if (canonical || (is8<DT> && nmajor)) return run_pipe<DT, OUT, 2, 2, 1, 2, 7, 6, kProducts>(a, st);
-        return run_pipe<DT, OUT, 4, 1, 1, 2, 8, 6, kProducts | kConvs>(a, st);
+        if (canonical || (is8<DT> && nmajor)) return run_pipe<DT, OUT, 2, 2, 1, 2, 7, 6, is8<DT> ? kSparseK | kSparseN | kDenseN : kSparseN>(a, st);
+        return run_pipe<DT, OUT, 4, 1, 1, 2, 8, 6, kTallUses>(a, st);
     }
     // 128x128 tiles.  With at most 256 one workgroup per compute unit is all there is: six (dense: four) stages, transfers five
     // (three) steps ahead.  The dense product and the convolutions, whose steps are the longer to issue (twice the bytes of A;
@@ -1162,7 +1147,7 @@ static sp24_status pick_tile_general(const MmArgs& a, hipStream_t st)
         const bool split = a.k_slices > 1;
         const int64_t groups = split ? small * a.k_slices : small, dense_most = split ? 192 : is8<DT> ? 160 : 176;
         const bool eight = a.conv.on ? small <= 210 : !a.sparse && groups <= dense_most && !(is8<DT> && a.bo == SP24_B_NMAJOR);
-        if (eight) return run_pipe<DT, OUT, 4, 2, 1, 2, 6, 4, kDense | kConvs>(a, st);
+        if (eight) return run_pipe<DT, OUT, 4, 2, 1, 2, 6, 4, kConvs | (is8<DT> ? kDenseK : kDenseK | kDenseN)>(a, st);
         return run_pipe<DT, OUT, 2, 2, 2, 2, 6, 4, kProducts | kConvs>(a, st);
     }
     // more of them: three (two) stages leave room for two workgroups per compute unit
