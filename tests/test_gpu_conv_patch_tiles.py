@@ -3,6 +3,7 @@ test_gpu_conv.py)."""
 import pytest
 
 from test_gpu_conv import run_case
+from test_gpu_scaled import test_quantised_convolution_int8_output_is_bit_exact as run_scaled
 
 pytestmark = pytest.mark.gpu
 
@@ -31,3 +32,26 @@ CASES = [
 def test_patch_tiles(case):
     dtype, out, M, n_img, H, W, C, pad = case
     run_case(dtype, out, M, n_img, H, W, C, 3, 3, pad, (1, 1), "tiled", sparse=True, seed=95)
+
+
+# 128 x 128 tiles with several chunks of channels: more than 256 tiles of 64 x 128
+SEVERAL_CHUNKS = [
+    ("bf16", "bf16", 128, 22, 28, 28, 128, (1, 1)),   # 192-pixel patch: two chunks
+    ("f16", "f32", 96, 28, 25, 26, 192, (1, 1)),      # three, ragged filters and pixels
+    ("i8", "i32", 160, 14, 28, 29, 256, (1, 1)),
+    ("f16", "f16", 128, 6, 56, 56, 128, (1, 1)),      # 256-pixel patch
+    ("bf16", "f32", 96, 6, 55, 57, 192, (1, 1)),
+    ("i8", "i32", 128, 6, 55, 57, 384, (1, 1)),
+]
+
+
+@pytest.mark.parametrize("case", SEVERAL_CHUNKS)
+def test_large_tiles_with_several_chunks(case):
+    dtype, out, M, n_img, H, W, C, pad = case
+    run_case(dtype, out, M, n_img, H, W, C, 3, 3, pad, (1, 1), "tiled", sparse=True, seed=96)
+
+
+# quantised results: 64 x 128 tiles, and 128 x 128 with several chunks on both patches
+@pytest.mark.parametrize("M,n_img,H,W,C", [(64, 30, 24, 24, 128), (128, 22, 28, 28, 256), (96, 6, 56, 56, 256)])
+def test_quantised_results(M, n_img, H, W, C):
+    run_scaled((M, n_img, H, W, C, 3, 3, (1, 1), (1, 1), "tiled"))

@@ -2,9 +2,14 @@
 test_gpu_conv.py): more than 256 tiles of 128 x 128 and at most 256 of these; and, at most 128 tiles of 128 x 128, on tiles of
 128 x 64 and 64 x 128 with four wavefronts, and the dense ones and the convolutions on 128 x 128 with eight."""
 import pytest
+import torch
 
+from paper_2104_08378_amd import sp24
 from test_gpu_conv import run_case as run_conv_case
+from test_gpu_f8 import test_f8_products_against_the_oracle as run_f8
 from test_gpu_parity import run_mm_case
+from test_gpu_scaled import test_float_outputs_match_the_double_epilogue as run_scaled_float
+from test_gpu_scaled import test_int8_output_is_bit_exact as run_scaled_int8
 
 pytestmark = pytest.mark.gpu
 
@@ -141,3 +146,42 @@ CANONICAL_N_MAJOR = [
 @pytest.mark.parametrize("case", CANONICAL_N_MAJOR)
 def test_canonical_n_major_products(case):
     run_mm_case(*case, layout="canonical", b_order="n", sparse=True, seed=94)
+
+
+# int8 with 32-bit results on 256 rows: 24 steps and a partial one, the fewest that a sparse product takes them with
+def test_int8_products_on_256_rows():
+    run_mm_case("i8", "i32", 256, 16400, 3104, layout="canonical", b_order="k", sparse=True, seed=97)
+    run_mm_case("i8", "i32", 224, 16400, 3136, layout="tiled", b_order="n", sparse=True, seed=98)
+
+
+# quantised results on 192 and 256 rows: the fewest steps of the sparse product (12; 16 and 24 for 32-bit results) and partial ones,
+# whole and ragged tiles, even and odd columns
+@pytest.mark.parametrize("case", [(384, 10990, 1632, "canonical"), (320, 11007, 1664, "tiled"), (256, 16400, 1632, "canonical"), (193, 16401, 1600, "canonical")])
+@pytest.mark.parametrize("sparse", [True, False])
+def test_quantised_products(case, sparse):
+    run_scaled_int8(case, sparse)
+
+
+@pytest.mark.parametrize("case,out", [((300, 11007, 1632, "canonical"), "bf16"), ((384, 10990, 2112, "tiled"), "f32"),
+                                      ((256, 16401, 1600, "tiled"), "bf16"), ((200, 16400, 3104, "canonical"), "f32")])
+def test_quantised_products_with_float_results(case, out):
+    run_scaled_float(case, out)
+
+
+# (half precision is subnormal near zero, where its rounding is absolute, up to 2^-25, and the bound above relative: against the
+# results of 32 bits, whose epilogue is the same, rounded once)
+@pytest.mark.parametrize("M,N", [(384, 10990), (256, 16401)])
+def test_quantised_products_with_half_precision_results(M, N):
+    g = torch.Generator(device="cuda").manual_seed(99)
+    rand = lambda *s: torch.randint(-127, 128, s, generator=g, device="cuda", dtype=torch.int8)
+    V, meta = sp24.sp24_compress(rand(M, 1600), layout="tiled")
+    B, scale = rand(N, 1600), torch.rand(M, generator=g, device="cuda") * 1e-3
+    half, single = [sp24.sp24_spmm_i8_scaled(V, meta, B, t, scale, 0.02, scale, True, layout="tiled") for t in (torch.float16, torch.float32)]
+    torch.cuda.synchronize()
+    assert torch.equal(half, single.to(torch.float16))
+
+
+@pytest.mark.parametrize("case,out", [((384, 10990, 1632, "canonical", "k"), torch.bfloat16), ((288, 11008, 2112, "tiled", "n"), torch.float32),
+                                      ((256, 16401, 1600, "tiled", "k"), torch.float16), ((200, 16400, 3104, "canonical", "n"), torch.float32)])
+def test_8_bit_float_products(case, out):
+    run_f8(case, out)
