@@ -303,7 +303,7 @@ static sp24_status mm_validate(const MmArgs& a, size_t x_bytes, bool* empty)
 // Measured at K = 4096 and 8192, M = 2048 .. 128256, operands from HBM, in tiles = ceil(M / 128):
 //  * N > 16: the dense product always (M = 4096, K = 8192, N = 32: 40.6 -> 32.6 us), the sparse one from 86 tiles on
 //    (11008 rows; below that it depends on M, within 15 % either way);
-//  * N <= 16, 16-bit: from 86 tiles on, sparse 3 - 10 % faster up to 128 tiles (64-row tiles), level to 191, then
+//  * N <= 16, 16-bit: from 86 tiles on, sparse 3 - 10 % faster up to 128 tiles (of 64 x 64 then), level to 191, then
 //    ahead for good (32000 x 4096, N = 1: 36.4 -> 31.5 us; 128256 rows: 133 -> 117 us); dense 15 - 30 % faster
 //    at 86 - 256 tiles, past that only for N > 8;
 //  * N <= 16, 8-bit: the dense product for N > 8 from 86 tiles on; the sparse one stays with the streaming kernel
@@ -319,15 +319,19 @@ static bool tiled_before_streaming(const MmArgs& a)
 
 // Sparse products whose tiles of 32 rows and 16, 32 or 64 columns each find a compute unit of their own: the kernel that
 // splits K across a workgroup's wavefronts.  One workgroup's rings fill a unit's LDS, so a second round costs the whole
-// time again: measured against the tiled and the streaming kernel, up to 256 workgroups 1.05 - 2.4 times as fast
-// (1024 x 128 x 4096 bf16 16.7 -> 9.9 us, 8192 x 32 x 8192 25.1 -> 14.0, 8192 x 16 x 8192 18.1 -> 13.3; 4096 x 1 x 1024
-// level; with the compressed operand from HBM 8192 x 16 x 8192 19.3 -> 16.4, 8192 x 64 x 8192 32.3 -> 27.8), past that 0.4 -
-// 1.0 times -- except for 16-bit inputs with N <= 32 up to the 86 tiles of 128 rows from which the tiled kernels take them
+// time again: measured against the streaming and the tiled kernels, up to 256 workgroups 1.0 - 2.7 times as fast with 65 - 512
+// columns (averages from the L2 / the last-level cache / HBM, K 512 - 8192: tiled layout bf16 1.28 / 1.3 / 1.41, int8 1.2 / 1.23 / 1.29,
+// canonical 1.6 / 1.71 / 1.91 and 1.25 / 1.42 / 1.54; 1024 x 128 x 4096 bf16 11.3 -> 8.3 us, from HBM 20.8 -> 13.0) and 1.05 - 2.4 with fewer
+// (8192 x 32 x 8192 25.1 -> 14.0, 8192 x 16 x 8192 18.1 -> 13.3; 4096 x 1 x 1024
+// level; with the compressed operand from HBM 8192 x 16 x 8192 19.3 -> 16.4, 8192 x 64 x 8192 32.3 -> 27.8), past that 0.7 -
+// 1.05 times in the tiled layout and 0.7 - 1.46 in the canonical one (averages 0.7 - 0.88 and 0.8 - 1.16) -- except for 16-bit inputs with N <= 32
+// up to the 86 tiles of 128 rows from which the tiled kernels take them
 // (9216 x 16 x 4096 17.0 -> 12.3 us in two rounds; 10976 x 16 x 1024, 86 tiles, 5.7 us on the tiled kernels against 6.6).  Where
 // K has few steps and a partial one behind them, two rounds are 5 - 20 % behind the tiled kernels too (9098 x 17 x 288 4.8 us
 // against 5.6).
-// The limit of 512 columns is not one of speed: 32 - 512 rows on 513 - 2048 columns would run 1.3 - 2.0 times as fast here
-// (128 x 1000 x 4096 bf16 16.9 -> 9.8 us).  It keeps wide products of 16-bit types with few rows, convolutions written out
+// The limit of 512 columns is not one of speed: 32 - 512 rows on 513 - 2048 columns, up to 256 workgroups, would run 1.0 - 1.8 times as
+// fast here in the tiled layout and 1.0 - 2.7 in the canonical one (128 x 1000 x 4096 bf16 11.7 -> 8.2 us, 17.3 -> 9.9 canonical).
+// It keeps wide products of 16-bit types with few rows, convolutions written out
 // among them, on the kernel that adds K in the order of the implicit convolution with one chunk of channels, so that the two
 // agree bit for bit; narrower ones have not agreed since this kernel takes them, and the interface promises neither.
 static bool stream_first(const MmArgs& a)

@@ -11,7 +11,7 @@
 // registers in the matrix instruction's own lane order.
 //
 // Measured against the general kernel that took these before (us, operands rotating): 1024 x 509 x 4096 int8 482 -> 12.7;
-// 8192 x 17 x 8192 bf16 443 -> 30; 2048 x 509 x 2048 bf16 12.3.  Products with many tiles go to mm_staged.hpp.
+// 8192 x 17 x 8192 bf16 443 -> 30; 2048 x 509 x 2048 bf16 12.3.  Products with many tiles, or few steps of K, go to mm_staged.hpp.
 #include "mm_operands.hpp"
 
 namespace sp24 {

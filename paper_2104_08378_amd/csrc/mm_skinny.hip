@@ -193,7 +193,7 @@ sp24_status launch_mm_skinny(const MmArgs& a, hipStream_t st, bool* handled)
               a.M >= 32 && (a.M + 31) / 32 < ((int64_t)1 << 31);
     // A canonical K that ends inside a tile of 64 columns; the check at every piece is not always worth it.
     //  * Half a tile, 16-bit: the tiled kernels are ahead (9098 x 1 x 32 bf16 3.1 us against 5.7, 10880 x 17 x 96 4.2 against 6.2).
-    //  * Half a tile, 8-bit, up to 128 tiles of 128 rows (the tiled kernels' 64-row tiles): those are up to 9 % ahead at K = 96,
+    //  * Half a tile, 8-bit, up to 128 tiles of 128 rows (the tiled kernels take 64 x 64 then): those are up to 9 % ahead at K = 96,
     //    7 - 30 % behind from 160 to 1568, within 7 % at 2080 and up to 30 % ahead past that (12000 x 8 x 544 5.2 us there, 4.5
     //    here; x 6176 17 and 22).  Up to 384 tiles they are ahead below K = 512 and 5 - 70 % behind from there (33333 x 1 x 4128
     //    49.9 and 29.9; level again for 203 tiles past 3104), with more behind from some 1000 on, where N <= 8 (10 - 40 %).

@@ -1060,9 +1060,10 @@ template <int DT, int OUT>
 static sp24_status pick_tile_general(const MmArgs& a, hipStream_t st)
 {
     // What sets the pace of a product whose tiles make one round of workgroups is the bytes a compute unit brings in, a step
-    // of 80 per row and 128 per column (dense: 128 and 128) at some 60 - 70 GB/s from HBM and 110 - 150 from the last-level
-    // cache and the L2, whatever the number of units (a unit has only so many lines on their way: eight times the
-    // transfers in flight do not change it).  So: the smallest tile whose workgroups still find a unit each.
+    // of 80 per row (16-bit types 72) and 128 per column (dense: 128 and 128), at some 60 - 70 GB/s from HBM whatever the number
+    // of units (a unit has only so many lines on their way: eight times the transfers in flight do not change it), and from the
+    // last-level cache and the L2 at 110 - 150 on up to 128 units, 81 - 88 on 174 (11008 x 333 x 4096 bf16) and 71 - 78 on 256 (4096 x 1024 x
+    // 4096 bf16, dense and sparse).  So: the smallest tile whose workgroups still find a unit each.
     const int64_t cols = (a.N + 127) / 128, small = ((a.M + 127) / 128) * cols;
     // More than 256 tiles of 128x128, two and three workgroups to some units: tiles of 192 rows (six wavefronts) or 256 (eight)
     // where those are at most 256.  Against 128x128 (16-bit dense: 256x256), us: 11008 x 333 x 4096 bf16, 258 tiles, 192
@@ -1079,7 +1080,7 @@ static sp24_status pick_tile_general(const MmArgs& a, hipStream_t st)
     // 9 and 18 steps 0.97 - 1.01 / 1.0 / 1.04 - 1.17 on average).
     // 8-bit products there run at the power limit: 4096 x 2048 x 4096 int8 takes 34.6 thousand clocks at 1.4 GHz on random operands
     // and 39 thousand at 2.3 GHz on zeros.  How the tiles compare then depends on the device, most of all with few steps: 256 rows
-    // against 128x128, averages over seven devices, dense int8 with 32-bit results 0.98 / 1.01 / 1.04 at 12 steps (one device 0.73 -
+    // against 128x128, averages over six or seven devices, dense int8 with 32-bit results 0.98 / 1.01 / 1.04 at 12 steps (one device 0.73 -
     // 1.02), 1.0 / 1.0 / 1.07 at 16, 1.04 / 1.05 / 1.11 at 24; sparse int8 with them 1.0 / 1.01 / 1.18 at 24 (one device 0.76 - 1.1 in the
     // caches), sparse 8-bit floats with 16-bit results 1.0 / 0.95 / 1.2 at 12 and 16 (three devices, 0.79 - 1.15 in the caches).
     const int64_t steps = a.K * (is8<DT> ? 1 : 2) / kRowBytes, tall = ((a.M + 255) / 256) * cols;
@@ -1101,7 +1102,8 @@ static sp24_status pick_tile_general(const MmArgs& a, hipStream_t st)
     const double cover_small = (double)(((a.M + 127) / 128) * 128) * (double)(((a.N + 127) / 128) * 128);
     if (big >= 129 && cover_big <= 1.35 * cover_small) return run_pipe<DT, OUT, 4, 2, 2, 4, 3, 2, kProducts | kConvs>(a, st);
     // At most 128 tiles of 128x128: twice as many of 128x64 (64x128), four wavefronts of 32x64 each.  A row of the compressed
-    // operand costs 80 bytes a step and a column 128, so the tall tile is the cheaper of the two (18.4 against 21.5 KB), and
+    // operand costs 80 or 72 bytes a step and a column 128, so the tall tile is the cheaper of the two (18.4 against 21.5 KB, 16-bit
+    // types 17.4 against 21.0), and
     // four wavefronts, one to a SIMD, issue a step's reads and transfers in half the time that two need: against 64x128
     // on two wavefronts (dense, N > 128: 128x128), 16 shapes per type, K 512 / 1024 / 4096, times as fast: bf16 1.12 - 1.24 /
     // 1.07 - 1.29 / 1.09 - 1.38 (2048 x 1024 x 4096 19.1 -> 16.8 us, from HBM 26.6 -> 21.4), int8 1.05 - 1.2 / 1.07 - 1.27 /
@@ -1136,8 +1138,10 @@ static sp24_status pick_tile_general(const MmArgs& a, hipStream_t st)
     // of 64x64, times as fast from the L2 / the last-level cache / HBM, dense bf16 on 132 - 176 tiles 1.01 - 1.16 / 0.99 -
     // 1.09 / 1.01 - 1.08 (2048 x 1152 x 1024 9.9 -> 8.6 us), int8 on 132 - 160 1.02 - 1.13 / 1.03 - 1.08 / 1.01 - 1.09;
     // convolutions (5x5, strided) on 154 - 210 tiles, sparse 0.99 - 1.08 (256 -> 256 channels, 28x28, stride 2, 55 images f16 17.4 -> 16.3 us), dense 1.0 -
-    // 1.12 (20.1 -> 18.2).  Beyond, eight wavefronts on nearly every unit cost clock: int8 2048 x 2048 x 1024 took 9.9 -> 16.5 us on
-    // some devices (on 176 tiles 8.1 -> 9.9 now and then), bf16 0.92 - 1.05, convolutions on 227 - 256 0.85 - 1.05.  The sparse
+    // 1.12 (20.1 -> 18.2).  Beyond, it depends on the device: int8 2048 x 2048 x 1024 K-major needs 15.1 thousand clocks on four and 11.2
+    // on eight, and takes 9.6 -> 8.1 us on two devices (2.2 GHz either way), but took 9.9 -> 16.5 back to back on the one that the
+    // lines were set on, for no cause that was found (on 176 tiles 8.1 -> 9.9 now and then; bf16 0.92 - 1.05, convolutions on 227 - 256
+    // 0.85 - 1.05).  The lines keep clear of that.  The sparse
     // product, whose A is read twice as often from LDS with half the rows to a wavefront, is level with eight (0.92 - 1.1), and an
     // 8-bit dense one with an N-major B 3 - 6 % slower.
     // Dense products split along K make several workgroups of a tile: eight wavefronts are 1.0 - 1.1 times as fast on up to 192
