@@ -226,6 +226,23 @@ sp24_status sp24_permute_search(const void* A, int32_t* perm, int64_t M, int64_t
                                 sp24_dtype t, int sweeps, void* stream);
 
 /*
+ * The same search, the same order found, on a copy of the matrix in `workspace`
+ * that lies column by column: about twice as fast.  workspace (device, 16-byte
+ * aligned, not overlapping A or perm; contents before the call are ignored,
+ * after it unspecified) holds sp24_permute_search_workspace_bytes(M, K, t)
+ * bytes, the matrix at two bytes an element with M rounded up to 512 and a
+ * few dozen bytes a column.  0 bytes (no rounds, an illegal shape or type, a
+ * matrix too large): the call is sp24_permute_search, and so it is with
+ * workspace NULL.  Errors as for sp24_permute_search, and SP24_ERR_ALIGN for a
+ * misaligned workspace, SP24_ERR_SHAPE for one that is too small or overlaps.
+ * Calls sharing one workspace must not overlap in time.
+ */
+size_t sp24_permute_search_workspace_bytes(int64_t M, int64_t K, sp24_dtype t);
+sp24_status sp24_permute_search_workspace(const void* A, int32_t* perm, int64_t M, int64_t K, int64_t lda,
+                                          sp24_dtype t, int sweeps, void* workspace,
+                                          size_t workspace_bytes, void* stream);
+
+/*
  * Sec. 6: a pattern that satisfies the 2:4 constraint along rows and along
  * columns, so that the transposed matrix (the backward pass) can use the
  * sparse product too.  The exhaustive search the paper names, per aligned

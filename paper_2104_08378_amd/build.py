@@ -18,7 +18,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsp24.so")
 HOST = os.path.join(HERE, "_sp24_host.so")      # native marshalling of the binding's calls (csrc/host_calls.cpp)
 PROBE = os.path.join(HERE, "sp24_probe")        # stand-alone measurement of the chip's ceilings (csrc/probe.hip)
-SOURCES = ["api.hip", "prune_compress.hip", "permute.hip", "permute_search.hip", "splitk.hip", "mm_simple.hip", "mm_ksplit.hip", "conv_narrow.hip", "mm_skinny.hip", "mm_stream.hip", "mm_tiled.hip", "mm_staged.hip",
+SOURCES = ["api.hip", "prune_compress.hip", "permute.hip", "permute_search.hip", "permute_search_columns.hip", "splitk.hip", "mm_simple.hip", "mm_ksplit.hip", "conv_narrow.hip", "mm_skinny.hip", "mm_stream.hip", "mm_tiled.hip", "mm_staged.hip",
            "mm_staged_f16.hip", "mm_staged_bf16.hip", "mm_staged_i8.hip", "mm_staged_f8.hip"] + [
     "mm_tiled_%s_%s.hip" % (i, o) for i, o in
     [("f16", "f32"), ("f16", "f16"), ("f16", "bf16"), ("bf16", "f32"), ("bf16", "f16"), ("bf16", "bf16"),

@@ -235,7 +235,7 @@ sp24_status sp24_retained_magnitude(const void* A, const int32_t* perm, double* 
     return launch_retained_magnitude(A, perm, total, M, K, lda, t, static_cast<hipStream_t>(stream));
 }
 
-sp24_status sp24_permute_search(const void* A, int32_t* perm, int64_t M, int64_t K, int64_t lda, sp24_dtype t, int sweeps, void* stream)
+static sp24_status check_permute_search(const void* A, const int32_t* perm, int64_t M, int64_t K, int64_t lda, sp24_dtype t, int sweeps)
 {
     if (!is_input_type(t)) return SP24_ERR_DTYPE;
     if (M < 0 || !k_legal(K, t) || K > 0x7FFFFFFF || sweeps < 0 || sweeps > 64) return SP24_ERR_SHAPE;
@@ -245,7 +245,32 @@ sp24_status sp24_permute_search(const void* A, int32_t* perm, int64_t M, int64_t
     if (!perm) return SP24_ERR_NULL;
     if (reinterpret_cast<uintptr_t>(perm) % 4 != 0) return SP24_ERR_ALIGN;
     if (M > 0 && ranges_overlap(A, ((size_t)(M - 1) * lda + K) * es, perm, (size_t)K * 4)) return SP24_ERR_SHAPE;
-    return launch_permute_search(A, perm, M, K, lda, t, sweeps, static_cast<hipStream_t>(stream));
+    return SP24_OK;
+}
+
+sp24_status sp24_permute_search(const void* A, int32_t* perm, int64_t M, int64_t K, int64_t lda, sp24_dtype t, int sweeps, void* stream)
+{
+    const sp24_status s = check_permute_search(A, perm, M, K, lda, t, sweeps);
+    return s != SP24_OK ? s : launch_permute_search(A, perm, M, K, lda, t, sweeps, static_cast<hipStream_t>(stream));
+}
+
+size_t sp24_permute_search_workspace_bytes(int64_t M, int64_t K, sp24_dtype t)
+{
+    return is_input_type(t) && M >= 0 && k_legal(K, t) && K <= 0x7FFFFFFF ? permute_search_workspace(M, K) : 0;
+}
+
+sp24_status sp24_permute_search_workspace(const void* A, int32_t* perm, int64_t M, int64_t K, int64_t lda, sp24_dtype t, int sweeps,
+                                          void* workspace, size_t workspace_bytes, void* stream)
+{
+    const sp24_status s = check_permute_search(A, perm, M, K, lda, t, sweeps);
+    if (s != SP24_OK) return s;
+    const size_t need = permute_search_workspace(M, K);
+    if (!workspace || need == 0) return launch_permute_search(A, perm, M, K, lda, t, sweeps, static_cast<hipStream_t>(stream));
+    if (reinterpret_cast<uintptr_t>(workspace) % 16 != 0) return SP24_ERR_ALIGN;
+    if (workspace_bytes < need || ranges_overlap(workspace, need, A, ((size_t)(M - 1) * lda + K) * esize_of(t)) ||
+        ranges_overlap(workspace, need, perm, (size_t)K * 4))
+        return SP24_ERR_SHAPE;
+    return launch_permute_search_columns(A, perm, M, K, lda, t, sweeps, workspace, static_cast<hipStream_t>(stream));
 }
 
 // Argument checks of every product entry point.  *empty: nothing to compute (M or N is 0).

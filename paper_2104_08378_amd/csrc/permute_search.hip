@@ -35,32 +35,11 @@
 
 #include "common.hpp"
 #include "launch.hpp"
+#include "permute_search.hpp"
 
 namespace sp24 {
 
 namespace {
-
-// The 35 ways in lexicographic order of (a, b, c), as bit masks of the positions a, b, c (1 .. 7; bit 0 for position 1),
-// nine to a word: read with shifts, not from memory.
-struct Ways {
-    uint64_t word[4];
-};
-constexpr Ways make_ways()
-{
-    Ways t{};
-    int n = 0;
-    for (int a = 1; a < 8; ++a)
-        for (int b = a + 1; b < 8; ++b)
-            for (int c = b + 1; c < 8; ++c, ++n) t.word[n / 9] |= (uint64_t)((1u << (a - 1)) | (1u << (b - 1)) | (1u << (c - 1))) << (7 * (n % 9));
-    return t;
-}
-
-// position of the i-th set bit
-__device__ __forceinline__ int nth_bit(uint32_t mask, int i)
-{
-    for (; i > 0; --i) mask &= mask - 1;
-    return __builtin_ctz(mask);
-}
 
 // magnitude of element `bits` as the type the row sums are formed in
 template <int DT>
@@ -78,10 +57,6 @@ __device__ __forceinline__ auto search_magnitude(uint32_t bits)
         return (f != f) ? (double)__builtin_inff() : (double)f;
     }
 }
-
-// (sums of magnitudes: never NaN)
-__device__ __forceinline__ int larger(int a, int b) { return a > b ? a : b; }
-__device__ __forceinline__ double larger(double a, double b) { return __builtin_fmax(a, b); }
 
 // One step of the halving: of L scores held, a lane with bit W of its number clear keeps the first half and adds its
 // partner's, the other keeps the second half; first, n: the number of the first score held, and how many are scores (the
@@ -114,7 +89,6 @@ __global__ __launch_bounds__(256) void k_permute_search_round(const uint8_t* __r
 {
     constexpr int ES = is8<DT> ? 1 : 2;
     using sum_t = typename std::conditional<DT == SP24_I8, int, double>::type;
-    constexpr Ways ways = make_ways();
     __shared__ double part[4][70];
     __shared__ int winner;
 
@@ -219,8 +193,7 @@ __global__ __launch_bounds__(256) void k_permute_search_round(const uint8_t* __r
     if (arg != 0 && threadIdx.x < 8) {
         // position threadIdx.x of the new arrangement: the winner's four positions, then the other four, ascending
         const int i = threadIdx.x;
-        const uint32_t three = (uint32_t)((arg < 9 ? ways.word[0] : arg < 18 ? ways.word[1] : arg < 27 ? ways.word[2] : ways.word[3]) >> (7 * (arg % 9))) & 127u;
-        const uint32_t mine = 1u | (three << 1);
+        const uint32_t mine = way_mask(arg);
         const int src = nth_bit(i < 4 ? mine : mine ^ 0xFFu, i & 3);
         int32_t c = 0;
 #pragma unroll

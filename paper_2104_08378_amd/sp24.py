@@ -61,6 +61,10 @@ def lib():
         L.sp24_retained_magnitude.argtypes = [vp, vp, vp, i64, i64, i64, i32, vp]
         L.sp24_permute_search.argtypes = [vp, vp, i64, i64, i64, i32, i32, vp]
         L.sp24_permute_search.restype = i32
+        L.sp24_permute_search_workspace_bytes.argtypes = [i64, i64, i32]
+        L.sp24_permute_search_workspace_bytes.restype = ctypes.c_size_t
+        L.sp24_permute_search_workspace.argtypes = [vp, vp, i64, i64, i64, i32, i32, vp, ctypes.c_size_t, vp]
+        L.sp24_permute_search_workspace.restype = i32
         L.sp24_spmm.argtypes = [vp, vp, vp, vp, i64, i64, i64, i64, i64, i32, i32, i32, i32, vp]
         L.sp24_gemm_dense.argtypes = [vp, vp, vp, i64, i64, i64, i64, i64, i64, i32, i32, i32, vp]
         L.sp24_splitk_workspace_bytes.argtypes = [i64, i64, i64, i32]
@@ -291,6 +295,18 @@ def sp24_retained_magnitude(A, perm=None, out=None):
     return total
 
 
+def _search_workspace(A):
+    """Room for the search's copy of A, or None where it works in place: shapes that need none, no memory left, and a
+    matrix on another device than the current one (whose allocator does not order the buffer with this stream)."""
+    need = lib().sp24_permute_search_workspace_bytes(A.shape[0], A.shape[1], _DT[A.dtype])
+    if need == 0 or A.device.index != torch.cuda.current_device():
+        return None
+    try:
+        return torch.empty(need, dtype=torch.uint8, device=A.device)
+    except torch.cuda.OutOfMemoryError:
+        return None
+
+
 def sp24_permute_search(A, sweeps=1, perm=None):
     """Search for a column order under which 2:4 pruning keeps more magnitude, starting from ``perm`` (refined in
     place; default: a new tensor holding 0, 1, 2, ...).  Returns the int32 device tensor of K column numbers."""
@@ -299,7 +315,10 @@ def sp24_permute_search(A, sweeps=1, perm=None):
     if perm is None:
         perm = torch.arange(K, dtype=torch.int32, device=A.device)
     _perm_arg(perm, K)
-    _check(lib().sp24_permute_search(A.data_ptr(), perm.data_ptr(), M, K, A.stride(0), _DT[A.dtype], int(sweeps), _stream()),
+    workspace = _search_workspace(A) if int(sweeps) > 0 else None
+    _check(lib().sp24_permute_search_workspace(A.data_ptr(), perm.data_ptr(), M, K, A.stride(0), _DT[A.dtype], int(sweeps),
+                                               workspace.data_ptr() if workspace is not None else None,
+                                               workspace.numel() if workspace is not None else 0, _stream()),
            "sp24_permute_search")
     return perm
 

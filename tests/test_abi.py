@@ -300,6 +300,22 @@ def test_permute_search_validation():
     assert f(A, PERM, 64, 64, 64, sp24.F16, 0, None) == OK              # no sweeps: nothing launched
 
 
+def test_permute_search_workspace_validation():
+    L, A, PERM, WS = sp24.lib(), P, P + 0x4000000, P + 0x8000000
+    f, need = L.sp24_permute_search_workspace, L.sp24_permute_search_workspace_bytes(64, 64, sp24.F16)
+    assert need >= 64 * 512 * 2
+    for bad in ((0, 64, sp24.F16), (-1, 64, sp24.F16), (64, 40, sp24.F16), (64, 64, sp24.F32), (64, 0, sp24.F16), (1 << 40, 64, sp24.I8)):
+        assert L.sp24_permute_search_workspace_bytes(*bad) == 0
+    assert f(A, 0, 64, 64, 64, sp24.F16, 1, WS, need, None) == NULL
+    assert f(A, PERM, 64, 40, 64, sp24.F16, 1, WS, need, None) == SHAPE
+    assert f(A, PERM, 64, 64, 64, sp24.F16, 1, WS + 8, need, None) == ALIGN
+    assert f(A, PERM, 64, 64, 64, sp24.F16, 1, WS, need - 1, None) == SHAPE
+    assert f(A, PERM, 64, 64, 64, sp24.F16, 1, A + 4096, need, None) == SHAPE        # the workspace inside A
+    assert f(A, PERM, 64, 64, 64, sp24.F16, 1, PERM - 1024, need, None) == SHAPE
+    assert f(A, PERM, 0, 64, 64, sp24.F16, 3, WS, need, None) == OK
+    assert f(A, PERM, 64, 64, 64, sp24.F16, 0, WS, need, None) == OK
+
+
 @pytest.mark.parametrize("contents", [None, b"", b"not a shared object"])
 def test_without_the_native_half_the_python_code_takes_the_calls(monkeypatch, tmp_path, contents):
     """_sp24_host.so missing, or not loadable by this interpreter and torch: one warning, and the call goes on to the Python

@@ -180,6 +180,24 @@ def test_permute_search_of_a_large_matrix_from_any_order(dtype, K):
     assert np.array_equal(got.cpu().numpy(), oracle.permute_search(A, dtype, sweeps=1, perm=start))
 
 
+# one, two and four workgroups to a pair of groups (from 258 groups on, 130, 2) at the edges of the copy's blocks of 512 rows
+# and of their halves; int8 sums past what 16 bits hold; the search in place and the one on a copy find the same order
+@pytest.mark.parametrize("dtype,M,K", [("bf16", 256, 512), ("f16", 257, 528), ("f8", 513, 544), ("i8", 1024, 1024), ("bf16", 1537, 1040),
+                                       ("f16", 2048, 1040), ("i8", 769, 1056), ("i8", 130_600, 32)])
+def test_permute_search_in_place_and_on_a_copy(dtype, M, K):
+    A = adversarial(dtype, M, K, 210) if dtype != "f8" else synth.f64_to_f8_bits(np.random.default_rng(210).standard_normal((M, K)))
+    if M > 100_000:
+        A = np.where(A % 3, np.int8(-128), A)                    # the largest magnitude in most places
+    Ad, lib = to_gpu(A, dtype), sp24.lib()
+    start = np.random.default_rng(211).permutation(K).astype(np.int32)
+    copied, placed = sp24.sp24_permute_search(Ad, sweeps=2, perm=dev_perm(start)), dev_perm(start)
+    assert lib.sp24_permute_search_workspace_bytes(M, K, sp24._DT[Ad.dtype]) > 0
+    assert lib.sp24_permute_search(Ad.data_ptr(), placed.data_ptr(), M, K, K, sp24._DT[Ad.dtype], 2, sp24._stream()) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(copied, placed)
+    assert np.array_equal(copied.cpu().numpy(), oracle.permute_search(A, dtype, sweeps=2, perm=start))
+
+
 def test_permute_search_starts_from_a_given_order_and_takes_pitched_rows():
     dtype, M, K = "bf16", 500, 96
     A = synth.make(NAME_OF[dtype], M=M, N=16, K=K, seed=181)[0]
