@@ -549,7 +549,7 @@ static sp24_status mm_splitk(const MmArgs& a, void* workspace, size_t workspace_
         // The unsplit product has one workgroup on each tile of 32 rows already, which takes 40 ns (N <= 32) or 100 ns per
         // 128-byte step whatever their number; of the plan's slices as many as find a unit of their own and as the
         // images are worth (written and read at 4 TB/s).  Against the plan's slices on the tiled or the streaming kernel:
-        // 1000 x 64 x 2048 f16 13.4 -> 8.4 us, 512 x 16 x 16384 bf16 10.1 -> 9.1, 1024 x 128 x 4096 12.5 -> 9.3.
+        // 512 x 16 x 16384 bf16 10.1 -> 9.1 us, 1024 x 128 x 4096 12.5 -> 9.3.
         const int64_t steps = a.K * es / 128, steps_ns = steps * (a.N <= 32 ? 40 : 100), image_ns = a.M * plan.ldw / 500;
         const int most = (int)std::min<int64_t>(plan.slices, 256 / stream_workgroups(a));
         int n = most <= 1 ? 1 : 2;
@@ -565,7 +565,13 @@ static sp24_status mm_splitk(const MmArgs& a, void* workspace, size_t workspace_
         // Operands in the last-level cache favour the kernel at one and two slices by some 10 % more.  The tiled kernels are slower
         // on a canonical operand: one slice of it is level at 128 steps, and two stay 9 % and more ahead as far as measured
         // (1000 x 200 x 20480 bf16 29.8 against 37.6).
+        // Few steps are not worth the second kernel and the images: past 32 columns the unsplit product is ahead up to 40 steps, of a
+        // canonical operand up to 32 (us, unsplit / split, operands in the caches, then from HBM; ten shapes of 256 - 2048 rows each:
+        // 24 steps 5.3 - 6.1 / 7.4 - 8.1, 6.4 - 7.3 / 8.5 - 10.4; 32 5.8 - 6.7 / 8.0 - 8.7, 6.9 - 8.2 / 8.7 - 9.9; 48 tiled 6.9 - 8.6 / 8.3 - 9.3, 8.2 - 11.4 /
+        // 9.1 - 10.4, canonical 7.7 - 9.8 / 8.3 - 9.6, 9.6 - 12.7 / 9.1 - 10.7; 64 7.9 - 11.7 / 8.5 - 10.6, 9.0 - 16.1 / 9.4 - 11.5).
+        // 1000 x 64 x 2048 f16, canonical: 8.3 -> 6.6.
         const bool canonical = a.layout == SP24_LAYOUT_CANONICAL;
+        if (a.N > 32 && steps <= (canonical ? 32 : 40)) n = 1;
         int64_t longest = steps;
         if (a.N > 32 && n <= (a.N <= 64 ? 3 : 2)) {
             if (n == 1) longest = canonical ? 128 : 104;
