@@ -361,7 +361,18 @@ static bool tiled_before_streaming(const MmArgs& a)
 // agree bit for bit; narrower ones have not agreed since this kernel takes them, and the interface promises neither.
 static bool stream_first(const MmArgs& a)
 {
-    if (!a.sparse || a.conv.on || a.bo != SP24_B_KMAJOR || a.N > 512) return false;
+    if (!a.sparse || a.conv.on) return false;
+    // An N-major B whose rows the transfers can fetch: the same rule without the limit of 512 columns.  Against the tiled kernels, times as fast
+    // from the caches / from HBM, 18 shapes of 32 - 8192 rows and 16 - 4096 columns, 2 - 128 steps: tiled layout bf16 1.13 - 2.9 / 1.1 - 2.6 (1024 x 512 x
+    // 4096 15.4 -> 11.7 us, 512 x 128 x 8192 from HBM 37.4 -> 21.0), int8 1.0 - 3.0 / 1.02 - 2.5 (1024 x 512 x 4096 11.2 -> 9.4); canonical
+    // from 8 steps on 0.99 - 2.1 / 1.0 - 2.6 and 1.04 - 2.5 / 1.02 - 2.2, with fewer 0.92 - 1.09.  On 257 - 512 workgroups 0.63 - 1.04, canonical
+    // 16-bit operands of 32 steps and more 0.94 - 1.25.
+    if (a.bo == SP24_B_NMAJOR) {
+        const int64_t es = esize_of(a.in), steps = a.K * es / 128;
+        const bool whole_chunks = reinterpret_cast<uintptr_t>(a.B) % 16 == 0 && a.ldb * es % 16 == 0 && a.N * es % 16 == 0;
+        return whole_chunks && steps >= (a.layout == SP24_LAYOUT_CANONICAL ? 8 : 2) && stream_workgroups(a) <= 256;
+    }
+    if (a.N > 512) return false;
     // Few steps of an 8-bit operand: a wavefront has one at most, and the partial step at the end of K comes behind it.  With
     // N <= 32 the streaming kernel is 5 - 17 % ahead below four whole steps, and below eight where the last is a partial one
     // (33 - 8192 rows, replayed: K = 64 2.6 - 3.0 us against 3.0 - 3.5, 192 2.7 - 3.1 against 3.0 - 3.4, 576 2.9 - 3.6 against
@@ -564,19 +575,21 @@ static sp24_status mm_splitk(const MmArgs& a, void* workspace, size_t workspace_
         // and more always (256 x 500 x 40960 1.41 times as fast, 128 x 512 2.1 times).
         // Operands in the last-level cache favour the kernel at one and two slices by some 10 % more.  The tiled kernels are slower
         // on a canonical operand: one slice of it is level at 128 steps, and two stay 9 % and more ahead as far as measured
-        // (1000 x 200 x 20480 bf16 29.8 against 37.6).
+        // (1000 x 200 x 20480 bf16 29.8 against 37.6).  An 8-bit N-major B in two slices of the tiled layout: 48 steps each 3 - 5 % ahead, 64 2 - 5 %
+        // behind (1024 x 192 x 16384).
         // Few steps are not worth the second kernel and the images: past 32 columns the unsplit product is ahead up to 40 steps, of a
         // canonical operand up to 32 (us, unsplit / split, operands in the caches, then from HBM; ten shapes of 256 - 2048 rows each:
         // 24 steps 5.3 - 6.1 / 7.4 - 8.1, 6.4 - 7.3 / 8.5 - 10.4; 32 5.8 - 6.7 / 8.0 - 8.7, 6.9 - 8.2 / 8.7 - 9.9; 48 tiled 6.9 - 8.6 / 8.3 - 9.3, 8.2 - 11.4 /
         // 9.1 - 10.4, canonical 7.7 - 9.8 / 8.3 - 9.6, 9.6 - 12.7 / 9.1 - 10.7; 64 7.9 - 11.7 / 8.5 - 10.6, 9.0 - 16.1 / 9.4 - 11.5).
-        // 1000 x 64 x 2048 f16, canonical: 8.3 -> 6.6.
+        // 1000 x 64 x 2048 f16, canonical: 8.3 -> 6.6.  N-major: the line of the tiled kernels below (32 steps 5.8 - 6.5 / 8.1 - 9.2; 48 7.0 - 8.5 / 8.1 - 9.2,
+        // from HBM 8.1 - 8.5 / 8.5 - 9.2).
         const bool canonical = a.layout == SP24_LAYOUT_CANONICAL;
-        if (a.N > 32 && steps <= (canonical ? 32 : 40)) n = 1;
+        if (a.N > 32 && steps <= (a.bo == SP24_B_NMAJOR ? (es == 2 ? 32 : 31) : canonical ? 32 : 40)) n = 1;
         int64_t longest = steps;
         if (a.N > 32 && n <= (a.N <= 64 ? 3 : 2)) {
             if (n == 1) longest = canonical ? 128 : 104;
             else if (canonical) longest = 256;
-            else longest = n == 3 ? 96 : a.N <= 64 ? 72 : 88;
+            else longest = n == 3 ? 96 : a.N <= 64 ? 72 : a.bo == SP24_B_NMAJOR && es == 1 ? 56 : 88;
         }
         if (steps <= longest * n) {
             if (n == 1) return mm_dispatch(a, st);

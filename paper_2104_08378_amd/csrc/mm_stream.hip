@@ -13,6 +13,11 @@
 // cache (4.2 TB/s); every workgroup reads all of B besides, 268 MB from the L2, so that a unit brings in 48 and 73 GB/s.
 // 8192 x 16 x 8192: 76 MB in 16.4 us from HBM (4.6 TB/s).  Measured and not kept: the compressed operand marked as passing once (nt), which
 // helps loads into registers, costs these transfers 10 - 60 % (512 x 16 x 16384: 13.2 -> 21.2 us).
+//
+// NMAJ: B N-major, rows of whole 16-byte chunks: a transfer takes the tile's columns of as many K rows as 1 KiB holds, and fragments
+// come through the transposing LDS reads of the tiled kernels.  Those had these products on 32 x 64 to 128 x 64 tiles before, a step
+// behind a barrier each and fewer than half of the units at work: 1024 x 512 x 4096 bf16 15.4 -> 11.7 us, int8 11.2 -> 9.4, 1024 x 16 x 8192
+// bf16 20.0 -> 7.8 (K-major 6.8), 512 x 128 x 8192 from HBM 37.4 -> 21.0.
 #include "mm_operands.hpp"
 
 namespace sp24 {
@@ -31,7 +36,7 @@ __device__ __forceinline__ void count_down(F&& f)
 
 } // namespace
 
-template <int DT, int BR, int NW, int NS>
+template <int DT, int BR, int NW, int NS, bool NMAJ>
 __global__ __launch_bounds__(64 * NW) void k_spmm_stream(MmArgs a, int tiles_m, int tiles_n)
 {
     constexpr int ES = is8<DT> ? 1 : 2;
@@ -63,9 +68,11 @@ __global__ __launch_bounds__(64 * NW) void k_spmm_stream(MmArgs a, int tiles_m, 
 
     // ---- transfers: base address of the tile (the same in all lanes), the lane's offset ----
     const int64_t ldb = a.ldb * ES, n0 = (int64_t)tn * BR;
-    const uint8_t* const b_base = reinterpret_cast<const uint8_t*>(a.B) + n0 * ldb;
+    const uint8_t* const b_base = reinterpret_cast<const uint8_t*>(a.B) + (NMAJ ? n0 * ES : n0 * ldb);
+    const int64_t b_step = NMAJ ? (kRowBytes / ES) * ldb : (int64_t)kRowBytes;
     uint32_t b_off[NB];
-    dma_offsets<BR, 1>(n0, a.N, ldb, 0, lane, b_off);
+    if constexpr (NMAJ) dma_offsets_nmajor<BR, 1, ES>(n0, a.N, ldb, 0, lane, b_off);
+    else dma_offsets<BR, 1>(n0, a.N, ldb, 0, lane, b_off);
     const bool canonical = a.layout == SP24_LAYOUT_CANONICAL;
     const int64_t vrow = a.K / 2 * ES, mrow = a.K / 8, KB64 = a.K / 64;
     const uint8_t* v_base = reinterpret_cast<const uint8_t*>(a.A) + (canonical ? (int64_t)tm * 32 * vrow : tm * KB64 * (1024 * ES));
@@ -93,7 +100,7 @@ __global__ __launch_bounds__(64 * NW) void k_spmm_stream(MmArgs a, int tiles_m, 
 #pragma unroll
         for (int t = 0; t < T64; ++t) lds_dma4(m_base + (int64_t)step * m_step, m_off[t], stage + kMOff + t * 256);
 #pragma unroll
-        for (int j = 0; j < NB; ++j) lds_dma16(b_base + (int64_t)step * kRowBytes, b_off[j], stage + j * 1024);
+        for (int j = 0; j < NB; ++j) lds_dma16(b_base + step * b_step, b_off[j], stage + j * 1024);
     };
     // the partial step: what lies past K comes from the row of zeros
     auto fetch_tail = [&](int step) {
@@ -107,7 +114,8 @@ __global__ __launch_bounds__(64 * NW) void k_spmm_stream(MmArgs a, int tiles_m, 
                                ring + kMOff + t * 256);
 #pragma unroll
         for (int j = 0; j < NB; ++j)
-            lds_dma_tail<false>(b_base + (int64_t)step * kRowBytes, b_off[j], past_k_kmajor<BR, 1>(j, 0, lane, tail), ring + j * 1024);
+            lds_dma_tail<false>(b_base + step * b_step, b_off[j],
+                                NMAJ ? past_k_nmajor<BR, 1, ES>(j, 0, lane, tail) : past_k_kmajor<BR, 1>(j, 0, lane, tail), ring + j * 1024);
     };
 
     // ---- operand reads: values of instruction j, and the two pieces of B (as in the tiled kernels) ----
@@ -123,6 +131,8 @@ __global__ __launch_bounds__(64 * NW) void k_spmm_stream(MmArgs a, int tiles_m, 
     const int br = BR == 16 ? r & 15 : r;             // 16 columns: the upper half computes them again, never stored
 #pragma unroll
     for (int c2 = 0; c2 < 4; ++c2) frag_off[c2] = br * kRowBytes + ((((2 * c2) | q) ^ ((br >> 1) & 7)) << 4);
+    nmajor_frags<BR, TN, ES> b_nm;
+    if constexpr (NMAJ) b_nm.init(0, BR == 16 ? lane & ~16 : lane);
 
     // Floats: two sums of each element, one per half of a step, added at the end, which leaves half the roundings in each (with the sums
     // in pairs below, 1000 x 64 x 2048 f16: relative error 9.7e-8 -> 8.0e-8, split in four slices 8.1e-8; times unchanged)
@@ -143,8 +153,13 @@ __global__ __launch_bounds__(64 * NW) void k_spmm_stream(MmArgs a, int tiles_m, 
 #pragma unroll
             for (int nj = 0; nj < TN; ++nj) {
                 const int c2lo = is8<DT> ? 2 * j : j, c2hi = is8<DT> ? 2 * j + 1 : 2 + j;
-                lo[j][nj] = *reinterpret_cast<const uint4v*>(stage + frag_off[c2lo] + nj * 32 * kRowBytes);
-                hi[j][nj] = *reinterpret_cast<const uint4v*>(stage + frag_off[c2hi] + nj * 32 * kRowBytes);
+                if constexpr (NMAJ) {
+                    lo[j][nj] = b_nm.piece(stage, c2lo, nj);
+                    hi[j][nj] = b_nm.piece(stage, c2hi, nj);
+                } else {
+                    lo[j][nj] = *reinterpret_cast<const uint4v*>(stage + frag_off[c2lo] + nj * 32 * kRowBytes);
+                    hi[j][nj] = *reinterpret_cast<const uint4v*>(stage + frag_off[c2hi] + nj * 32 * kRowBytes);
+                }
             }
 #pragma unroll
         for (int j = 0; j < 2; ++j)
@@ -226,7 +241,7 @@ __global__ __launch_bounds__(64 * NW) void k_spmm_stream(MmArgs a, int tiles_m, 
     }
 }
 
-template <int DT>
+template <int DT, bool NMAJ>
 static sp24_status run_stream(const MmArgs& a, hipStream_t st)
 {
     const int br = stream_columns(a);
@@ -237,26 +252,31 @@ static sp24_status run_stream(const MmArgs& a, hipStream_t st)
     };
     // As many wavefronts as the LDS holds with two or more stages each.  Eight of 4 (N <= 16) and 3 stages (N <= 32) are
     // ahead of 16 x 2, 10 x 3, 12 x 2, 6 x 4 and 4 x 8 by 1 - 20 %; for 64 columns 7 x 2 of 5 x 3, 4 x 3 and 3 x 5 by 1 - 15 %
-    if (br == 16) return run(k_spmm_stream<DT, 16, 8, 4>, 8);
-    if (br == 32) return run(k_spmm_stream<DT, 32, 8, 3>, 8);
-    return run(k_spmm_stream<DT, 64, 7, 2>, 7);
+    if (br == 16) return run(k_spmm_stream<DT, 16, 8, 4, NMAJ>, 8);
+    if (br == 32) return run(k_spmm_stream<DT, 32, 8, 3, NMAJ>, 8);
+    return run(k_spmm_stream<DT, 64, 7, 2, NMAJ>, 7);
 }
 
 sp24_status launch_mm_stream(const MmArgs& a, hipStream_t st, bool* handled)
 {
     *handled = false;
     const int es = esize_of(a.in);
-    bool ok = a.sparse && !a.conv.on && a.bo == SP24_B_KMAJOR && (reinterpret_cast<uintptr_t>(a.B) & 15u) == 0 && (a.ldb * es) % 16 == 0 &&
+    const bool nmajor = a.bo == SP24_B_NMAJOR;
+    bool ok = a.sparse && !a.conv.on && (reinterpret_cast<uintptr_t>(a.B) & 15u) == 0 && (a.ldb * es) % 16 == 0 && (!nmajor || a.N * es % 16 == 0) &&
               a.M <= ((int64_t)1 << 30) && a.N <= ((int64_t)1 << 30) && ((a.M + 31) / 32) * ((a.N + 15) / 16) < ((int64_t)1 << 30) &&
-              a.K <= ((int64_t)1 << 24);                   // 32-bit offsets inside a tile: 64 rows of B, 32 rows of values
-    ok = ok && a.ldb * es < ((int64_t)1 << 25);
+              a.K <= ((int64_t)1 << 24);                   // 32-bit offsets inside a tile: 64 rows of B (N-major: up to 128), 32 rows of values
+    ok = ok && a.ldb * es < (nmajor ? (int64_t)1 << 24 : (int64_t)1 << 25);
     if (a.layout == SP24_LAYOUT_CANONICAL) ok = ok && a.K % 32 == 0;      // codes as 4-byte words
     if (!ok) return SP24_OK;
     *handled = true;
-    if (a.in == SP24_I8) return run_stream<SP24_I8>(a, st);
-    if (a.in == SP24_F8) return run_stream<SP24_F8>(a, st);
-    if (a.in == SP24_F16) return run_stream<SP24_F16>(a, st);
-    return run_stream<SP24_BF16>(a, st);
+    auto run = [&](auto dt) {
+        constexpr int DT = decltype(dt)::value;
+        return nmajor ? run_stream<DT, true>(a, st) : run_stream<DT, false>(a, st);
+    };
+    if (a.in == SP24_I8) return run(std::integral_constant<int, SP24_I8>{});
+    if (a.in == SP24_F8) return run(std::integral_constant<int, SP24_F8>{});
+    if (a.in == SP24_F16) return run(std::integral_constant<int, SP24_F16>{});
+    return run(std::integral_constant<int, SP24_BF16>{});
 }
 
 } // namespace sp24
