@@ -222,20 +222,24 @@ __global__ void k_zero_double(double* out) { *out = 0.0; }
 
 // out += sum over this workgroup's rows and all groups g of the two largest magnitudes among columns
 // perm[4g] .. perm[4g+3] (the selection rule of sp24_prune: ties to the lower position, NaN highest).
-template <int DT>
-__global__ __launch_bounds__(64 * kPermWaves) void k_retained_magnitude(const uint8_t* A, const int32_t* perm, double* out, int64_t M, int64_t K,
+//
+// The workgroups' sums meet at one address, some 10 ns each one behind the other whatever the matrix: as many wavefronts to a
+// workgroup (16, 8 or 4) as their rows find room for in LDS, and as few workgroups.  4096 x 1024 bf16: 512 of four 12.0 us, 256 of eight 9.1,
+// 128 of sixteen 8.0, without that addition 6.8; 4096 x 8192 int8, call to call, 28.5 -> 25.1 with eight; 8192 x 8192 bf16 66.7 -> 58.0.
+template <int DT, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_retained_magnitude(const uint8_t* A, const int32_t* perm, double* out, int64_t M, int64_t K,
                                                                         int64_t lda)
 {
     constexpr int ES = is8<DT> ? 1 : 2;
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];   // staged: the order (2 K bytes), then kPermWaves rows
-    __shared__ double partial[kPermWaves];
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];   // staged: the order (2 K bytes), then WAVES rows
+    __shared__ double partial[WAVES];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const bool staged = K * ES <= kPermRowBytes;
     const StagedOrder in_lds = {(lds_order)lds};
     const PlainOrder in_memory = {perm, K};
     const lds_row region = (lds_row)lds + (2 * K + wave * K * ES);
     double sum = 0.0;
-    const int64_t first = (int64_t)blockIdx.x * kPermWaves + wave, stride = (int64_t)gridDim.x * kPermWaves;
+    const int64_t first = (int64_t)blockIdx.x * WAVES + wave, stride = (int64_t)gridDim.x * WAVES;
     if (perm == nullptr) {
         // the given order: every group lies in place, nothing to stage or gather; eight loads in flight per lane
         const int64_t chunks = K * ES / 16;
@@ -278,7 +282,7 @@ __global__ __launch_bounds__(64 * kPermWaves) void k_retained_magnitude(const ui
     __syncthreads();
     if (threadIdx.x == 0) {
         double s = 0.0;
-        for (int w = 0; w < kPermWaves; ++w) s += partial[w];
+        for (int w = 0; w < WAVES; ++w) s += partial[w];
         atomicAdd(out, s);
     }
 }
@@ -323,11 +327,12 @@ static size_t staged_lds_bytes(int64_t K, int es)
     return K * es <= kPermRowBytes ? (size_t)(2 * K + kPermWaves * K * es) : 0;
 }
 constexpr int kPermMaxLds = 2 * kPermRowBytes + kPermWaves * kPermRowBytes;   // int8 rows of 16384 columns
+constexpr int kKeptMaxLds = 150 * 1024;                                       // of a workgroup of eight
 
 template <typename KERNEL>
-static bool allow_lds(KERNEL kernel)
+static bool allow_lds(KERNEL kernel, int bytes = kPermMaxLds)
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kPermMaxLds) == hipSuccess;
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
 }
 
 sp24_status launch_permute_columns(const void* A, const void* perm, void* P, int64_t M, int64_t K, int64_t lda, int64_t ldp, sp24_dtype t,
@@ -358,22 +363,35 @@ sp24_status launch_permute_rows(const void* A, const void* perm, void* P, int64_
     return launch_result();
 }
 
+// out += the total; 2048 wavefronts at most, in workgroups of 16 (two to a unit, 80 KiB each), 8 or 4
+template <int DT>
+static sp24_status retained_magnitude(const void* A, const void* perm, double* out, int64_t M, int64_t K, int64_t lda, hipStream_t st)
+{
+    constexpr int ES = is8<DT> ? 1 : 2;
+    auto run = [&](auto waves) {
+        constexpr int WAVES = decltype(waves)::value;
+        static const bool ready = allow_lds(k_retained_magnitude<DT, WAVES>, kKeptMaxLds);
+        if (!ready) return SP24_ERR_LAUNCH;
+        const int64_t passes = (M + WAVES - 1) / WAVES;
+        const size_t lds = perm && K * ES <= kPermRowBytes ? (size_t)(2 * K + WAVES * K * ES) : 0;   // the given order needs no staging
+        k_retained_magnitude<DT, WAVES><<<dim3((unsigned)(passes < 2048 / WAVES ? passes : 2048 / WAVES)), dim3(64 * WAVES), lds, st>>>(
+            static_cast<const uint8_t*>(A), static_cast<const int32_t*>(perm), out, M, K, lda);
+        return launch_result();
+    };
+    if (perm && 2 * K + 16 * K * ES <= 80 * 1024) return run(std::integral_constant<int, 16>{});
+    if (perm && 2 * K + 8 * K * ES <= kKeptMaxLds) return run(std::integral_constant<int, 8>{});
+    return run(std::integral_constant<int, kPermWaves>{});
+}
+
 sp24_status launch_retained_magnitude(const void* A, const void* perm, double* out, int64_t M, int64_t K, int64_t lda, sp24_dtype t,
                                       hipStream_t st)
 {
-    static const bool ready = allow_lds(k_retained_magnitude<SP24_F16>) && allow_lds(k_retained_magnitude<SP24_BF16>) &&
-                              allow_lds(k_retained_magnitude<SP24_I8>) && allow_lds(k_retained_magnitude<SP24_F8>);
-    if (!ready) return SP24_ERR_LAUNCH;
     k_zero_double<<<1, 1, 0, st>>>(out);
     if (M * K != 0) {
-        const dim3 grid(grid_for_rows(M)), block(64 * kPermWaves);
-        const uint8_t* a = static_cast<const uint8_t*>(A);
-        const int32_t* p = static_cast<const int32_t*>(perm);
-        const size_t lds = p ? staged_lds_bytes(K, esize_of(t)) : 0;   // the given order needs no staging
-        if (t == SP24_F16) k_retained_magnitude<SP24_F16><<<grid, block, lds, st>>>(a, p, out, M, K, lda);
-        else if (t == SP24_BF16) k_retained_magnitude<SP24_BF16><<<grid, block, lds, st>>>(a, p, out, M, K, lda);
-        else if (t == SP24_F8) k_retained_magnitude<SP24_F8><<<grid, block, lds, st>>>(a, p, out, M, K, lda);
-        else k_retained_magnitude<SP24_I8><<<grid, block, lds, st>>>(a, p, out, M, K, lda);
+        if (t == SP24_F16) return retained_magnitude<SP24_F16>(A, perm, out, M, K, lda, st);
+        if (t == SP24_BF16) return retained_magnitude<SP24_BF16>(A, perm, out, M, K, lda, st);
+        if (t == SP24_F8) return retained_magnitude<SP24_F8>(A, perm, out, M, K, lda, st);
+        return retained_magnitude<SP24_I8>(A, perm, out, M, K, lda, st);
     }
     return launch_result();
 }

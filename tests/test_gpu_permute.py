@@ -111,6 +111,16 @@ def test_retained_magnitude_matches_the_oracle(dtype):
     assert cell.item() == 0.0
 
 
+@pytest.mark.parametrize("dtype,M,K", [("bf16", 37, 2400), ("f16", 37, 2416), ("i8", 100, 4544), ("i8", 100, 4576), ("bf16", 2051, 64),
+                                       ("i8", 41, 15360), ("i8", 41, 15392)])
+def test_retained_magnitude_on_both_sides_of_the_workgroup_sizes(dtype, M, K):
+    """Rows that 16, 8 or 4 wavefronts to a workgroup find room for, and more rows than one pass takes."""
+    A = synth.make(NAME_OF[dtype], M=M, N=16, K=K, seed=K)[0]
+    perm = np.random.default_rng(K).permutation(K).astype(np.int32)
+    got = sp24.sp24_retained_magnitude(to_gpu(A, dtype), dev_perm(perm))
+    assert got.item() == pytest.approx(oracle.retained_magnitude(A, dtype, perm=perm), rel=1e-12)      # exact terms, any order
+
+
 def test_joint_permutation_leaves_the_dense_product_unchanged():
     """Sec. 4.1 Step 2: columns of A and rows of B (the columns of a K-major B) permuted alike -- same product.  Exact
     for int8; checked on the GPU's own dense product."""
