@@ -365,12 +365,14 @@ static bool stream_first(const MmArgs& a)
     // An N-major B whose rows the transfers can fetch: the same rule without the limit of 512 columns.  Against the tiled kernels, times as fast
     // from the caches / from HBM, 18 shapes of 32 - 8192 rows and 16 - 4096 columns, 2 - 128 steps: tiled layout bf16 1.13 - 2.9 / 1.1 - 2.6 (1024 x 512 x
     // 4096 15.4 -> 11.7 us, 512 x 128 x 8192 from HBM 37.4 -> 21.0), int8 1.0 - 3.0 / 1.02 - 2.5 (1024 x 512 x 4096 11.2 -> 9.4); canonical
-    // from 8 steps on 0.99 - 2.1 / 1.0 - 2.6 and 1.04 - 2.5 / 1.02 - 2.2, with fewer 0.92 - 1.09.  On 257 - 512 workgroups 0.63 - 1.04, canonical
-    // 16-bit operands of 32 steps and more 0.94 - 1.25.
+    // from 8 steps on 0.99 - 2.1 / 1.0 - 2.6 and 1.04 - 2.5 / 1.02 - 2.2, with fewer 0.92 - 1.09.  On 257 - 512 workgroups 0.63 - 1.04, except for
+    // canonical 16-bit operands, past 32 columns and from 32 steps on: 1.02 - 1.20 / 1.03 - 1.25 (4096 x 192 x 2048 14.1 -> 13.0, from HBM 16.7 -> 13.9).
     if (a.bo == SP24_B_NMAJOR) {
         const int64_t es = esize_of(a.in), steps = a.K * es / 128;
         const bool whole_chunks = reinterpret_cast<uintptr_t>(a.B) % 16 == 0 && a.ldb * es % 16 == 0 && a.N * es % 16 == 0;
-        return whole_chunks && steps >= (a.layout == SP24_LAYOUT_CANONICAL ? 8 : 2) && stream_workgroups(a) <= 256;
+        const bool canonical = a.layout == SP24_LAYOUT_CANONICAL;
+        const int most = canonical && es == 2 && a.N > 32 && steps >= 32 ? 512 : 256;
+        return whole_chunks && steps >= (canonical ? 8 : 2) && stream_workgroups(a) <= most;
     }
     if (a.N > 512) return false;
     // Few steps of an 8-bit operand: a wavefront has one at most, and the partial step at the end of K comes behind it.  With
@@ -556,7 +558,7 @@ static sp24_status mm_splitk(const MmArgs& a, void* workspace, size_t workspace_
     part.k_slices = plan.slices;
     part.slice_steps = plan.slice_steps;
     bool handled = false;
-    if (stream_first(a)) {
+    if (stream_first(a) && (a.bo == SP24_B_KMAJOR || stream_workgroups(a) <= 256)) {
         // The unsplit product has one workgroup on each tile of 32 rows already, which takes 40 ns (N <= 32) or 100 ns per
         // 128-byte step whatever their number; of the plan's slices as many as find a unit of their own and as the
         // images are worth (written and read at 4 TB/s).  Against the plan's slices on the tiled or the streaming kernel:
