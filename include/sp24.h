@@ -321,9 +321,8 @@ sp24_status sp24_gemm_dense(const void* A, const void* B, void* D, int64_t M, in
  * call are ignored, contents after it unspecified), or 0 when the shape would
  * not be split (or is not legal).  With 0 the call is sp24_spmm /
  * sp24_gemm_dense and `workspace` may be NULL; with more it is all the same that call for operands the
- * tiled and streaming kernels do not take (alignment of B; N <= 32 with an
- * N-major B), for shapes whose unsplit tiles occupy the chip and for compressed operands in the tiled
- * layout that are faster unsplit (few steps of K).  Errors as for sp24_spmm, and
+ * tiled and streaming kernels do not take (alignment of B), for shapes whose unsplit tiles occupy the chip and for compressed operands that
+ * are faster unsplit (few steps of K).  Errors as for sp24_spmm, and
  * SP24_ERR_NULL / SP24_ERR_ALIGN for a missing or misaligned workspace,
  * SP24_ERR_SHAPE when workspace_bytes is too small or it overlaps an operand.
  * Calls sharing one workspace must not overlap in time.
