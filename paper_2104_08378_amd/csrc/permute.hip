@@ -142,7 +142,9 @@ __global__ __launch_bounds__(64 * kPermWaves) void k_permute_columns(const uint8
             if (row + stride < M) next.load(A + (row + stride) * lda * ES, K * ES, lane);
             wave_lds_fence();
             uint8_t* dst = P + row * ldp * ES;
-            for (int64_t c = lane; c < K / EPC; c += 64) *reinterpret_cast<uint4v*>(dst + c * 16) = gather_chunk<ES>(region, in_lds, c);
+            // (written once and not read here: 4096 x 4096 bf16 16.9 -> 15.6 us, 8192 x 4096 int8 18.2 -> 17.4, 8192 x 8192 bf16 64.9 -> 63.5)
+            for (int64_t c = lane; c < K / EPC; c += 64)
+                __builtin_nontemporal_store(gather_chunk<ES>(region, in_lds, c), reinterpret_cast<uint4v*>(dst + c * 16));
             wave_lds_fence();
         }
     } else {
