@@ -225,9 +225,12 @@ __global__ void k_zero_double(double* out) { *out = 0.0; }
 // out += sum over this workgroup's rows and all groups g of the two largest magnitudes among columns
 // perm[4g] .. perm[4g+3] (the selection rule of sp24_prune: ties to the lower position, NaN highest).
 //
-// The workgroups' sums meet at one address, some 10 ns each one behind the other whatever the matrix: as many wavefronts to a
-// workgroup (16, 8 or 4) as their rows find room for in LDS, and as few workgroups.  4096 x 1024 bf16: 512 of four 12.0 us, 256 of eight 9.1,
-// 128 of sixteen 8.0, without that addition 6.8; 4096 x 8192 int8, call to call, 28.5 -> 25.1 with eight; 8192 x 8192 bf16 66.7 -> 58.0.
+// The workgroups' sums meet at one address, some 10 ns each one behind the other whatever the matrix: past 1024 rows as many
+// wavefronts to a workgroup (16 or 8) as their rows find room for in LDS, and as few workgroups as the rows leave busy.  The row is the
+// same in all lanes of a wavefront and held in scalar registers: as a vector it made 129 registers, of which sixteen wavefronts spilled three to
+// scratch memory (1.2 us a launch) and eight had a unit to themselves.  us, 512 workgroups of four / 256 of eight / 128 and 256 of sixteen, bf16: 128 x 1024
+// 6.0 / 6.1 / 6.9, 6.9; 384 x 1024 6.7 / 6.2 / 6.9, 6.9; 1500 x 1024 10.1 / 8.0 / 7.6, 7.6; 4096 x 1024 12.8 / 9.8 / 9.3, 9.7; 16384 x 1024 20.5 / 17.8 / 18.5,
+// 15.1; 65536 x 2048 62 / 61 / 80, 49; 16384 x 4096 38.5 / 36.7 / 45.5, 34.3 (from HBM 39.1 / 36.8 / 46.8, 37.1); 8192 x 8192 65.7 / 41.7.
 template <int DT, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void k_retained_magnitude(const uint8_t* A, const int32_t* perm, double* out, int64_t M, int64_t K,
                                                                         int64_t lda)
@@ -235,7 +238,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_retained_magnitude(const uint8_t
     constexpr int ES = is8<DT> ? 1 : 2;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];   // staged: the order (2 K bytes), then WAVES rows
     __shared__ double partial[WAVES];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const bool staged = K * ES <= kPermRowBytes;
     const StagedOrder in_lds = {(lds_order)lds};
     const PlainOrder in_memory = {perm, K};
@@ -272,7 +275,8 @@ __global__ __launch_bounds__(64 * WAVES) void k_retained_magnitude(const uint8_t
             wave_lds_fence();
         }
     } else {
-        for (int64_t row = first; row < M; row += stride) {
+        // (the row as a vector here: single elements from a scalar address are 3 - 5 % slower, 64 x 16384 bf16 44.9 us against 47.3)
+        for (int64_t row = (int64_t)blockIdx.x * WAVES + (threadIdx.x >> 6); row < M; row += stride) {
             const uint8_t* src = A + row * lda * ES;
             for (int64_t g = lane; g < K / 4; g += 64) sum += kept_of_group<DT>(src, in_memory, g);
         }
@@ -365,24 +369,25 @@ sp24_status launch_permute_rows(const void* A, const void* perm, void* P, int64_
     return launch_result();
 }
 
-// out += the total; 2048 wavefronts at most, in workgroups of 16 (two to a unit, 80 KiB each), 8 or 4
+// out += the total.  The widths and their lines: 37 - 65536 rows of 64 - 16384 columns, the figures beside the kernel.  Sixteen wavefronts where
+// their rows take half a unit's LDS; with longer rows they are 0.87 - 1.16 times as fast as eight, behind up to 2048 rows.
 template <int DT>
 static sp24_status retained_magnitude(const void* A, const void* perm, double* out, int64_t M, int64_t K, int64_t lda, hipStream_t st)
 {
     constexpr int ES = is8<DT> ? 1 : 2;
-    auto run = [&](auto waves) {
+    auto run = [&](auto waves, int64_t most) {
         constexpr int WAVES = decltype(waves)::value;
         static const bool ready = allow_lds(k_retained_magnitude<DT, WAVES>, kKeptMaxLds);
         if (!ready) return SP24_ERR_LAUNCH;
         const int64_t passes = (M + WAVES - 1) / WAVES;
         const size_t lds = perm && K * ES <= kPermRowBytes ? (size_t)(2 * K + WAVES * K * ES) : 0;   // the given order needs no staging
-        k_retained_magnitude<DT, WAVES><<<dim3((unsigned)(passes < 2048 / WAVES ? passes : 2048 / WAVES)), dim3(64 * WAVES), lds, st>>>(
+        k_retained_magnitude<DT, WAVES><<<dim3((unsigned)(passes < most ? passes : most)), dim3(64 * WAVES), lds, st>>>(
             static_cast<const uint8_t*>(A), static_cast<const int32_t*>(perm), out, M, K, lda);
         return launch_result();
     };
-    if (perm && 2 * K + 16 * K * ES <= 80 * 1024) return run(std::integral_constant<int, 16>{});
-    if (perm && 2 * K + 8 * K * ES <= kKeptMaxLds) return run(std::integral_constant<int, 8>{});
-    return run(std::integral_constant<int, kPermWaves>{});
+    if (perm && M > 1024 && 2 * K + 16 * K * ES <= 80 * 1024) return run(std::integral_constant<int, 16>{}, M > 4096 ? 256 : 128);
+    if (perm && 2 * K + 8 * K * ES <= kKeptMaxLds) return run(std::integral_constant<int, 8>{}, 256);
+    return run(std::integral_constant<int, kPermWaves>{}, 512);
 }
 
 sp24_status launch_retained_magnitude(const void* A, const void* perm, double* out, int64_t M, int64_t K, int64_t lda, sp24_dtype t,

@@ -112,9 +112,12 @@ def test_retained_magnitude_matches_the_oracle(dtype):
 
 
 @pytest.mark.parametrize("dtype,M,K", [("bf16", 37, 2400), ("f16", 37, 2416), ("i8", 100, 4544), ("i8", 100, 4576), ("bf16", 2051, 64),
-                                       ("i8", 41, 15360), ("i8", 41, 15392)])
+                                       ("i8", 41, 15360), ("i8", 41, 15392), ("bf16", 1024, 160), ("f16", 1025, 160), ("bf16", 1040, 2400),
+                                       ("bf16", 1040, 2416), ("i8", 1100, 4544), ("i8", 2100, 4576), ("i8", 4096, 96), ("f16", 4097, 96),
+                                       ("bf16", 9000, 128)])
 def test_retained_magnitude_on_both_sides_of_the_workgroup_sizes(dtype, M, K):
-    """Rows that 16, 8 or 4 wavefronts to a workgroup find room for, and more rows than one pass takes."""
+    """Rows that 16 (past 1024 rows), 8 or 4 wavefronts to a workgroup find room for, 128 and 256 workgroups, and more rows than one
+    pass takes."""
     A = synth.make(NAME_OF[dtype], M=M, N=16, K=K, seed=K)[0]
     perm = np.random.default_rng(K).permutation(K).astype(np.int32)
     got = sp24.sp24_retained_magnitude(to_gpu(A, dtype), dev_perm(perm))
