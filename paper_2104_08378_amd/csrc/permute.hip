@@ -118,8 +118,8 @@ __device__ __forceinline__ uint4v gather_chunk(ROW row, const ORDER& col, int64_
     return out;
 }
 
-// P[m][k] = A[m][perm[k]]: a lane writes 16 bytes of P (8 or 16 elements) gathered one by one
-template <int ES>
+// P[m][k] = A[m][perm[k]]: a lane writes 16 bytes of P (8 or 16 elements) gathered one by one.  PAST_L2: the staged path's stores pass the L2
+template <int ES, bool PAST_L2>
 __global__ __launch_bounds__(64 * kPermWaves) void k_permute_columns(const uint8_t* A, const int32_t* perm, uint8_t* P, int64_t M, int64_t K,
                                                                      int64_t lda, int64_t ldp)
 {
@@ -142,9 +142,11 @@ __global__ __launch_bounds__(64 * kPermWaves) void k_permute_columns(const uint8
             if (row + stride < M) next.load(A + (row + stride) * lda * ES, K * ES, lane);
             wave_lds_fence();
             uint8_t* dst = P + row * ldp * ES;
-            // (written once and not read here: 4096 x 4096 bf16 16.9 -> 15.6 us, 8192 x 4096 int8 18.2 -> 17.4, 8192 x 8192 bf16 64.9 -> 63.5)
-            for (int64_t c = lane; c < K / EPC; c += 64)
-                __builtin_nontemporal_store(gather_chunk<ES>(region, in_lds, c), reinterpret_cast<uint4v*>(dst + c * 16));
+            for (int64_t c = lane; c < K / EPC; c += 64) {
+                const uint4v chunk = gather_chunk<ES>(region, in_lds, c);
+                if constexpr (PAST_L2) __builtin_nontemporal_store(chunk, reinterpret_cast<uint4v*>(dst + c * 16));
+                else *reinterpret_cast<uint4v*>(dst + c * 16) = chunk;
+            }
             wave_lds_fence();
         }
     } else {
@@ -349,11 +351,19 @@ sp24_status launch_permute_columns(const void* A, const void* perm, void* P, int
     const uint8_t* a = static_cast<const uint8_t*>(A);
     const int32_t* p = static_cast<const int32_t*>(perm);
     uint8_t* o = static_cast<uint8_t*>(P);
-    static const bool ready = allow_lds(k_permute_columns<1>) && allow_lds(k_permute_columns<2>);
+    static const bool ready = allow_lds(k_permute_columns<1, false>) && allow_lds(k_permute_columns<1, true>) && allow_lds(k_permute_columns<2, false>) &&
+                              allow_lds(k_permute_columns<2, true>);
     if (!ready) return SP24_ERR_LAUNCH;
     const size_t lds = staged_lds_bytes(K, esize_of(t));
-    if (esize_of(t) == 1) k_permute_columns<1><<<grid, block, lds, st>>>(a, p, o, M, K, lda, ldp);
-    else k_permute_columns<2><<<grid, block, lds, st>>>(a, p, o, M, K, lda, ldp);
+    // Stores past the L2 where the call and its reader (sp24_prune_transposable, sp24_compress) together gain, operands in the caches and from HBM: results of 5 - 32
+    // MB in up to 5120 rows, the call alone 0.99 - 1.5 times as fast (3072 x 4096 bf16 15.5 -> 10.2 us, 4096 x 4096 18.6 -> 15.2), with its reader 0.99 - 1.3.
+    // A smaller result is level alone and its reader finds it in the L2 (0.94 - 1.0 together, 512 x 256 bf16 6.9 -> 7.2 us); larger ones 0.88 - 1.09
+    // alone and 0.91 - 1.09 together (16384 x 4096 bf16 146 -> 154); more and shorter rows 0.93 - 0.99 together from HBM (6144 x 1024 bf16 13.9 -> 15.0).
+    const int64_t bytes = M * K * esize_of(t);
+    const bool past_l2 = bytes > (int64_t)5 << 20 && bytes <= (int64_t)32 << 20 && M <= 5120;
+    auto run = [&](auto kernel) { kernel<<<grid, block, lds, st>>>(a, p, o, M, K, lda, ldp); };
+    if (esize_of(t) == 1) past_l2 ? run(k_permute_columns<1, true>) : run(k_permute_columns<1, false>);
+    else past_l2 ? run(k_permute_columns<2, true>) : run(k_permute_columns<2, false>);
     return launch_result();
 }
 

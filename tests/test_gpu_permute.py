@@ -77,6 +77,22 @@ def test_permute_rows_bit_exact(dtype):
     assert not to_bits(out[:, K:]).any()
 
 
+# results on both sides of 5 MiB, 32 MiB and 5120 rows, between which they are stored past the L2: read back at once by the pruning
+@pytest.mark.parametrize("dtype,M,K", [("bf16", 1280, 2048), ("bf16", 1281, 2048), ("i8", 4967, 1056), ("f8", 5120, 1056), ("i8", 5121, 1056),
+                                       ("f16", 1366, 6144), ("bf16", 2048, 8192), ("bf16", 2051, 8192)])
+def test_permute_columns_of_results_on_both_sides_of_the_l2(dtype, M, K):
+    words = {"f16": np.uint16, "bf16": np.uint16, "i8": np.int8, "f8": np.uint8}[dtype]
+    A = np.frombuffer(np.random.default_rng(K).bytes(M * K * np.dtype(words).itemsize), words).reshape(M, K).copy()
+    perm = np.random.default_rng(M).permutation(K).astype(np.int32)
+    Ad = to_gpu(A, dtype)
+    for _ in range(2):
+        P = sp24.sp24_permute_columns(Ad, dev_perm(perm))
+        kept = sp24.sp24_prune(P)
+        torch.cuda.synchronize()
+        assert np.array_equal(to_bits(P), A[:, perm])
+        assert torch.equal(kept.view(torch.uint8), sp24.sp24_prune(to_gpu(np.ascontiguousarray(A[:, perm]), dtype)).view(torch.uint8))
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "i8"])
 def test_retained_magnitude_matches_the_oracle(dtype):
     for i, (M, K) in enumerate(SHAPES):
