@@ -134,9 +134,11 @@ __global__ __launch_bounds__(64 * NW) void k_spmm_stream(MmArgs a, int tiles_m, 
     nmajor_frags<BR, TN, ES> b_nm;
     if constexpr (NMAJ) b_nm.init(0, BR == 16 ? lane & ~16 : lane);
 
-    // Floats: two sums of each element, one per half of a step, added at the end, which leaves half the roundings in each (with the sums
-    // in pairs below, 1000 x 64 x 2048 f16: relative error 9.7e-8 -> 8.0e-8, split in four slices 8.1e-8; times unchanged)
-    constexpr bool kTwo = DT != SP24_I8;
+    // 16-bit floats: two sums of each element, one per half of a step, added at the end, which leaves half the roundings in each (with the sums
+    // in pairs below, 1000 x 64 x 2048 f16: relative error 9.7e-8 -> 8.0e-8, split in four slices 8.1e-8; up to 0.1 us).  8-bit floats, whose error is
+    // what the instruction drops, have the same with one (5.7e-6 on normal values, 5.3e-5 on every bit pattern, 512 - 16384 columns of A), and
+    // lose by the second: 288 x 316 x 1472, canonical, from HBM 5.5 -> 6.0 us, 634 x 52 x 3168 9.2 -> 9.9.
+    constexpr bool kTwo = !is8<DT>;
     acc_t acc[TN], acc_second[TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[j] = acc_second[j] = acc_t{};
@@ -168,9 +170,8 @@ __global__ __launch_bounds__(64 * NW) void k_spmm_stream(MmArgs a, int tiles_m, 
                 int8v f;
                 f[0] = lo[j][nj][0]; f[1] = lo[j][nj][1]; f[2] = lo[j][nj][2]; f[3] = lo[j][nj][3];
                 f[4] = hi[j][nj][0]; f[5] = hi[j][nj][1]; f[6] = hi[j][nj][2]; f[7] = hi[j][nj][3];
-                if (j == 0) acc[nj] = smfmac32<DT, 0>(va[0], f, acc[nj], code[0]);
-                else if constexpr (!kTwo) acc[nj] = smfmac32<DT, 0>(va[1], f, acc[nj], code[T64 - 1]);
-                else if constexpr (is8<DT>) acc_second[nj] = smfmac32<DT, 0>(va[1], f, acc_second[nj], code[T64 - 1]);
+                if constexpr (is8<DT>) acc[nj] = smfmac32<DT, 0>(va[j], f, acc[nj], code[j]);
+                else if (j == 0) acc[nj] = smfmac32<DT, 0>(va[0], f, acc[nj], code[0]);
                 else acc_second[nj] = smfmac32<DT, 1>(va[1], f, acc_second[nj], code[0]);
             }
     };
