@@ -363,15 +363,18 @@ static bool stream_first(const MmArgs& a)
 {
     if (!a.sparse || a.conv.on) return false;
     // An N-major B whose rows the transfers can fetch: the same rule without the limit of 512 columns.  Against the tiled kernels, times as fast
-    // from the caches / from HBM, 18 shapes of 32 - 8192 rows and 16 - 4096 columns, 2 - 128 steps: tiled layout bf16 1.13 - 2.9 / 1.1 - 2.6 (1024 x 512 x
+    // from the caches / from HBM, 32 - 8192 rows and 16 - 16384 columns, 2 - 128 steps: tiled layout bf16 1.13 - 2.9 / 1.1 - 2.6 (1024 x 512 x
     // 4096 15.4 -> 11.7 us, 512 x 128 x 8192 from HBM 37.4 -> 21.0), int8 1.0 - 3.0 / 1.02 - 2.5 (1024 x 512 x 4096 11.2 -> 9.4); canonical
-    // from 8 steps on 0.99 - 2.1 / 1.0 - 2.6 and 1.04 - 2.5 / 1.02 - 2.2, with fewer 0.92 - 1.09.  On 257 - 512 workgroups 0.63 - 1.04, except for
-    // canonical 16-bit operands, past 32 columns and from 32 steps on: 1.02 - 1.20 / 1.03 - 1.25 (4096 x 192 x 2048 14.1 -> 13.0, from HBM 16.7 -> 13.9).
+    // from 8 steps on 0.95 - 2.1 / 1.0 - 2.6 and 1.04 - 2.5 / 1.02 - 2.2, with fewer 0.92 - 1.09; past 4096 columns 0.98 and more throughout.
+    // On 257 - 512 workgroups 0.63 - 1.04, except for canonical 16-bit operands, past 32 columns and from 32 steps on: 0.98 - 1.20 / 1.04 - 1.54
+    // (4096 x 192 x 2048 14.1 -> 13.0, from HBM 16.7 -> 13.9) with 128 rows and more and rows of B that are whole cache lines.  Rows that begin
+    // inside a line 0.83 - 1.0 from the caches (1024 x 784 x 2048 14.1 -> 15.6), 64 - 96 rows 0.83 - 1.04 / 0.90 - 1.02 (96 x 10624 x 3072 from HBM 27.7 -> 30.2).
     if (a.bo == SP24_B_NMAJOR) {
         const int64_t es = esize_of(a.in), steps = a.K * es / 128;
         const bool whole_chunks = reinterpret_cast<uintptr_t>(a.B) % 16 == 0 && a.ldb * es % 16 == 0 && a.N * es % 16 == 0;
+        const bool whole_lines = reinterpret_cast<uintptr_t>(a.B) % 128 == 0 && a.ldb * es % 128 == 0;
         const bool canonical = a.layout == SP24_LAYOUT_CANONICAL;
-        const int most = canonical && es == 2 && a.N > 32 && steps >= 32 ? 512 : 256;
+        const int most = canonical && es == 2 && a.N > 32 && a.M >= 128 && steps >= 32 && whole_lines ? 512 : 256;
         return whole_chunks && steps >= (canonical ? 8 : 2) && stream_workgroups(a) <= most;
     }
     if (a.N > 512) return false;

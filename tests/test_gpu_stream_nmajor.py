@@ -1,5 +1,5 @@
 """Sparse products with few tiles and an N-major second operand of whole 16-byte chunks (the streaming kernel up to 256 workgroups
-of 32 rows, canonical 16-bit operands of many steps 512, the tiled ones past it): against the oracle at the edges of column tiles, steps of K and rows."""
+of 32 rows, canonical 16-bit operands of many steps and a B of whole lines 512, the tiled ones past it): against the oracle at the edges of column tiles, steps of K and rows."""
 import numpy as np
 import pytest
 import torch
@@ -24,6 +24,10 @@ pytestmark = pytest.mark.gpu
     ("bf16", "f32", 64, 1032, 256, "tiled", 0),          # many columns
     ("bf16", "f32", 2080, 256, 2048, "canonical", 0),    # 260 workgroups in two rounds
     ("bf16", "f32", 2080, 256, 1984, "canonical", 0),    # 31 steps: not here
+    ("f16", "f16", 2080, 240, 2048, "canonical", 16),    # 260 workgroups, a ragged column tile in whole lines
+    ("bf16", "f32", 2080, 256, 2048, "canonical", 8),    # rows that begin inside a line: not here
+    ("bf16", "f32", 128, 4160, 2048, "canonical", 0),    # 260 workgroups on few rows
+    ("bf16", "f32", 96, 5568, 2048, "canonical", 0),     # 261 on fewer: not here
     ("i8", "i32", 32, 16, 256, "tiled", 0),
     ("i8", "i32", 96, 48, 1120, "canonical", 16),        # 8 steps and three quarters
     ("i8", "i32", 128, 32, 2112, "tiled", 0),            # 16 steps and a half
