@@ -583,13 +583,17 @@ static sp24_status mm_splitk(const MmArgs& a, void* workspace, size_t workspace_
         // (1000 x 200 x 20480 bf16 29.8 against 37.6).  An 8-bit N-major B in two slices of the tiled layout: 48 steps each 3 - 5 % ahead, 64 2 - 5 %
         // behind (1024 x 192 x 16384).
         // Few steps are not worth the second kernel and the images: past 32 columns the unsplit product is ahead up to 40 steps, of a
-        // canonical operand up to 32 (us, unsplit / split, operands in the caches, then from HBM; ten shapes of 256 - 2048 rows each:
-        // 24 steps 5.3 - 6.1 / 7.4 - 8.1, 6.4 - 7.3 / 8.5 - 10.4; 32 5.8 - 6.7 / 8.0 - 8.7, 6.9 - 8.2 / 8.7 - 9.9; 48 tiled 6.9 - 8.6 / 8.3 - 9.3, 8.2 - 11.4 /
-        // 9.1 - 10.4, canonical 7.7 - 9.8 / 8.3 - 9.6, 9.6 - 12.7 / 9.1 - 10.7; 64 7.9 - 11.7 / 8.5 - 10.6, 9.0 - 16.1 / 9.4 - 11.5).
-        // 1000 x 64 x 2048 f16, canonical: 8.3 -> 6.6.  N-major: the line of the tiled kernels below (32 steps 5.8 - 6.5 / 8.1 - 9.2; 48 7.0 - 8.5 / 8.1 - 9.2,
-        // from HBM 8.1 - 8.5 / 8.5 - 9.2).
+        // canonical operand up to 32, as long as its few workgroups bring in what HBM would give the split one's many: with fewer than 256 rows on more
+        // than 160 columns up to 28 and 22, below 512 rows there, tiled, up to 37.  Times as fast as split, operands in the caches / from HBM (64 -
+        // 1024 rows, 40 - 500 columns, three types): tiled up to 26 steps 1.3 - 1.4 / 1.0 - 1.3; 30 - 37 1.2 - 1.4 / 0.95 - 1.3, at 40 1.15 - 1.28 / 0.85 - 1.15
+        // (512 x 64 x 2560 bf16 the least), and on the other side of the line 1.2 - 1.35 / 0.81 - 1.0 (64 x 400 x 2560); canonical up to 20 1.3 - 1.4 / 1.0 - 1.2, 30 - 32
+        // 1.17 - 1.36 / 0.92 - 1.17, on the other side 1.2 - 1.3 / 0.84 - 1.0.  48 steps are level (tiled 6.9 - 8.6 / 8.3 - 9.3 us unsplit / split, from HBM 8.2 - 11.4 /
+        // 9.1 - 10.4).  1000 x 64 x 2048 f16, canonical: 8.3 -> 6.6.  N-major: the line of the tiled kernels below, past which HBM
+        // favours the cut (33 steps 1.22 - 1.35 / 0.81 - 1.11, 48 1.02 - 1.22 / 0.63 - 1.0; 8-bit, 32 steps, 1.24 - 1.37 / 0.70 - 1.04).
         const bool canonical = a.layout == SP24_LAYOUT_CANONICAL;
-        if (a.N > 32 && steps <= (a.bo == SP24_B_NMAJOR ? (es == 2 ? 32 : 31) : canonical ? 32 : 40)) n = 1;
+        const bool few_rows = a.N > 160 && a.M < 256, some_rows = a.N > 160 && a.M < 512;
+        const int64_t kmajor_line = canonical ? (few_rows ? 22 : 32) : few_rows ? 28 : some_rows ? 37 : 40;
+        if (a.N > 32 && steps <= (a.bo == SP24_B_NMAJOR ? (es == 2 ? 32 : 31) : kmajor_line)) n = 1;
         int64_t longest = steps;
         if (a.N > 32 && n <= (a.N <= 64 ? 3 : 2)) {
             if (n == 1) longest = canonical ? 128 : 104;

@@ -1,5 +1,5 @@
 """Split sparse products on both sides of the line below which they are not split (40 whole 128-byte steps of K in the tiled
-layout, 32 in the canonical one, more than 32 columns): int8 equal to the oracle, floats within the bound of K fp32 additions;
+layout, 32 in the canonical one, more than 32 columns; fewer with few rows on more than 160 columns): int8 equal to the oracle, floats within the bound of K fp32 additions;
 up to the line the call is the unsplit product bit for bit."""
 import numpy as np
 import pytest
@@ -21,6 +21,13 @@ pytestmark = pytest.mark.gpu
     ("i8", "i32", 256, 65, 5120, "tiled", True),           # 40, odd N
     ("i8", "i32", 256, 500, 4096, "canonical", True),      # 32
     ("i8", "i32", 256, 500, 4224, "canonical", False),     # 33
+    ("f16", "f32", 1000, 100, 2080, "canonical", True),    # 32 and half a one that the streaming kernel takes
+    ("bf16", "f32", 224, 200, 1792, "tiled", True),        # fewer than 256 rows on more than 160 columns: 28
+    ("bf16", "f32", 224, 200, 1856, "tiled", False),       # 29
+    ("f16", "f32", 100, 300, 1408, "canonical", True),     # 22
+    ("f16", "f32", 100, 300, 1472, "canonical", False),    # 23
+    ("i8", "i32", 256, 161, 4736, "tiled", True),          # fewer than 512: 37
+    ("i8", "i32", 256, 161, 4864, "tiled", False),         # 38
 ])
 def test_line_below_which_products_are_not_split(dtype, out, M, N, K, layout, unsplit):
     need = sp24.sp24_splitk_workspace_bytes(M, N, K, IN_DT[dtype])
