@@ -483,7 +483,10 @@ static size_t records_offset(int64_t M, int64_t K) { return columns_offset(M, K)
 
 size_t permute_search_workspace(int64_t M, int64_t K)
 {
-    if (M == 0 || search_rounds(K / 4) == 0 || K * ((M + 511) / 512) > (int64_t)1 << 31) return 0;
+    if (M == 0 || search_rounds(K / 4) == 0) return 0;
+    // a launch is less than 2^32 threads: the copy's 1024 to 64 columns and a block of 512 rows, and 512 to a pair
+    const int64_t blocks = M / 512 + (M % 512 != 0), column_blocks = (K + 63) / 64;
+    if (K >= (int64_t)1 << 26 || blocks > (((int64_t)1 << 22) - 1) / column_blocks) return 0;
     // Many pairs of few rows: a workgroup's start and end count, which are longer here (in place -> copy, from the order of memory: 64 x 4096
     // bf16 83 -> 102 us, 256 x 16384 334 -> 405, 512 x 16384 396 -> 443; 512 x 4096 122 -> 110, 1024 x 16384 583 -> 532)
     if (K / 8 > 256 && M <= (K / 8 > 1024 ? 512 : 256)) return 0;

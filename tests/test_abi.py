@@ -304,6 +304,13 @@ def test_permute_search_workspace_validation():
     L, A, PERM, WS = sp24.lib(), P, P + 0x4000000, P + 0x8000000
     f, need = L.sp24_permute_search_workspace, L.sp24_permute_search_workspace_bytes(64, 64, sp24.F16)
     assert need >= 64 * 512 * 2
+    # the size is 0 where the copy's launches would not fit (4 workgroups of 256 threads to 64 columns and 512 rows), and for no M does it wrap
+    rows = 512 * ((1 << 22) - 1)
+    assert L.sp24_permute_search_workspace_bytes(rows, 32, sp24.BF16) > 0 and L.sp24_permute_search_workspace_bytes(rows, 64, sp24.I8) > 0
+    for big in ((rows + 1, 32, sp24.BF16), (1 << 31, 32, sp24.I8), (512 * ((1 << 21) - 1) + 1, 80, sp24.F16), ((1 << 58) + 512, 64, sp24.F16),
+                (1 << 62, 32, sp24.I8), ((1 << 63) - 1, 64, sp24.I8), (1024, 1 << 26, sp24.BF16)):
+        assert L.sp24_permute_search_workspace_bytes(*big) == 0
+    assert L.sp24_permute_search_workspace_bytes(512 * ((1 << 21) - 1), 80, sp24.F16) > 0
     for bad in ((0, 64, sp24.F16), (-1, 64, sp24.F16), (64, 40, sp24.F16), (64, 64, sp24.F32), (64, 0, sp24.F16), (1 << 40, 64, sp24.I8)):
         assert L.sp24_permute_search_workspace_bytes(*bad) == 0
     assert f(A, 0, 64, 64, 64, sp24.F16, 1, WS, need, None) == NULL
