@@ -230,9 +230,10 @@ sp24_status sp24_permute_search(const void* A, int32_t* perm, int64_t M, int64_t
  * that lies column by column: about twice as fast.  workspace (device, 16-byte
  * aligned, not overlapping A or perm; contents before the call are ignored,
  * after it unspecified) holds sp24_permute_search_workspace_bytes(M, K, t)
- * bytes, the matrix at two bytes an element with M rounded up to 512 and a
- * few dozen bytes a column.  0 bytes (no rounds, an illegal shape or type, a
- * matrix too large): the call is sp24_permute_search, and so it is with
+ * bytes, the matrix at two bytes an element with M rounded up to 512 and 12 bytes
+ * a column for each of the ceil(log2(K / 4)) rounds and one more.  0 bytes (no
+ * rounds, an illegal shape or type, a matrix too large, and few rows, which are
+ * faster in place): the call is sp24_permute_search, and so it is with
  * workspace NULL.  Errors as for sp24_permute_search, and SP24_ERR_ALIGN for a
  * misaligned workspace, SP24_ERR_SHAPE for one that is too small or overlaps.
  * Calls sharing one workspace must not overlap in time.

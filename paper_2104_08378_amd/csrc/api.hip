@@ -256,7 +256,7 @@ sp24_status sp24_permute_search(const void* A, int32_t* perm, int64_t M, int64_t
 
 size_t sp24_permute_search_workspace_bytes(int64_t M, int64_t K, sp24_dtype t)
 {
-    return is_input_type(t) && M >= 0 && k_legal(K, t) && K <= 0x7FFFFFFF ? permute_search_workspace(M, K) : 0;
+    return is_input_type(t) && M >= 0 && k_legal(K, t) && K <= 0x7FFFFFFF ? permute_search_workspace(M, K, t) : 0;
 }
 
 sp24_status sp24_permute_search_workspace(const void* A, int32_t* perm, int64_t M, int64_t K, int64_t lda, sp24_dtype t, int sweeps,
@@ -264,7 +264,7 @@ sp24_status sp24_permute_search_workspace(const void* A, int32_t* perm, int64_t 
 {
     const sp24_status s = check_permute_search(A, perm, M, K, lda, t, sweeps);
     if (s != SP24_OK) return s;
-    const size_t need = permute_search_workspace(M, K);
+    const size_t need = permute_search_workspace(M, K, t);
     if (!workspace || need == 0) return launch_permute_search(A, perm, M, K, lda, t, sweeps, static_cast<hipStream_t>(stream));
     if (reinterpret_cast<uintptr_t>(workspace) % 16 != 0) return SP24_ERR_ALIGN;
     if (workspace_bytes < need || ranges_overlap(workspace, need, A, ((size_t)(M - 1) * lda + K) * esize_of(t)) ||

@@ -20,7 +20,7 @@ sp24_status launch_retained_magnitude(const void* A, const void* perm, double* o
                                       hipStream_t st);
 sp24_status launch_permute_search(const void* A, int32_t* perm, int64_t M, int64_t K, int64_t lda, sp24_dtype t, int sweeps, hipStream_t st);
 // on a copy that lies column by column, in permute_search_workspace() bytes (0: not for this shape)
-size_t permute_search_workspace(int64_t M, int64_t K);
+size_t permute_search_workspace(int64_t M, int64_t K, sp24_dtype t);
 sp24_status launch_permute_search_columns(const void* A, int32_t* perm, int64_t M, int64_t K, int64_t lda, sp24_dtype t, int sweeps,
                                           void* workspace, hipStream_t st);
 sp24_status launch_compress_masked(const void* W, const void* meta, void* V, int64_t M, int64_t K, int64_t ldw, sp24_dtype t,

@@ -481,15 +481,18 @@ constexpr int kMostParts = 4;
 static size_t columns_offset(int64_t M, int64_t K) { return (size_t)K * ((M + 511) / 512) * 1024; }
 static size_t records_offset(int64_t M, int64_t K) { return columns_offset(M, K) + (size_t)((search_rounds(K / 4) + 1) * K) * sizeof(int32_t); }
 
-size_t permute_search_workspace(int64_t M, int64_t K)
+size_t permute_search_workspace(int64_t M, int64_t K, sp24_dtype t)
 {
     if (M == 0 || search_rounds(K / 4) == 0) return 0;
     // a launch is less than 2^32 threads: the copy's 1024 to 64 columns and a block of 512 rows, and 512 to a pair
     const int64_t blocks = M / 512 + (M % 512 != 0), column_blocks = (K + 63) / 64;
     if (K >= (int64_t)1 << 26 || blocks > (((int64_t)1 << 22) - 1) / column_blocks) return 0;
     // Many pairs of few rows: a workgroup's start and end count, which are longer here (in place -> copy, from the order of memory: 64 x 4096
-    // bf16 83 -> 102 us, 256 x 16384 334 -> 405, 512 x 16384 396 -> 443; 512 x 4096 122 -> 110, 1024 x 16384 583 -> 532)
+    // bf16 83 -> 102 us, 256 x 16384 334 -> 405, 512 x 16384 396 -> 443; 512 x 4096 122 -> 110, 1024 x 16384 583 -> 532).  int8 of fewer than 256 rows from 193 pairs
+    // on, too (128 x 2048 57 -> 64; 256 x 2048 65 -> 64, 128 x 1024 51 -> 49), and two or three rounds, beside which the copy's two other launches
+    // count (128 x 16 bf16 16.4 -> 17.5, 128 x 32 int8 21.9 -> 23.0; 256 x 32 25.0 -> 23.3)
     if (K / 8 > 256 && M <= (K / 8 > 1024 ? 512 : 256)) return 0;
+    if (M < 256 && (K <= 32 || (t == SP24_I8 && K / 8 > 192))) return 0;
     return records_offset(M, K) + (size_t)(search_rounds(K / 4) + 1) * ((K / 4 + 1) / 2) * kMostParts * sizeof(Record);
 }
 
@@ -524,10 +527,12 @@ sp24_status launch_permute_search_columns(const void* A, int32_t* perm, int64_t 
     if (hipGetLastError() != hipSuccess) return SP24_ERR_LAUNCH;
     const History h{perm, reinterpret_cast<int32_t*>(ws + columns_offset(M, K)), reinterpret_cast<Record*>(ws + records_offset(M, K)), K, G, (G + 1) / 2, rounds, 0};
     // As many parts as leave the workgroups of a round room on the chip at once (4096 x 512 bf16 in one, two and four parts: 116, 81 and
-    // 70 us a sweep, 4096 x 1024: 133, 96 and 106), and two again where float workgroups outnumber the units and are long: one
-    // holds 276 registers, which leaves a wavefront to a SIMD, each of two 178 (4096 x 11008: 945 -> 789; 1024 x 4096 level; int8 501 and 498)
+    // 70 us a sweep, 4096 x 1024: 133, 96 and 106; 2048 x 2048, 256 pairs: 103, 107 and 126, with 16 rows 57, 63 and 77), and two again where float workgroups
+    // outnumber the units: one holds 276 registers, which leaves a wavefront to a SIMD, each of two 178 (4096 x 11008: 945 -> 789; 300 x 2560
+    // 97 -> 89, 600 x 16384 529 -> 497; 512 x 4096 115 and 119, 768 x 4096 132 and 135, 512 x 6144 168 and 171, 1024 x 4096 level; int8 501 and 498)
     const int64_t pairs = G / 2;
-    const int parts = pairs <= 64 ? 4 : pairs <= 192 || (t != SP24_I8 && pairs > 256 && M >= 1024) ? 2 : 1;
+    const bool two_again = t != SP24_I8 && pairs > 256 && (M >= 1024 || pairs <= 448 || (pairs >= 1024 && M > 512));
+    const int parts = pairs <= 64 ? 4 : pairs <= 192 || two_again ? 2 : 1;
     auto run = [&](auto dt) {
         constexpr int DT = decltype(dt)::value;
         if (parts == 4) return run_rounds<DT, 4>(T, h, perm, M, blocks, sweeps, st);

@@ -227,6 +227,22 @@ def test_permute_search_in_place_and_on_a_copy(dtype, M, K):
     assert np.array_equal(copied.cpu().numpy(), oracle.permute_search(A, dtype, sweeps=2, perm=start))
 
 
+# few rows: in place from the order of memory, on a copy from a given one (floats, many columns), in place both ways (two or three rounds; int8 from 193
+# pairs on)
+@pytest.mark.parametrize("dtype,M,K,default,given", [("bf16", 300, 4096, False, True), ("f16", 401, 4096, True, True), ("bf16", 600, 8192, False, True),
+                                                     ("i8", 300, 4096, True, True), ("i8", 255, 2048, False, False), ("i8", 256, 2048, True, True),
+                                                     ("bf16", 255, 32, False, False), ("f16", 256, 32, True, True)])
+def test_permute_search_of_few_rows_by_either_route(dtype, M, K, default, given):
+    A = synth.make(NAME_OF[dtype], M=M, N=16, K=K, seed=220)[0]
+    Ad = to_gpu(A, dtype)
+    assert (sp24._search_workspace(Ad, True) is not None, sp24._search_workspace(Ad, False) is not None) == (default, given)
+    first = sp24.sp24_permute_search(Ad)
+    again = sp24.sp24_permute_search(Ad, perm=dev_perm(np.arange(K)))
+    torch.cuda.synchronize()
+    assert torch.equal(first, again)
+    assert np.array_equal(first.cpu().numpy(), oracle.permute_search(A, dtype, sweeps=1))
+
+
 def test_permute_search_starts_from_a_given_order_and_takes_pitched_rows():
     dtype, M, K = "bf16", 500, 96
     A = synth.make(NAME_OF[dtype], M=M, N=16, K=K, seed=181)[0]
