@@ -166,7 +166,7 @@ def test_f8_other_operations():
     found = sp24.sp24_permute_search(to_gpu(An, "f8"), sweeps=1)
     torch.cuda.synchronize()
     assert np.array_equal(found.cpu().numpy(), oracle.permute_search(An, "f8", sweeps=1))
-    # split product: few tiles, long K
+    # the split entry point, few tiles (32 steps: not split; test_f8_products_that_are_split)
     M2, N2, K2 = 256, 96, 4096
     A2, B2 = draw(M2, K2, 0.5, 83), synth.normal_bits((N2, K2), 1.0, "f8", 84, 9, 1)
     assert sp24.sp24_splitk_workspace_bytes(M2, N2, K2, torch.float8_e4m3fn) > 0
@@ -185,6 +185,26 @@ def test_f8_other_operations():
     refc = oracle.conv2d(oracle.prune(W, "f8"), X, "f8", R, S, (1, 1), (1, 1))
     Bcol = synth.im2col_nhwc(X.reshape(2, 9, 9, C), R, S, 1)    # the same second operand as a matrix, for the magnitudes
     assert f8_close(out_to_f64(Dc), refc, oracle.prune(W, "f8"), Bcol)
+
+
+@pytest.mark.parametrize("M,N,K,layout,b_order", [
+    (256, 96, 5376, "tiled", "k"),           # 42 steps
+    (224, 168, 3712, "tiled", "k"),          # few rows: 29
+    (200, 100, 5472, "canonical", "k"),      # 42 and three quarters
+    (256, 96, 5376, "canonical", "n"),
+    (512, 16, 16384, "tiled", "k"),           # N <= 32
+])
+def test_f8_products_that_are_split(M, N, K, layout, b_order):
+    """Partial products go through the workspace (filled with NaN patterns) and are added."""
+    A, Bt = draw(M, K, 0.5, 95), synth.normal_bits((N, K), 1.0, "f8", 96, 9, 1)
+    ws = torch.full((sp24.sp24_splitk_workspace_bytes(M, N, K, torch.float8_e4m3fn),), 0xFF, dtype=torch.uint8, device="cuda")
+    V, meta = sp24.sp24_compress(to_gpu(A, "f8"), layout=layout)
+    Bd = to_gpu(Bt if b_order == "k" else np.ascontiguousarray(Bt.T), "f8")
+    D = sp24.sp24_spmm_splitk(V, meta, Bd, torch.float32, b_order=b_order, layout=layout, workspace=ws)
+    torch.cuda.synchronize()
+    assert not bool((ws == 0xFF).all())
+    P = oracle.prune(A, "f8")
+    assert f8_close(out_to_f64(D), oracle.gemm(P, np.ascontiguousarray(Bt.T), "f8"), P, Bt)
 
 
 def test_f8_rejected_where_it_does_not_apply():

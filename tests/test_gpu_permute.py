@@ -193,8 +193,8 @@ def test_permute_search_on_group_counts_that_are_no_power_of_two(K):
 
 @pytest.mark.parametrize("dtype,K", [("bf16", 4096), ("f16", 4112), ("i8", 8192), ("f8", 8192)])
 def test_permute_search_of_a_large_matrix_from_any_order(dtype, K):
-    """Rows enough for the form of the kernel whose wavefronts go through them together, the last pass over the rows a
-    partial one.  Rows of zeros add nothing to any sum: the oracle gets the others, each at its place modulo the 256 lanes."""
+    """On a copy, and in place with rows enough for the form of the kernel whose wavefronts go through them together, the last pass
+    over the rows a partial one.  Rows of zeros add nothing to any sum: the oracle gets the others, each at its place modulo the 256 lanes."""
     M = 8200
     if dtype == "f8":
         A = synth.f64_to_f8_bits(np.random.default_rng(201).standard_normal((520, K)))
@@ -204,15 +204,22 @@ def test_permute_search_of_a_large_matrix_from_any_order(dtype, K):
     big = torch.zeros((M, K), dtype=Ad.dtype, device="cuda")
     big.view(torch.uint8)[:512], big.view(torch.uint8)[8192:] = Ad.view(torch.uint8)[:512], Ad.view(torch.uint8)[512:]
     start = np.random.default_rng(202).permutation(K).astype(np.int32)
-    got = sp24.sp24_permute_search(big, perm=dev_perm(start))
+    got, placed = sp24.sp24_permute_search(big, perm=dev_perm(start)), dev_perm(start)
+    assert sp24.lib().sp24_permute_search(big.data_ptr(), placed.data_ptr(), M, K, K, sp24._DT[big.dtype], 1, sp24._stream()) == 0
     torch.cuda.synchronize()
-    assert np.array_equal(got.cpu().numpy(), oracle.permute_search(A, dtype, sweeps=1, perm=start))
+    want = oracle.permute_search(A, dtype, sweeps=1, perm=start)
+    assert np.array_equal(got.cpu().numpy(), want)
+    assert np.array_equal(placed.cpu().numpy(), want)
 
 
-# one, two and four workgroups to a pair of groups (from 258 groups on, 130, 2) at the edges of the copy's blocks of 512 rows
-# and of their halves; int8 sums past what 16 bits hold; the search in place and the one on a copy find the same order
+# four workgroups to a pair of groups (up to 64 pairs, 512 columns), two (up to 192, and floats past 256 with few pairs or 1024 rows) and one (the
+# others), at the edges of the copy's blocks of 512 rows and of their halves; int8 sums past what 16 bits hold; the search in place and the one
+# on a copy find the same order
 @pytest.mark.parametrize("dtype,M,K", [("bf16", 256, 512), ("f16", 257, 528), ("f8", 513, 544), ("i8", 1024, 1024), ("bf16", 1537, 1040),
-                                       ("f16", 2048, 1040), ("i8", 769, 1056), ("i8", 130_600, 32)])
+                                       ("f16", 2048, 1040), ("i8", 769, 1056), ("i8", 130_600, 32),
+                                       ("bf16", 769, 1536), ("bf16", 513, 1552), ("f16", 300, 2048), ("f8", 1025, 2048), ("i8", 300, 2048),  # 192 | 194, 256, one
+                                       ("f16", 600, 2064), ("f8", 513, 3584), ("bf16", 700, 3600), ("f16", 1023, 4096), ("bf16", 1024, 4096),  # 258, 448 | 450, one to 1023
+                                       ("bf16", 513, 8192), ("i8", 513, 8192)])
 def test_permute_search_in_place_and_on_a_copy(dtype, M, K):
     A = adversarial(dtype, M, K, 210) if dtype != "f8" else synth.f64_to_f8_bits(np.random.default_rng(210).standard_normal((M, K)))
     if M > 100_000:
@@ -241,6 +248,52 @@ def test_permute_search_of_few_rows_by_either_route(dtype, M, K, default, given)
     torch.cuda.synchronize()
     assert torch.equal(first, again)
     assert np.array_equal(first.cpu().numpy(), oracle.permute_search(A, dtype, sweeps=1))
+
+
+def test_permute_search_without_memory_for_the_copy(monkeypatch):
+    dtype, M, K = "bf16", 300, 1024
+    A = synth.make(NAME_OF[dtype], M=M, N=16, K=K, seed=230)[0]
+    Ad, start = to_gpu(A, dtype), np.random.default_rng(231).permutation(K).astype(np.int32)
+    perm = dev_perm(start)
+    asked = []
+
+    def no_memory(*args, **kwargs):
+        asked.append(args)
+        raise torch.cuda.OutOfMemoryError("none left")
+
+    monkeypatch.setattr(torch, "empty", no_memory)
+    sp24.sp24_permute_search(Ad, sweeps=2, perm=perm)
+    monkeypatch.undo()
+    torch.cuda.synchronize()
+    assert asked and np.array_equal(perm.cpu().numpy(), oracle.permute_search(A, dtype, sweeps=2, perm=start))
+
+
+def test_permute_search_on_a_copy_replays_from_a_graph():
+    """The copy's memory is the graph's own; each replay on other weights, with eager searches in between."""
+    dtype, M, K = "bf16", 700, 1024
+    sets = [synth.make(NAME_OF[dtype], M=M, N=16, K=K, seed=240 + i)[0] for i in range(3)]
+    A, perm, start = to_gpu(sets[0], dtype).clone(), dev_perm(np.arange(K)), dev_perm(np.random.default_rng(241).permutation(K))
+    assert sp24._search_workspace(A, False) is not None
+
+    def path():
+        perm.copy_(start)
+        sp24.sp24_permute_search(A, sweeps=2, perm=perm)
+
+    path()
+    torch.cuda.synchronize()
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        path()
+    torch.cuda.synchronize()
+    for bits in sets[1:] + sets[:1]:
+        A.copy_(to_gpu(bits, dtype))
+        graph.replay()
+        torch.cuda.synchronize()
+        replayed = perm.clone()
+        path()
+        torch.cuda.synchronize()
+        assert torch.equal(replayed, perm)
+        assert np.array_equal(perm.cpu().numpy(), oracle.permute_search(bits, dtype, sweeps=2, perm=start.cpu().numpy()))
 
 
 def test_permute_search_starts_from_a_given_order_and_takes_pitched_rows():

@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
 IN_DT = {"f16": torch.float16, "bf16": torch.bfloat16, "i8": torch.int8}
 
 CASES = [
-    # dtype, out, M, N, K, layout, B order -- every one a shape that is split (asserted below)
+    # dtype, out, M, N, K, layout, B order -- every one a shape with a plan to split it (asserted below), and every sparse product
+    # split (test_sparse_products_that_are_split)
     ("i8", "i32", 1024, 64, 8192, "tiled", "k"),        # 64 steps in 8 slices
     ("i8", "i32", 1000, 100, 6176, "canonical", "k"),   # ragged M and N; a partial last step (in the last slice)
     ("bf16", "bf16", 512, 96, 3104, "canonical", "k"),  # 48 steps and half a step
@@ -34,7 +35,7 @@ CASES = [
     ("i8", "i32", 512, 32, 16384, "canonical", "k"),    # 16 row blocks, 8 slices
     ("f16", "f32", 96, 7, 8192, "canonical", "k"),      # ragged N; 3 row blocks
     ("i8", "i32", 2048, 1, 12352, "tiled", "k"),        # N = 1; 193 tiles: uneven slices
-    ("f16", "f16", 128, 16, 8208, "canonical", "k"),    # K % 64 = 16: the dense product has a partial last tile, the sparse one is not split
+    ("f16", "f16", 128, 16, 8208, "canonical", "k"),    # K % 64 = 16: a partial last tile
 ]
 
 
@@ -77,6 +78,16 @@ def test_split_products_match_oracle_and_the_unsplit_products(case):
             # against the unsplit product: two roundings to the output type and two fp32 summation orders apart
             ulp = {"f32": 2.0 ** -23, "f16": 2.0 ** -10, "bf16": 2.0 ** -7}[out]
             assert (np.abs(out_to_f64(D) - out_to_f64(U)) <= 2 * K * 2.0 ** -24 * scale + ulp * np.abs(ref) + 1e-30).all(), (case, sparse)
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_sparse_products_that_are_split(case):
+    dtype, out, M, N, K, layout, b_order = case
+    ws = torch.full((sp24.sp24_splitk_workspace_bytes(M, N, K, IN_DT[dtype]),), 0xFF, dtype=torch.uint8, device="cuda")
+    _, _, Bd, V, meta = operands(dtype, M, N, K, layout, b_order, seed=21)
+    sp24.sp24_spmm_splitk(V, meta, Bd, OUT_DT[out], b_order=b_order, layout=layout, workspace=ws)
+    torch.cuda.synchronize()
+    assert not bool((ws == 0xFF).all())
 
 
 def test_workspace_contents_are_ignored_and_a_workspace_serves_calls_of_different_shapes():
