@@ -20,7 +20,7 @@
 // Measured (us a sweep, in place -> here): 4096 x 1024 bf16 179 -> 96 (a round 20.8 -> 10.9, of which the arithmetic is 4.3), int8 162 -> 76;
 // 8192 x 8192 bf16 2405 -> 1030, from an arbitrary order 10446 -> 1030; 1024 x 512 68 -> 45; 64 x 128 level.
 //
-// int8 magnitudes are summed two rows at a time in packed 16-bit arithmetic (exact; moved to 32 bits every 255 rows).
+// int8 magnitudes are summed two rows at a time in packed 16-bit arithmetic (exact; moved to 32 bits every 254 rows of a lane).
 #include <algorithm>
 
 #include "common.hpp"
@@ -32,7 +32,7 @@ namespace sp24 {
 namespace {
 
 // The workgroups of a pair: their ways, and the triples and pairs of positions that their sums are made from.  Found by
-// a search for the fewest operations: 284 a row in one part, 146 in each of two, 72 - 81 in each of four.
+// a search for the fewest operations: 284 a row in one part, 146 and 145 in two, 74 - 81 in each of four.
 struct Part {
     uint64_t ways;            // bit w: way w is this part's
     int triples, pairs;
@@ -327,15 +327,17 @@ __device__ __forceinline__ void search_part(const uint32_t* T, const int32_t (&c
     load(row[0], 0);
     load(row[1], min((int64_t)1, blocks - 1));
     if constexpr (DT == SP24_I8) {
-        // packed halves hold 255 rows of at most 256
+        // packed halves hold 255 rows of at most 256; an even number of them, because of the two rows of `row`
+        constexpr int kPacked = 254;
+        static_assert(kPacked * 256 < 65536 && kPacked % 2 == 0, "no carry into the upper half; blocks b0, b0 + 2, .. lie in row[0]");
         int wide[N];
 #pragma unroll
         for (int s = 0; s < N; ++s) wide[s] = 0;
-        for (int64_t b0 = 0; b0 < blocks; b0 += 254) {
+        for (int64_t b0 = 0; b0 < blocks; b0 += kPacked) {
             ushort2v acc[N];
 #pragma unroll
             for (int s = 0; s < N; ++s) acc[s] = ushort2v{0, 0};
-            const int64_t end = min(b0 + 254, blocks);
+            const int64_t end = min(b0 + kPacked, blocks);
             for (int64_t b = b0; b < end; b += 2) {
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
