@@ -305,6 +305,12 @@ def _search_workspace(A, one_sweep_in_memory_order):
     M, K = A.shape
     if one_sweep_in_memory_order and A.dtype != torch.int8 and M <= (720 if K >= 8192 else 400 if K >= 3600 else 0):
         return None
+    # The copy is two more launches and an allocation, 8 us of a thread that launches eagerly and nothing in a recorded graph; what it saves on
+    # the GPU is less than the launches can hide there (a search, the figure of merit, the permutation and the pattern, in place and on a copy: 64 x 128
+    # bf16 46 and 59 us, 256 x 256 56 and 62, 64 x 512 57 and 66; 512 x 256 62 and 59, 128 x 2048 74 and 71, 256 x 1024 71 and 67;
+    # replayed, the search alone: 64 x 128 34.5 and 31.9, 256 x 256 44 and 35).
+    if M <= 256 and K <= (1024 if M <= 128 else 512) and not torch.cuda.is_current_stream_capturing():
+        return None
     need = lib().sp24_permute_search_workspace_bytes(A.shape[0], A.shape[1], _DT[A.dtype])
     if need == 0 or A.device.index != torch.cuda.current_device():
         return None

@@ -154,6 +154,17 @@ def test_joint_permutation_leaves_the_dense_product_unchanged():
     assert np.array_equal(D0.cpu().numpy(), oracle.gemm(A, np.ascontiguousarray(Bt.T), "i8"))
 
 
+def search_on_a_copy(Ad, start, sweeps):
+    """sp24_permute_search_workspace with a workspace of its own (the binding brings one where the copy is faster)."""
+    lib, (M, K), dt = sp24.lib(), Ad.shape, sp24._DT[Ad.dtype]
+    need, perm = lib.sp24_permute_search_workspace_bytes(M, K, dt), dev_perm(start)
+    assert need > 0
+    workspace = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+    assert lib.sp24_permute_search_workspace(Ad.data_ptr(), perm.data_ptr(), M, K, Ad.stride(0), dt, sweeps, workspace.data_ptr(), need, sp24._stream()) == 0
+    torch.cuda.synchronize()
+    return perm
+
+
 # --- the search for a column order: the order found must equal the oracle's entry for entry -------------------
 # rows x columns: K/4 a power of two and not (groups that sit out rounds); fewer rows than lanes, a ragged last pass
 # over the rows, several passes
@@ -188,7 +199,24 @@ def test_permute_search_on_group_counts_that_are_no_power_of_two(K):
     A = synth.make(NAME_OF[dtype], M=M, N=16, K=K, seed=190 + K)[0]
     got = sp24.sp24_permute_search(to_gpu(A, dtype), sweeps=2)
     torch.cuda.synchronize()
-    assert np.array_equal(got.cpu().numpy(), oracle.permute_search(A, dtype, sweeps=2))
+    want = oracle.permute_search(A, dtype, sweeps=2)
+    assert np.array_equal(got.cpu().numpy(), want)
+    if K > 32:
+        assert np.array_equal(search_on_a_copy(to_gpu(A, dtype), np.arange(K, dtype=np.int32), 2).cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "i8", "f8"])
+@pytest.mark.parametrize("M,K", [(40, 64), (17, 160), (256, 64), (200, 96), (3, 288), (300, 32)])
+def test_permute_search_of_small_matrices_on_a_copy(dtype, M, K):
+    """Ties, infinities and NaN among them; pitched rows."""
+    A = adversarial(dtype, M, K, 250) if dtype != "f8" else np.random.default_rng(250).choice(
+        np.array([0x00, 0x80, 0x01, 0x81, 0x38, 0xB8, 0x39, 0x08, 0x7E, 0xFE, 0x7F, 0xFF], dtype=np.uint8), size=(M, K))
+    Ad = to_gpu(A, dtype)
+    big = torch.zeros((M, K + 32), dtype=torch.uint8 if dtype == "f8" else Ad.dtype, device="cuda")
+    big[:, :K] = Ad.view(torch.uint8) if dtype == "f8" else Ad
+    start = np.random.default_rng(251).permutation(K).astype(np.int32)
+    got = search_on_a_copy((big.view(torch.float8_e4m3fn) if dtype == "f8" else big)[:, :K], start, 2)
+    assert np.array_equal(got.cpu().numpy(), oracle.permute_search(A, dtype, sweeps=2, perm=start))
 
 
 @pytest.mark.parametrize("dtype,K", [("bf16", 4096), ("f16", 4112), ("i8", 8192), ("f8", 8192)])
@@ -226,8 +254,7 @@ def test_permute_search_in_place_and_on_a_copy(dtype, M, K):
         A = np.where(A % 3, np.int8(-128), A)                    # the largest magnitude in most places
     Ad, lib = to_gpu(A, dtype), sp24.lib()
     start = np.random.default_rng(211).permutation(K).astype(np.int32)
-    copied, placed = sp24.sp24_permute_search(Ad, sweeps=2, perm=dev_perm(start)), dev_perm(start)
-    assert lib.sp24_permute_search_workspace_bytes(M, K, sp24._DT[Ad.dtype]) > 0
+    copied, placed = search_on_a_copy(Ad, start, 2), dev_perm(start)
     assert lib.sp24_permute_search(Ad.data_ptr(), placed.data_ptr(), M, K, K, sp24._DT[Ad.dtype], 2, sp24._stream()) == 0
     torch.cuda.synchronize()
     assert torch.equal(copied, placed)
@@ -235,12 +262,14 @@ def test_permute_search_in_place_and_on_a_copy(dtype, M, K):
 
 
 # few rows: in place from the order of memory, on a copy from a given one (floats, many columns), in place both ways (two or three rounds; int8 from 193
-# pairs on)
+# pairs on; small matrices, unless a graph is recorded)
 @pytest.mark.parametrize("dtype,M,K,default,given", [("bf16", 300, 4096, False, True), ("f16", 401, 4096, True, True), ("bf16", 600, 8192, False, True),
                                                      ("i8", 300, 4096, True, True), ("i8", 255, 2048, False, False), ("i8", 256, 2048, True, True),
-                                                     ("bf16", 255, 32, False, False), ("f16", 256, 32, True, True)])
+                                                     ("bf16", 255, 32, False, False), ("f16", 257, 32, True, True),
+                                                     ("f8", 256, 512, False, False), ("bf16", 257, 512, True, True), ("f16", 128, 1024, False, False),
+                                                     ("f16", 129, 1024, True, True)])
 def test_permute_search_of_few_rows_by_either_route(dtype, M, K, default, given):
-    A = synth.make(NAME_OF[dtype], M=M, N=16, K=K, seed=220)[0]
+    A = synth.make(NAME_OF[dtype], M=M, N=16, K=K, seed=220)[0] if dtype != "f8" else synth.f64_to_f8_bits(np.random.default_rng(220).standard_normal((M, K)))
     Ad = to_gpu(A, dtype)
     assert (sp24._search_workspace(Ad, True) is not None, sp24._search_workspace(Ad, False) is not None) == (default, given)
     first = sp24.sp24_permute_search(Ad)
